@@ -34,6 +34,7 @@ namespace pf {
 
 int decode_dims(const pf_decode_config* c, DecodeDims* d, const char** why) {
   *why = nullptr;
+  memset(d, 0, sizeof(*d));  // the sizing memo compares whole structs
   if (!c) return *why = "config is NULL", PF_ERR_INVALID_ARG;
   if (c->dtype != PF_FP32 && c->dtype != PF_BF16) return *why = "dtype must be PF_FP32 or PF_BF16", PF_ERR_INVALID_ARG;
   if (c->batch < 1 || c->d_model < 1 || c->n_heads < 1 || c->head_dim < 1)
@@ -737,19 +738,25 @@ static size_t decode_gemm_need(const DecodeDims& d, const DecodeWs& W) {
 }
 
 DecodeWs decode_ws(const DecodeDims& d) {
-  // memoised: the sizing sweep is pure arithmetic but runs on every call
-  static thread_local DecodeDims last{};
-  static thread_local size_t last_need = 0;
-  static thread_local bool have = false;
+  // memoised for the last few configs of the thread: the sizing sweep plans
+  // every append size (about 0.25 ms) and its result is asked for on every
+  // call; sessions of several configs may take turns
+  constexpr int kMemo = 8;
+  static thread_local DecodeDims seen[kMemo];
+  static thread_local size_t seen_need[kMemo];
+  static thread_local int count = 0, next = 0;
   DecodeWs w = decode_ws_layout(d, kDecodeMaxSplits, d.append_rows);
-  size_t need;
-  if (have && memcmp(&last, &d, sizeof(d)) == 0) {
-    need = last_need;
+  size_t need = 0;
+  int at = 0;
+  while (at < count && memcmp(&seen[at], &d, sizeof(d)) != 0) ++at;
+  if (at < count) {
+    need = seen_need[at];
   } else {
     need = decode_gemm_need(d, w);
-    last = d;
-    last_need = need;
-    have = true;
+    seen[next] = d;
+    seen_need[next] = need;
+    next = (next + 1) % kMemo;
+    count = std::min(count + 1, kMemo);
   }
   w.bytes = w.gemm + align256(need);
   return w;

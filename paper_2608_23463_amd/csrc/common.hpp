@@ -6,7 +6,13 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace pf {
+
+// Epilogues whose GEMMs are also launched in groups (a kernel variant each).
+template <class Epi>
+struct GemmGrouped : std::false_type {};
 
 typedef __bf16 bf16;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));

@@ -530,6 +530,9 @@ struct EpiCache {
   }
 };
 
+template <typename T>
+struct GemmGrouped<EpiCache<T>> : std::true_type {};
+
 // ---- launch sequences ---------------------------------------------------------
 
 template <typename T>
@@ -558,7 +561,9 @@ static void append_impl(Runner& run, const DecodeDims& d, const DecodeWs& W, con
     }
     const pf_linear* maps[2] = {&w->k_proxy, &w->v_proxy};
     void* caches[2] = {st.k_cache, st.v_cache};
-    for (int i = 0; i < 2; ++i) {  // cached rows K_p, V_p (Eq. 21)
+    GemmProblem prs[2];
+    EpiCache<T> epis[2];
+    for (int i = 0; i < 2; ++i) {  // cached rows K_p, V_p (Eq. 21), one launch
       GemmProblem pr{};
       pr.a = zin;
       pr.lda = d.d;
@@ -567,10 +572,11 @@ static void append_impl(Runner& run, const DecodeDims& d, const DecodeWs& W, con
       pr.M = rows;
       pr.N = d.d;
       pr.K = d.d;
-      EpiCache<T> e{reinterpret_cast<T*>(caches[i]), reinterpret_cast<const T*>(maps[i]->b), st.n_cap, st.n, nblk, r0,
-                    d.nh, d.dh, pos};
-      run.gemm<T, LAYOUT_K, LAYOUT_K>("append_kv_gemm", pr, e);
+      prs[i] = pr;
+      epis[i] = EpiCache<T>{reinterpret_cast<T*>(caches[i]), reinterpret_cast<const T*>(maps[i]->b), st.n_cap, st.n,
+                            nblk, r0, d.nh, d.dh, pos};
     }
+    run.gemm_group<T, LAYOUT_K, LAYOUT_K>("append_kv_gemm", prs, epis, 2);
   }
 }
 

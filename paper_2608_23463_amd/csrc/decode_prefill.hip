@@ -546,6 +546,8 @@ static void prefill_impl(Runner& run, const DecodeDims& d, const pf_decode_weigh
   // exp2 units
   T* outs[3] = {nullptr, k, vrow ? vt : nullptr};
   T* outs_t[3] = {nullptr, nullptr, vrow ? nullptr : vt};
+  GemmProblem qkv[3];
+  EpiHeads<T> qkv_e[3];
   for (int i = 0; i < 3; ++i) {
     GemmProblem pr{};
     pr.a = u;
@@ -560,8 +562,10 @@ static void prefill_impl(Runner& run, const DecodeDims& d, const pf_decode_weigh
       e.outs = q;
       e.scale = (float)(1.4426950408889634 / std::sqrt((double)d.dh));
     }
-    run.gemm<T, LAYOUT_K, LAYOUT_K>("prefill_qkv_gemm", pr, e);
+    qkv[i] = pr;
+    qkv_e[i] = e;
   }
+  run.gemm_group<T, LAYOUT_K, LAYOUT_K>("prefill_qkv_gemm", qkv, qkv_e, 3);
   {
     GemmProblem pr{};
     pr.a = u;

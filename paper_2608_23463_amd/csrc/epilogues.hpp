@@ -183,6 +183,9 @@ struct EpiHeads {
   }
 };
 
+template <typename T>
+struct GemmGrouped<EpiHeads<T>> : std::true_type {};
+
 // Output map of the interaction with the token-causal shift folded in: row
 // r = b*m + i of H-bar goes to row r + 1 of S (the proxy block i + 1 receives);
 // the row i = m - 1 has no receiver and instead clears row b*m (block 0
@@ -386,5 +389,8 @@ struct EpiF32 {
     store8(p, v);
   }
 };
+
+template <>
+struct GemmGrouped<EpiF32> : std::true_type {};
 
 }  // namespace pf

@@ -11,6 +11,7 @@
 // (A2[m * lda2 + k - a_ksplit]), and for k >= b_ksplit the B values from B2.
 // Used for the gate input [X, Delta], and for the split-precision products
 // [X_hi | X_lo] [W | W]^T = X W^T to ~16 mantissa bits.
+// Several problems of one tile shape and layout can share a launch (GemmArgs).
 // Split-K: gridDim.z slices of the reduction range, each slice handing its
 // partial sums to the epilogue (normally a store into an fp32 workspace,
 // reduced afterwards in a fixed order, so results are deterministic).
@@ -58,6 +59,16 @@ struct GemmParams {
   int tiles_m, tiles_n;
   int group_m;
   int64_t batch_a, batch_b;  // element offsets of batch blockIdx.y in A and B (direct kernel)
+  float* colsum;       // bf16 M/N-major A: sums of A over each K slice [slice][M] (NULL: not formed)
+};
+
+// Kernel arguments of one launch over up to G problems of one tile shape and
+// layout: blockIdx.y picks the problem (with G = 1 it is the batch index).
+constexpr int kGemmGroup = 4;
+template <class Epi, int G>
+struct GemmArgs {
+  GemmParams p[G];
+  Epi e[G];
 };
 
 template <typename T, int BM, int BN, int BK, int WM, int WN>
@@ -375,9 +386,10 @@ __device__ __forceinline__ void gemm_store(f32x16 (&acc)[S::kFM][S::kFN], float*
 // others still multiply. The epilogue's global reads (Epi::pre) run kAhead
 // steps ahead of their use; their coordinates are clamped into the matrix
 // (a clamped chunk's values are not used), which needs N >= 8.
+// `rot`: acc[i] holds row block (i + rot) % kFM of the wave's tile.
 template <class S, int kRows, class Epi>
 __device__ __forceinline__ void gemm_store_wave(f32x16 (&acc)[S::kFM][S::kFN], float* region, const GemmParams& p,
-                                                int row0, int col0, int lane, const Epi& epi) {
+                                                int row0, int col0, int lane, const Epi& epi, int rot = 0) {
   constexpr int kTN = S::kTN;
   constexpr int kSRow = kTN + 8;               // rows r and r + 4 land on disjoint banks
   constexpr int kCpr = kTN / 8;                // 8-column chunks per row
@@ -393,10 +405,11 @@ __device__ __forceinline__ void gemm_store_wave(f32x16 (&acc)[S::kFM][S::kFN], f
   typename EpiCol<Epi>::type colv;
   if (p.N >= 8) epi_col(epi, min(col, p.N - 8), colv);
   typename EpiPre<Epi>::type pre[kAhead + 1][kPer];
+  auto step_row = [&](int step) { return row0 + ((step / kHalves + rot) % S::kFM) * 32 + (step % kHalves) * kRows; };
   auto issue = [&](int step, typename EpiPre<Epi>::type (&q)[kPer]) {
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
-      const int row = row0 + step * kRows + rl0 + u * kRowsPerPass;
+      const int row = step_row(step) + rl0 + u * kRowsPerPass;
       epi_pre(epi, min(row, p.M - 1), min(col, p.N - 8), q[u]);
     }
   };
@@ -435,7 +448,7 @@ __device__ __forceinline__ void gemm_store_wave(f32x16 (&acc)[S::kFM][S::kFN], f
     asm volatile("" ::: "memory");
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
-      const int row = row0 + step * kRows + rl0 + u * kRowsPerPass;
+      const int row = step_row(step) + rl0 + u * kRowsPerPass;
       if (row >= p.M || col >= p.N) continue;
       if (col + 8 <= p.N) {
         epi_vec8(epi, row, col, v[u], colv, pre[step % (kAhead + 1)][u]);
@@ -643,11 +656,25 @@ __device__ __forceinline__ void wait_stages(int pending) {
 // FAST (K-major operands whose slices hold whole BK tiles): the buffer
 // descriptors of A, A2, B and B2 are built once per workgroup, their ranges
 // clamp the tile rows, and a K step only moves the scalar offset of the loads.
+//
+// Column sums of A (weight gradients: A is the output gradient, so these are
+// the bias gradient): with both operands M/N-major every A fragment passes
+// through registers anyway, so the wave adds up the eight k values of one of
+// its row blocks per k-step (16 vector instructions under 8 or 4 MFMAs) and
+// the workgroups of the first column tile write the sums. Which block a wave
+// sums is its column index, so the waves of a row share the work; the blocks
+// are held rotated by that index to keep the choice out of the loop. This
+// replaces two further launches and one more read of A per bias.
 template <typename T, int BM, int BN, int BK, int WM, int WN, int NS, class Epi, int LA = LAYOUT_K,
-          int LB = LAYOUT_K, bool FAST = false>
+          int LB = LAYOUT_K, bool FAST = false, int G = 1>
 __global__ void __launch_bounds__(WM* WN* kWave)
     __attribute__((amdgpu_waves_per_eu(WM* WN / 4, (BM >= 256 ? 1 : 2) * WM * WN / 4)))
-    gemm_direct_kernel(const GemmParams p, const Epi epi) {
+    gemm_direct_kernel(const GemmArgs<Epi, G> args) {
+  const int prob = G == 1 ? 0 : (int)blockIdx.y;
+  const GemmParams& p = args.p[prob];
+  const Epi& epi = args.e[prob];
+  if (G > 1 && (int)blockIdx.x >= p.tiles_m * p.tiles_n) return;  // a smaller problem of the group
+  if (G > 1 && (int)blockIdx.z * p.k_slice >= p.K && blockIdx.z > 0) return;
   typedef DirectShape<T, BM, BN, BK, WM, WN, NS, LA, LB> D;
   typedef typename D::S S;
   typedef typename D::OA OA;
@@ -693,11 +720,12 @@ __global__ void __launch_bounds__(WM* WN* kWave)
   // k0, each read from column m0 (n0); only the rows below kend and the
   // columns below M (N) of the last row are in range.
   // batch blockIdx.y of a batched problem starts at its own A and B
-  const char* a1 = reinterpret_cast<const char*>(p.a) + (int64_t)blockIdx.y * p.batch_a * (int64_t)sizeof(T) +
+  const int64_t batch = G == 1 ? (int64_t)blockIdx.y : 0;
+  const char* a1 = reinterpret_cast<const char*>(p.a) + batch * p.batch_a * (int64_t)sizeof(T) +
                    (OA::kMN ? m0 * (int64_t)sizeof(T) : m0 * lda_b);
   const char* a2 = p.a2 ? reinterpret_cast<const char*>(p.a2) + (OA::kMN ? m0 * (int64_t)sizeof(T) : m0 * lda_b)
                         : nullptr;
-  const char* b1 = reinterpret_cast<const char*>(p.b) + (int64_t)blockIdx.y * p.batch_b * (int64_t)sizeof(T) +
+  const char* b1 = reinterpret_cast<const char*>(p.b) + batch * p.batch_b * (int64_t)sizeof(T) +
                    (OB::kMN ? n0 * (int64_t)sizeof(T) : n0 * ldb_b);
   const char* b2 = p.b2 ? reinterpret_cast<const char*>(p.b2) + (OB::kMN ? n0 * (int64_t)sizeof(T) : n0 * ldb_b)
                         : nullptr;
@@ -826,11 +854,15 @@ __global__ void __launch_bounds__(WM* WN* kWave)
     return f;
   };
   typename MM::frag fa[2][S::kFM], fb[2][S::kFN];
+  constexpr bool kColsum = OA::kMN && OB::kMN;
+  const int rot = kColsum ? wn % S::kFM : 0;
+  float csum = 0.0f;  // of row block `rot`, this lane's row and k half
   auto read_frags = [&](int tile, int st, int buf) {
     const T* cur = smem + (tile % NS) * D::kStage;
     if constexpr (OA::kMN) {
 #pragma unroll
-      for (int i = 0; i < S::kFM; ++i) fa[buf][i] = frag_mn(cur, BM, wm * S::kTM + i * 32, st, OA{});
+      for (int i = 0; i < S::kFM; ++i)
+        fa[buf][i] = frag_mn(cur, BM, wm * S::kTM + (kColsum ? (i + rot) % S::kFM : i) * 32, st, OA{});
     } else {
       const T* sa = cur + (wm * S::kTM + frow) * BK;
 #pragma unroll
@@ -851,6 +883,12 @@ __global__ void __launch_bounds__(WM* WN* kWave)
     for (int i = 0; i < S::kFM; ++i)
 #pragma unroll
       for (int j = 0; j < S::kFN; ++j) acc[i][j] = MM::mma(fa[buf][i], fb[buf][j], acc[i][j]);
+    if constexpr (kColsum) {
+      float v[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = to_f32(fa[buf][0][e]);
+      csum += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+    }
   };
   // reads per k-step: one per K-major fragment, two per M/N-major one
   constexpr int kReads = S::kFM * (OA::kMN ? 2 : 1) + S::kFN * (OB::kMN ? 2 : 1);
@@ -898,32 +936,92 @@ __global__ void __launch_bounds__(WM* WN* kWave)
   constexpr int kRows = D::kEpiRegion16 <= D::kStage * sizeof(T) ? 16 : 8;
   static_assert(D::kEpiRegion16 / (16 / kRows) <= D::kStage * sizeof(T), "wave epilogue regions must fit one stage");
   float* region = reinterpret_cast<float*>(smem + free_stage * D::kStage) + wave * kRows * (S::kTN + 8);
-  gemm_store_wave<S, kRows>(acc, region, p, m0 + wm * S::kTM, n0 + wn * S::kTN, lane, epi);
+  if constexpr (kColsum) {
+    if (p.colsum && tn == 0 && wn < S::kFM) {
+      csum += __shfl_xor(csum, 32);
+      const int row = m0 + wm * S::kTM + rot * 32 + frow;
+      if (lane < 32 && row < p.M) p.colsum[(int64_t)blockIdx.z * p.M + row] = csum;
+    }
+  }
+  gemm_store_wave<S, kRows>(acc, region, p, m0 + wm * S::kTM, n0 + wn * S::kTN, lane, epi, rot);
 }
 
-// Fixed-order reduction of split-K partials ws[s][M][N], then the epilogue
-// (8 consecutive columns per thread when N is a multiple of 8).
+// Fixed-order reduction of split-K partials ws[s][M][N] through the epilogue.
+// Eight consecutive columns are summed by `zl` lanes of one wave (a power of
+// two): lane group z adds slices z, z + zl, ... in order, four loads in flight
+// each, and a butterfly joins the groups, so the order is fixed and the serial
+// chain is splits / zl loads instead of splits. A small result with many
+// slices was bound by that chain (64 slices of [10, 512]: 20 us with one lane
+// per chunk, 5 us here); the host takes more lanes while the result has too
+// few chunks to fill the chip. The blocks past `blocks` sum the column sums
+// [slice][M] of A the same way, one row per thread. blockIdx.y: the problem.
 template <class Epi>
-__global__ void __launch_bounds__(256) splitk_reduce_kernel(const float* __restrict__ ws, int splits, int M,
-                                                            int N, const Epi epi) {
+struct ReduceArgs {
+  const float* ws[kGemmGroup];
+  const float* cs_part[kGemmGroup];  // NULL: no column sums
+  float* cs_out[kGemmGroup];
+  int splits[kGemmGroup], M[kGemmGroup], N[kGemmGroup];
+  int blocks, zl;
+  Epi e[kGemmGroup];
+};
+
+template <class Epi>
+__global__ void __launch_bounds__(256) splitk_reduce_kernel(const ReduceArgs<Epi> args) {
+  const int g = blockIdx.y;
+  const int splits = args.splits[g], M = args.M[g], N = args.N[g];
+  const float* __restrict__ ws = args.ws[g];
+  const Epi& epi = args.e[g];
+  if ((int)blockIdx.x >= args.blocks) {
+    const float* part = args.cs_part[g];
+    const int r = ((int)blockIdx.x - args.blocks) * 256 + (int)threadIdx.x;
+    if (!part || r >= M) return;
+    float s = 0.0f;
+#pragma unroll 8
+    for (int z = 0; z < splits; ++z) s += part[(int64_t)z * M + r];
+    args.cs_out[g][r] = s;
+    return;
+  }
   const int64_t total = (int64_t)M * N;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   if ((N & 7) == 0) {
-    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < total / 8; c += stride) {
-      const int64_t idx = c * 8;
+    const int zl = args.zl, per = kWave / zl;  // chunks per wave pass
+    const int lane = threadIdx.x & 63, zi = lane / per;
+    const int64_t stride = (int64_t)args.blocks * 4 * per;
+    const int64_t c0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * per + lane % per;
+    for (int64_t cb = c0 - lane % per; cb < total / 8; cb += stride) {  // wave-uniform trip count
+      const int64_t c = cb + lane % per;
+      const bool live = c < total / 8;
+      const float* src = ws + (live ? c : 0) * 8;
       float v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-      for (int z = 0; z < splits; ++z) {
+      int z = zi;
+      for (; z + 3 * zl < splits; z += 4 * zl) {
+        float t[4][8];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) load8(src + (int64_t)(z + u * zl) * total, t[u]);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] += t[u][e];
+      }
+      for (; z < splits; z += zl) {
         float t[8];
-        load8(ws + (int64_t)z * total + idx, t);
+        load8(src + (int64_t)z * total, t);
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] += t[e];
       }
-      epi.vec8((int)(idx / N), (int)(idx % N), v);
+      for (int off = per; off < kWave; off <<= 1)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] += __shfl_xor(v[e], off);
+      if (live && zi == 0) {
+        const int64_t idx = c * 8;
+        epi.vec8((int)(idx / N), (int)(idx % N), v);
+      }
     }
     return;
   }
+  const int64_t stride = (int64_t)args.blocks * blockDim.x;
   for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total; idx += stride) {
     float s = 0.0f;
+#pragma unroll 8
     for (int z = 0; z < splits; ++z) s += ws[(int64_t)z * total + idx];
     epi((int)(idx / N), (int)(idx % N), s);
   }
@@ -946,6 +1044,11 @@ struct EpiPartial {
   }
 };
 
+template <>
+struct GemmGrouped<EpiPartial> : std::true_type {};
+template <class Epi>
+constexpr bool kGemmGrouped = GemmGrouped<Epi>::value;
+
 // ---- host side --------------------------------------------------------------
 
 struct GemmProblem {
@@ -965,6 +1068,10 @@ struct GemmProblem {
   // (elements); the epilogue finds z in blockIdx.y
   int batch = 1;
   int64_t batch_a = 0, batch_b = 0;
+  // bf16, both operands M/N-major: column sums of A to colsum [M] (NULL: not
+  // wanted), through cs_part [slices][M] when K is split
+  float* colsum = nullptr;
+  float* cs_part = nullptr;
 };
 
 // Tile configuration chosen for a problem.
@@ -977,22 +1084,34 @@ struct GemmPlan {
   int k_slice;
 };
 
+// One plan for a group of problems launched together (their tiles fill the
+// chip together; each has its own k_slice).
 template <typename T>
-inline GemmPlan plan_gemm(const GemmProblem& pr, int num_cu) {
+inline GemmPlan plan_gemm(const GemmProblem* prs, int count, int num_cu) {
   GemmPlan pl;
-  const int64_t mn = (int64_t)pr.M * pr.N;
+  int64_t mn = 0, t256 = 0;
+  int min_m = prs[0].M, min_n = prs[0].N, max_mn = 0, max_k = 0;
+  for (int i = 0; i < count; ++i) {
+    const GemmProblem& q = prs[i];
+    mn += (int64_t)q.M * q.N;
+    t256 += (int64_t)((q.M + 255) / 256) * ((q.N + 255) / 256);
+    min_m = std::min(min_m, q.M);
+    min_n = std::min(min_n, q.N);
+    max_mn = std::max(max_mn, std::max(q.M, q.N));
+    max_k = std::max(max_k, q.K);
+  }
   if (sizeof(T) == 4) {
     pl.tile = TILE_128x128;
     pl.bm = pl.bn = 128;
     pl.bk = 32;
-  } else if (pr.M >= 256 && pr.N >= 256 &&
+  } else if (min_m >= 256 && min_n >= 256 &&
              (mn >= (int64_t)256 * 256 * num_cu ||
               // long reductions: 256x256 tiles split along K still fill the chip
-              (int64_t)pr.K * (((pr.M + 255) / 256) * ((pr.N + 255) / 256)) >= (int64_t)num_cu * 64 * 64)) {
+              (int64_t)max_k * t256 >= (int64_t)num_cu * 64 * 64)) {
     pl.tile = TILE_256x256;
     pl.bm = pl.bn = 256;
     pl.bk = 64;
-  } else if (mn >= (int64_t)128 * 128 * num_cu / 2 || pr.M > 64 || pr.N > 64) {
+  } else if (mn >= (int64_t)128 * 128 * num_cu / 2 || max_mn > 64) {
     pl.tile = TILE_128x128;
     pl.bm = pl.bn = 128;
     pl.bk = 64;
@@ -1001,21 +1120,51 @@ inline GemmPlan plan_gemm(const GemmProblem& pr, int num_cu) {
     pl.bm = pl.bn = 64;
     pl.bk = 64;
   }
-  const int64_t tiles = (int64_t)((pr.M + pl.bm - 1) / pl.bm) * ((pr.N + pl.bn - 1) / pl.bn) * pr.batch;
-  const int kblocks = (pr.K + pl.bk - 1) / pl.bk;
+  int64_t tiles = 0;
+  int batch = 1;
+  for (int i = 0; i < count; ++i) {
+    tiles += (int64_t)((prs[i].M + pl.bm - 1) / pl.bm) * ((prs[i].N + pl.bn - 1) / pl.bn) * prs[i].batch;
+    batch = std::max(batch, prs[i].batch);
+  }
+  const int kblocks = (max_k + pl.bk - 1) / pl.bk;
   int splits = 1;
   // Deterministic split-K when the tile grid cannot fill the chip and the
   // reduction is long enough for each slice to stay efficient.
-  while (pr.batch == 1 && tiles * splits < num_cu && kblocks / (splits * 2) >= 8) splits *= 2;
+  while (batch == 1 && tiles * splits < num_cu && kblocks / (splits * 2) >= 8) splits *= 2;
   const int kb_per = (kblocks + splits - 1) / splits;
   pl.k_slice = kb_per * pl.bk;
   pl.splits = (kblocks + kb_per - 1) / kb_per;
   return pl;
 }
 
-template <typename T, int BM, int BN, int BK, int WM, int WN, int LA, int LB, class Epi>
-inline hipError_t launch_gemm_tile(const GemmProblem& pr, const GemmPlan& pl, const Epi& epi,
-                                   hipStream_t stream) {
+// Reduction length per slice of one problem of a group, and its slice count.
+inline int plan_k_slice(const GemmProblem& pr, const GemmPlan& pl) {
+  const int kblocks = std::max(1, (pr.K + pl.bk - 1) / pl.bk);
+  return (kblocks + pl.splits - 1) / pl.splits * pl.bk;
+}
+inline int plan_splits(const GemmProblem& pr, const GemmPlan& pl) {
+  const int ks = plan_k_slice(pr, pl);
+  return std::max(1, (pr.K + ks - 1) / ks);
+}
+// Floats of split-K workspace one problem of a planned group takes.
+inline size_t plan_partials(const GemmProblem& pr, const GemmPlan& pl) {
+  return ((size_t)plan_splits(pr, pl) * pr.M * pr.N + 7) / 8 * 8;  // the next problem's stay 32-byte aligned
+}
+
+template <typename T, int BM, int BN, int BK, int LA, int LB>
+inline bool gemm_runs_direct(const GemmProblem& pr, int k_slice) {
+  const bool aligned_split = (pr.a_ksplit >= pr.K || pr.a_ksplit % BK == 0) &&
+                             (pr.b_ksplit >= pr.K || pr.b_ksplit % BK == 0) &&
+                             (!pr.a2 || pr.lda2 == pr.lda) && (!pr.b2 || pr.ldb2 == pr.ldb);
+  if (!aligned_split || k_slice % BK != 0) return false;
+  if (LA == LAYOUT_K && LB == LAYOUT_K) return true;
+  // M/N-major operands through LDS transpose reads: rows of such an
+  // operand start 16-byte aligned and hold at least one tile width
+  return sizeof(T) == 2 && BM >= 128 && BN >= 128 && (LA == LAYOUT_K || (pr.lda % 8 == 0 && pr.lda >= BM)) &&
+         (LB == LAYOUT_K || (pr.ldb % 8 == 0 && pr.ldb >= BN));
+}
+
+inline GemmParams gemm_params(const GemmProblem& pr, int BM, int BN, int BK, int k_slice, size_t esize) {
   GemmParams p;
   p.a = pr.a;
   p.lda = pr.lda;
@@ -1030,93 +1179,147 @@ inline hipError_t launch_gemm_tile(const GemmProblem& pr, const GemmPlan& pl, co
   p.M = pr.M;
   p.N = pr.N;
   p.K = pr.K;
-  p.k_slice = pl.k_slice;
+  p.k_slice = k_slice;
   p.tiles_m = (pr.M + BM - 1) / BM;
   p.tiles_n = (pr.N + BN - 1) / BN;
   // row tiles per column sweep: the sweep's A rows (group_m x BM rows of one
   // K slice) fit about 4 MiB, one XCD's L2; 2 .. 8 (long reductions such as
   // the compression take 2, K = 2048 takes 4, K = 1024 keeps 8)
   p.group_m = (int)std::min<int64_t>(
-      8, std::max<int64_t>(2, ((int64_t)4 << 20) / ((int64_t)BM * std::max(pl.k_slice, BK) * (int64_t)sizeof(T))));
+      8, std::max<int64_t>(2, ((int64_t)4 << 20) / ((int64_t)BM * std::max(k_slice, BK) * (int64_t)esize)));
   p.batch_a = pr.batch_a;
   p.batch_b = pr.batch_b;
-  dim3 grid(p.tiles_m * p.tiles_n, pr.batch, pl.splits);
-  const bool aligned_split = (pr.a_ksplit >= pr.K || pr.a_ksplit % BK == 0) &&
-                             (pr.b_ksplit >= pr.K || pr.b_ksplit % BK == 0) &&
-                             (!pr.a2 || pr.lda2 == pr.lda) && (!pr.b2 || pr.ldb2 == pr.ldb);
+  p.colsum = pr.colsum;
+  return p;
+}
+
+// Launches `count` problems (1, or up to kGemmGroup unbatched ones) as one
+// grid of the direct kernel, or one after the other on the register-path
+// kernel where the direct one does not take them.
+template <typename T, int BM, int BN, int BK, int WM, int WN, int LA, int LB, class Epi>
+inline hipError_t launch_gemm_tile(const GemmProblem* prs, int count, const GemmPlan& pl, const Epi* epis,
+                                   hipStream_t stream) {
+  bool direct = true, whole = true;
+  int tiles = 0, splits = 1;
+  for (int i = 0; i < count; ++i) {
+    const int ks = plan_k_slice(prs[i], pl);
+    direct = direct && gemm_runs_direct<T, BM, BN, BK, LA, LB>(prs[i], ks);
+    whole = whole && prs[i].K % BK == 0;  // every slice holds whole tiles
+    tiles = std::max(tiles, ((prs[i].M + BM - 1) / BM) * ((prs[i].N + BN - 1) / BN));
+    splits = std::max(splits, plan_splits(prs[i], pl));
+  }
   // 256x256 tiles run as 8 waves of 128x64: two waves per SIMD, so one
   // wave's MFMAs cover the other's load issue and barrier waits.
   constexpr int DWN = (BM == 256 && BN == 256) ? 4 : WN;
-  if constexpr (LA == LAYOUT_K && LB == LAYOUT_K) {
-    if (aligned_split && pl.k_slice % BK == 0) {
-      if (pr.K % BK == 0)  // every slice holds whole tiles
-        hipLaunchKernelGGL((gemm_direct_kernel<T, BM, BN, BK, WM, DWN, 2, Epi, LAYOUT_K, LAYOUT_K, true>), grid,
-                           dim3(WM * DWN * kWave), 0, stream, p, epi);
-      else
-        hipLaunchKernelGGL((gemm_direct_kernel<T, BM, BN, BK, WM, DWN, 2, Epi>), grid, dim3(WM * DWN * kWave), 0,
-                           stream, p, epi);
-      return hipGetLastError();
-    }
-  } else if constexpr (sizeof(T) == 2 && BM >= 128 && BN >= 128) {
-    // M/N-major operands through LDS transpose reads: rows of such an
-    // operand start 16-byte aligned and hold at least one tile width
-    const bool rows_ok = (LA == LAYOUT_K || (pr.lda % 8 == 0 && pr.lda >= BM)) &&
-                         (LB == LAYOUT_K || (pr.ldb % 8 == 0 && pr.ldb >= BN));
-    if (aligned_split && pl.k_slice % BK == 0 && rows_ok) {
-      hipLaunchKernelGGL((gemm_direct_kernel<T, BM, BN, BK, WM, DWN, 2, Epi, LA, LB>), grid,
-                         dim3(WM * DWN * kWave), 0, stream, p, epi);
-      return hipGetLastError();
+  constexpr bool kCanDirect = (LA == LAYOUT_K && LB == LAYOUT_K) || (sizeof(T) == 2 && BM >= 128 && BN >= 128);
+  if constexpr (kCanDirect) {
+    if (direct) {
+      auto go = [&](auto group) {
+        constexpr int G = decltype(group)::value;
+        GemmArgs<Epi, G> args;
+        for (int i = 0; i < count; ++i) {
+          args.p[i] = gemm_params(prs[i], BM, BN, BK, plan_k_slice(prs[i], pl), sizeof(T));
+          args.e[i] = epis[i];
+        }
+        const dim3 grid(tiles, G == 1 ? prs[0].batch : count, splits), block(WM * DWN * kWave);
+        if constexpr (LA == LAYOUT_K && LB == LAYOUT_K) {
+          if (whole) {
+            hipLaunchKernelGGL((gemm_direct_kernel<T, BM, BN, BK, WM, DWN, 2, Epi, LAYOUT_K, LAYOUT_K, true, G>), grid,
+                               block, 0, stream, args);
+            return hipGetLastError();
+          }
+        }
+        hipLaunchKernelGGL((gemm_direct_kernel<T, BM, BN, BK, WM, DWN, 2, Epi, LA, LB, false, G>), grid, block, 0,
+                           stream, args);
+        return hipGetLastError();
+      };
+      if (count == 1) return go(std::integral_constant<int, 1>{});
+      if constexpr (kGemmGrouped<Epi>) return go(std::integral_constant<int, kGemmGroup>{});
     }
   }
-  if (pr.batch != 1) return hipErrorInvalidValue;  // batches run on the direct kernel only
-  hipLaunchKernelGGL((gemm_kernel<T, BM, BN, BK, WM, WN, LA, LB, Epi>), grid,
-                     dim3(WM * WN * kWave), 0, stream, p, epi);
+  if (count > 1) {
+    for (int i = 0; i < count; ++i) {
+      const hipError_t e = launch_gemm_tile<T, BM, BN, BK, WM, WN, LA, LB>(prs + i, 1, pl, epis + i, stream);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
+  if (prs->batch != 1 || prs->colsum) return hipErrorInvalidValue;  // direct kernel only
+  const GemmParams p = gemm_params(*prs, BM, BN, BK, plan_k_slice(*prs, pl), sizeof(T));
+  hipLaunchKernelGGL((gemm_kernel<T, BM, BN, BK, WM, WN, LA, LB, Epi>),
+                     dim3(p.tiles_m * p.tiles_n, 1, plan_splits(*prs, pl)), dim3(WM * WN * kWave), 0, stream, p, *epis);
   return hipGetLastError();
 }
 
+// Whether every problem of the group runs on the direct kernel.
+template <typename T, int LA, int LB>
+inline bool gemm_plan_direct(const GemmProblem* prs, int count, const GemmPlan& pl) {
+  for (int i = 0; i < count; ++i) {
+    const int ks = plan_k_slice(prs[i], pl);
+    bool ok;
+    if constexpr (sizeof(T) == 4)
+      ok = gemm_runs_direct<T, 128, 128, 32, LA, LB>(prs[i], ks);
+    else if (pl.tile == TILE_256x256)
+      ok = gemm_runs_direct<T, 256, 256, 64, LA, LB>(prs[i], ks);
+    else if (pl.tile == TILE_128x128)
+      ok = gemm_runs_direct<T, 128, 128, 64, LA, LB>(prs[i], ks);
+    else
+      ok = gemm_runs_direct<T, 64, 64, 64, LA, LB>(prs[i], ks);
+    if (!ok) return false;
+  }
+  return true;
+}
+
 template <typename T, int LA, int LB, class Epi>
-inline hipError_t launch_gemm_plan(const GemmProblem& pr, const GemmPlan& pl, const Epi& epi,
+inline hipError_t launch_gemm_plan(const GemmProblem* prs, int count, const GemmPlan& pl, const Epi* epis,
                                    hipStream_t stream) {
   if constexpr (sizeof(T) == 4) {
-    return launch_gemm_tile<T, 128, 128, 32, 2, 2, LA, LB>(pr, pl, epi, stream);
+    return launch_gemm_tile<T, 128, 128, 32, 2, 2, LA, LB>(prs, count, pl, epis, stream);
   } else {
     switch (pl.tile) {
       case TILE_256x256:
-        return launch_gemm_tile<T, 256, 256, 64, 2, 2, LA, LB>(pr, pl, epi, stream);
+        return launch_gemm_tile<T, 256, 256, 64, 2, 2, LA, LB>(prs, count, pl, epis, stream);
       case TILE_128x128:
-        return launch_gemm_tile<T, 128, 128, 64, 2, 2, LA, LB>(pr, pl, epi, stream);
+        return launch_gemm_tile<T, 128, 128, 64, 2, 2, LA, LB>(prs, count, pl, epis, stream);
       default:
-        return launch_gemm_tile<T, 64, 64, 64, 2, 2, LA, LB>(pr, pl, epi, stream);
+        return launch_gemm_tile<T, 64, 64, 64, 2, 2, LA, LB>(prs, count, pl, epis, stream);
     }
   }
 }
 
-// Bytes of fp32 workspace a problem needs for split-K partials.
-template <typename T>
-inline size_t gemm_workspace_bytes(const GemmProblem& pr, int num_cu) {
-  const GemmPlan pl = plan_gemm<T>(pr, num_cu);
-  return pl.splits > 1 ? (size_t)pl.splits * pr.M * pr.N * sizeof(float) : 0;
+// Lanes that share a chunk of the reduction and the blocks it takes: more
+// lanes while the chunks alone leave the chip under four waves per CU.
+inline void plan_reduce(int64_t chunks, int splits, int* zl, int* blocks) {
+  int z = 1;
+  while (z < 16 && 2 * z <= splits && chunks * z < (int64_t)256 * 4 * kWave) z *= 2;
+  *zl = z;
+  *blocks = (int)std::max<int64_t>(1, std::min<int64_t>((chunks * z + 255) / 256, 8192));
 }
 
-// Run C = A B^T through `epi`, splitting K through `ws` when that helps.
-template <typename T, int LA, int LB, class Epi>
-inline hipError_t run_gemm(const GemmProblem& pr, const Epi& epi, float* ws, int num_cu,
-                           hipStream_t stream) {
-  if (pr.M <= 0 || pr.N <= 0) return hipSuccess;
-  GemmPlan pl = plan_gemm<T>(pr, num_cu);
-  if (pl.splits <= 1 || ws == nullptr) {
-    pl.splits = 1;
-    pl.k_slice = ((pr.K + pl.bk - 1) / pl.bk) * pl.bk;
-    if (pl.k_slice == 0) pl.k_slice = pl.bk;
-    return launch_gemm_plan<T, LA, LB>(pr, pl, epi, stream);
+// Joins the split-K partials of a planned group (parts[i]: problem i's
+// [slices][M][N]) through the epilogues.
+template <class Epi>
+inline hipError_t launch_splitk_reduce(const GemmProblem* prs, int count, const GemmPlan& pl, float* const* parts,
+                                       const Epi* epis, hipStream_t stream) {
+  ReduceArgs<Epi> a;
+  int64_t chunks = 0;
+  int cs_rows = 0;
+  for (int i = 0; i < count; ++i) {
+    a.ws[i] = parts[i];
+    a.splits[i] = plan_splits(prs[i], pl);
+    a.M[i] = prs[i].M;
+    a.N[i] = prs[i].N;
+    a.cs_part[i] = prs[i].colsum ? prs[i].cs_part : nullptr;
+    a.cs_out[i] = prs[i].colsum;
+    a.e[i] = epis[i];
+    if (prs[i].colsum) cs_rows = std::max(cs_rows, prs[i].M);
+    const int64_t mn = (int64_t)prs[i].M * prs[i].N;
+    chunks = std::max<int64_t>(chunks, prs[i].N % 8 == 0 ? mn / 8 : mn);
   }
-  EpiPartial part{ws, pr.N, (int64_t)pr.M * pr.N};
-  hipError_t e = launch_gemm_plan<T, LA, LB>(pr, pl, part, stream);
-  if (e != hipSuccess) return e;
-  const int64_t total = (int64_t)pr.M * pr.N;
-  const int blocks = (int)std::min<int64_t>((total + 255) / 256, 8192);
-  hipLaunchKernelGGL((splitk_reduce_kernel<Epi>), dim3(blocks), dim3(256), 0, stream, ws, pl.splits,
-                     pr.M, pr.N, epi);
+  plan_reduce(chunks * count, pl.splits, &a.zl, &a.blocks);
+  a.blocks = (a.blocks + count - 1) / count;
+  const dim3 grid(a.blocks + (cs_rows + 255) / 256, count);
+  hipLaunchKernelGGL((splitk_reduce_kernel<Epi>), grid, dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 

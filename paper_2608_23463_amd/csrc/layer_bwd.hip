@@ -166,7 +166,43 @@ __global__ void __launch_bounds__(256) head_gate_bwd_kernel(const T* __restrict_
 }
 
 // Column sums in two fixed-order stages: partial sums over row chunks, then
-// the sum of the partials in chunk order.
+// the sum of the partials in chunk order. Used where the weight gradient's
+// GEMM does not form them itself (fp32, and bf16 widths under its tiles).
+// Bound by the read of `in`; a block covers 64 columns with 32 row streams of
+// 8 columns (n and ld multiples of 8) so narrow matrices still use every
+// thread, and the streams are joined through LDS.
+template <typename T>
+__global__ void __launch_bounds__(256) colsum_partial8_kernel(const T* __restrict__ in, int64_t rows, int n,
+                                                              int64_t ld, int64_t rows_per_chunk,
+                                                              float* __restrict__ part) {
+  __shared__ float sums[32][64 + 4];
+  const int cg = threadIdx.x & 7, rl = threadIdx.x >> 3;
+  const int c = blockIdx.x * 64 + cg * 8;
+  const int chunk = blockIdx.y;
+  const int64_t r0 = (int64_t)chunk * rows_per_chunk;
+  const int64_t r1 = std::min<int64_t>(rows, r0 + rows_per_chunk);
+  float s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  if (c < n) {
+#pragma unroll 4
+    for (int64_t r = r0 + rl; r < r1; r += 32) {
+      float v[8];
+      load8(in + r * ld + c, v);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s[e] += v[e];
+    }
+  }
+  store8(&sums[rl][cg * 8], s);
+  __syncthreads();
+  if (threadIdx.x < 64 && blockIdx.x * 64 + threadIdx.x < n) {
+    float o = 0.0f;
+#pragma unroll 8
+    for (int k = 0; k < 32; ++k) o += sums[k][threadIdx.x];
+    part[(int64_t)chunk * n + blockIdx.x * 64 + threadIdx.x] = o;
+  }
+}
+
+// The same for any width and stride (the per-64-row sums of a transpose, a
+// head gate's few columns), one column per thread.
 template <typename T>
 __global__ void __launch_bounds__(256) colsum_partial_kernel(const T* __restrict__ in, int64_t rows, int n,
                                                              int64_t ld, int64_t rows_per_chunk,
@@ -177,56 +213,26 @@ __global__ void __launch_bounds__(256) colsum_partial_kernel(const T* __restrict
   const int64_t r0 = (int64_t)chunk * rows_per_chunk;
   const int64_t r1 = std::min<int64_t>(rows, r0 + rows_per_chunk);
   float s = 0.0f;
+#pragma unroll 4
   for (int64_t r = r0; r < r1; ++r) s += to_f32(in[r * ld + c]);
   part[(int64_t)chunk * n + c] = s;
 }
 
-// The same partial sums, 8 columns per thread (16-byte loads; n and ld
-// multiples of 8) over four independent row streams combined in a fixed
-// order, so the sums stay deterministic.
-template <typename T>
-__global__ void __launch_bounds__(256) colsum_partial8_kernel(const T* __restrict__ in, int64_t rows, int n,
-                                                              int64_t ld, int64_t rows_per_chunk,
-                                                              float* __restrict__ part) {
-  const int c = (blockIdx.x * blockDim.x + threadIdx.x) * 8;
-  const int chunk = blockIdx.y;
-  if (c >= n) return;
-  const int64_t r0 = (int64_t)chunk * rows_per_chunk;
-  const int64_t r1 = std::min<int64_t>(rows, r0 + rows_per_chunk);
-  float s[4][8];
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) s[u][e] = 0.0f;
-  int64_t r = r0;
-  for (; r + 4 <= r1; r += 4) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      float v[8];
-      load8(in + (r + u) * ld + c, v);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) s[u][e] += v[e];
-    }
-  }
-  for (; r < r1; ++r) {
-    float v[8];
-    load8(in + r * ld + c, v);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) s[0][e] += v[e];
-  }
-  float o[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) o[e] = (s[0][e] + s[1][e]) + (s[2][e] + s[3][e]);
-  store8(part + (int64_t)chunk * n + c, o);
-}
-
+// 64 columns per block, four chunk streams per column joined through LDS in
+// a fixed order (one thread per column and a serial chain over 512 chunks
+// took 117 us, whatever the width).
 __global__ void __launch_bounds__(256) colsum_final_kernel(const float* __restrict__ part, int chunks, int n,
                                                            float* __restrict__ out) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= n) return;
+  __shared__ float sums[4][64];
+  const int c = blockIdx.x * 64 + (threadIdx.x & 63), q = threadIdx.x >> 6;
   float s = 0.0f;
-  for (int k = 0; k < chunks; ++k) s += part[(int64_t)k * n + c];
-  out[c] = s;
+  if (c < n) {
+#pragma unroll 16
+    for (int k = q; k < chunks; k += 4) s += part[(int64_t)k * n + c];
+  }
+  sums[q][threadIdx.x & 63] = s;
+  __syncthreads();
+  if (q == 0 && c < n) out[c] = (sums[0][threadIdx.x] + sums[1][threadIdx.x]) + (sums[2][threadIdx.x] + sums[3][threadIdx.x]);
 }
 
 // Gate dgrad epilogue: columns [0, d) are dG W_gx, columns [d, 2d) dG W_gd.
@@ -425,12 +431,12 @@ static void colsum(Runner& run, const char* label, const T* in, int64_t rows, in
   const int64_t rpc = (rows + chunks - 1) / chunks;
   run.launch(label, [&] {
     if (n % 8 == 0 && ld % 8 == 0)
-      hipLaunchKernelGGL((colsum_partial8_kernel<T>), dim3((n / 8 + 255) / 256, chunks), dim3(256), 0, run.stream,
-                         in, rows, n, ld, rpc, part);
+      hipLaunchKernelGGL((colsum_partial8_kernel<T>), dim3((n + 63) / 64, chunks), dim3(256), 0, run.stream, in,
+                         rows, n, ld, rpc, part);
     else
       hipLaunchKernelGGL((colsum_partial_kernel<T>), dim3((n + 255) / 256, chunks), dim3(256), 0, run.stream, in,
                          rows, n, ld, rpc, part);
-    hipLaunchKernelGGL(colsum_final_kernel, dim3((n + 255) / 256), dim3(256), 0, run.stream, part, chunks, n, out);
+    hipLaunchKernelGGL(colsum_final_kernel, dim3((n + 63) / 64), dim3(256), 0, run.stream, part, chunks, n, out);
     return hipGetLastError();
   });
 }
@@ -447,61 +453,107 @@ static void colsum_final(Runner& run, const char* label, int64_t rows, int n, co
   run.launch(label, [&] {
     hipLaunchKernelGGL((colsum_partial_kernel<float>), dim3((n + 255) / 256, groups), dim3(256), 0, run.stream, part,
                        (int64_t)chunks, n, (int64_t)n, per, part2);
-    hipLaunchKernelGGL(colsum_final_kernel, dim3((n + 255) / 256), dim3(256), 0, run.stream, part2, groups, n, out);
+    hipLaunchKernelGGL(colsum_final_kernel, dim3((n + 63) / 64), dim3(256), 0, run.stream, part2, groups, n, out);
     return hipGetLastError();
   });
 }
 
-// dW (fp32 [M, N] with row stride ldo) = sum over rows r of A[r, m] * B[r, n]:
-// both operands are row-major [rows, *] activations, i.e. contiguous along
-// the output dimensions. Over many rows both are first transposed into
-// tr_a / tr_b ([M, rows] and [N, rows], rows padded to a multiple of 8) so the
-// product runs on K-contiguous operands; `a_t` passes an A already
-// transposed into tr_a by the caller. With `db`, the column sums of A (a
-// bias gradient) are formed too, from the transpose's tiles when there is one.
+// One weight gradient dW (fp32 [M, N] with row stride ldo) = sum over rows r
+// of A[r, m] * B[r, n] (both operands row-major [rows, *] activations, i.e.
+// contiguous along the output dimensions), and with `db` the column sums of A
+// (the bias gradient).
 template <typename T>
-static void wgrad(Runner& run, const char* label, const T* a, int64_t lda, const T* b, int64_t ldb, int M, int N,
-                  int64_t rows, float* out, int64_t ldo, T* tr_a, T* tr_b, bool a_t = false, float* db = nullptr,
-                  float* part = nullptr, float* part2 = nullptr) {
-  GemmProblem pr{};
-  pr.M = M;
-  pr.N = N;
-  pr.K = (int)rows;
-  if constexpr (sizeof(T) == 2) {
-    // bf16: the direct kernel reads both row-major operands through LDS
-    // transpose reads; no transposed copies
-    if (db) colsum<T>(run, "bias_colsum", a, rows, M, lda, part, db);
-    if (!out) return;
-    pr.a = a;
-    pr.lda = lda;
-    pr.b = b;
-    pr.ldb = ldb;
-    run.gemm<T, LAYOUT_MN, LAYOUT_MN>(label, pr, EpiF32{out, ldo, 0});
-    return;
+struct WgradItem {
+  const T* a;
+  int64_t lda;
+  const T* b;
+  int64_t ldb;
+  int M, N;
+  float* out;
+  int64_t ldo;
+  float* db;
+};
+
+// bf16 weight gradients over the same rows, up to kGemmGroup of them in one
+// launch: the direct kernel reads the token-major operands as they are,
+// through LDS transpose reads, and forms the bias gradients from the A
+// fragments it multiplies. Widths under its tiles take the register-path
+// kernel and column-sum passes.
+static void wgrad_group(Runner& run, const char* label, const WgradItem<bf16>* items, int count, int64_t rows,
+                        float* part) {
+  GemmProblem prs[kGemmGroup];
+  for (int i = 0; i < count; ++i) {
+    GemmProblem pr{};
+    pr.a = items[i].a;
+    pr.lda = items[i].lda;
+    pr.b = items[i].b;
+    pr.ldb = items[i].ldb;
+    pr.M = items[i].M;
+    pr.N = items[i].N;
+    pr.K = (int)rows;
+    prs[i] = pr;
   }
-  const bool tr = wgrad_transposes(rows, sizeof(T));
-  if (out && tr && !a_t) {
-    transpose<T>(run, "transpose", a, lda, rows, M, tr_a, round8(rows), db ? part : nullptr);
-    if (db) colsum_final(run, "bias_colsum", rows, M, part, part2, db);
-  } else if (db) {
-    colsum<T>(run, "bias_colsum", a, rows, M, lda, part, db);
+  // the plan of the whole group also serves a call that leaves some gradients
+  // out, so such a call never needs more split-K workspace than was sized
+  const GemmPlan plan = plan_gemm<bf16>(prs, count, Runner::kPlanCUsGemm);
+  const bool fused = gemm_plan_direct<bf16, LAYOUT_MN, LAYOUT_MN>(prs, count, plan);
+  EpiF32 epis[kGemmGroup];
+  float* cs = part;
+  int n = 0;
+  for (int i = 0; i < count; ++i) {
+    const WgradItem<bf16>& t = items[i];
+    if (t.db && !(t.out && fused)) colsum<bf16>(run, "bias_colsum", t.a, rows, t.M, t.lda, part, t.db);
+    if (!t.out) continue;
+    prs[n] = prs[i];
+    if (t.db && fused) {
+      prs[n].colsum = t.db;
+      prs[n].cs_part = cs;
+      cs += (size_t)plan_splits(prs[n], plan) * t.M;
+    }
+    epis[n] = EpiF32{t.out, t.ldo, 0};
+    ++n;
   }
-  if (!out) return;
-  if (tr) {
-    const int64_t ldt = round8(rows);
-    transpose<T>(run, "transpose", b, ldb, rows, N, tr_b, ldt);
-    pr.a = tr_a;
-    pr.lda = ldt;
-    pr.b = tr_b;
-    pr.ldb = ldt;
-    run.gemm<T, LAYOUT_K, LAYOUT_K>(label, pr, EpiF32{out, ldo, 0});
-    return;
+  run.gemm_group<bf16, LAYOUT_MN, LAYOUT_MN>(label, prs, epis, n, &plan);
+}
+
+// fp32: over many rows both operands are first transposed into tr_a / tr_b
+// ([M, rows] and [N, rows], rows padded to a multiple of 8) so the product
+// runs on K-contiguous operands, the transpose of A leaving the column sums;
+// an A that is the previous item's is transposed once.
+static void wgrad_group(Runner& run, const char* label, const WgradItem<float>* items, int count, int64_t rows,
+                        float* part, float* part2, float* tr_a, float* tr_b) {
+  const bool tr = wgrad_transposes(rows, sizeof(float));
+  const int64_t ldt = round8(rows);
+  const float* have = nullptr;  // the operand tr_a holds
+  for (int i = 0; i < count; ++i) {
+    const WgradItem<float>& t = items[i];
+    if (t.out && tr && (t.a != have || t.db)) {
+      transpose<float>(run, "transpose", t.a, t.lda, rows, t.M, tr_a, ldt, t.db ? part : nullptr);
+      if (t.db) colsum_final(run, "bias_colsum", rows, t.M, part, part2, t.db);
+      have = t.a;
+    } else if (t.db) {
+      colsum<float>(run, "bias_colsum", t.a, rows, t.M, t.lda, part, t.db);
+    }
+    if (!t.out) continue;
+    GemmProblem pr{};
+    pr.M = t.M;
+    pr.N = t.N;
+    pr.K = (int)rows;
+    if (tr) {
+      transpose<float>(run, "transpose", t.b, t.ldb, rows, t.N, tr_b, ldt);
+      pr.a = tr_a;
+      pr.lda = ldt;
+      pr.b = tr_b;
+      pr.ldb = ldt;
+      run.gemm<float, LAYOUT_K, LAYOUT_K>(label, pr, EpiF32{t.out, t.ldo, 0});
+    } else {
+      pr.a = t.a;
+      pr.lda = t.lda;
+      pr.b = t.b;
+      pr.ldb = t.ldb;
+      run.gemm<float, LAYOUT_MN, LAYOUT_MN>(label, pr, EpiF32{t.out, t.ldo, 0});
+    }
   }
-  pr.a = a;
-  pr.lda = lda;
-  pr.b = b;
-  pr.ldb = ldb;
-  run.gemm<T, LAYOUT_MN, LAYOUT_MN>(label, pr, EpiF32{out, ldo, 0});
 }
 
 // dA [rows, N] = G [rows, K] W [K, N] for a weight W stored [K (out), N (in)]:
@@ -542,6 +594,13 @@ static void backward_impl(Runner& run, const LayerDims& d, const pf_layer_config
   T* tra = WT(W.tr_a);
   T* trb = WT(W.tr_b);
   T* trw = WT(W.tr_w);
+  auto wgrads = [&](const char* label, const WgradItem<T>* items, int count, int64_t rows) {
+    if constexpr (sizeof(T) == 2)
+      wgrad_group(run, label, items, count, rows, part);
+    else
+      wgrad_group(run, label, items, count, rows, part, part2, tra, trb);
+  };
+  auto F = [](void* p) { return reinterpret_cast<float*>(p); };
   const int64_t BL = (int64_t)d.B * d.L;
   const int64_t Bm = (int64_t)d.B * d.m;
   const int df = d.d_f, dp = d.d_p;
@@ -560,13 +619,9 @@ static void backward_impl(Runner& run, const LayerDims& d, const pf_layer_config
     // dDelta = [dS | dT] W_a
     dgrad<T>(run, "affine_dgrad_gemm", WT(W.dst), 2 * df, w->affine.w, df, BL, df, 2 * df,
              EpiLinear<T>{WT(W.ddelta), df, nullptr, nullptr, 0, nullptr}, trw);
-    // dW_a = [dS | dT]^T Delta, one half (and its bias columns) at a time
-    float* dwa = reinterpret_cast<float*>(gr->affine.dw);
-    float* dba = reinterpret_cast<float*>(gr->affine.db);
-    for (int half = 0; half < 2; ++half)
-      wgrad<T>(run, "affine_wgrad_gemm", WT(W.dst) + half * df, 2 * df, S(A.delta), df, df, df, BL,
-               dwa ? dwa + (int64_t)half * df * df : nullptr, df, tra, trb, false, dba ? dba + half * df : nullptr,
-               part, part2);
+    // dW_a = [dS | dT]^T Delta
+    const WgradItem<T> item{WT(W.dst), 2 * df, S(A.delta), df, 2 * df, df, F(gr->affine.dw), df, F(gr->affine.db)};
+    wgrads("affine_wgrad_gemm", &item, 1, BL);
   } else if (cfg->injection == PF_INJECT_GATED_HEAD) {
     const int ldg = (int)round8(d.nh);
     run.launch("head_gate_bwd", [&] {
@@ -576,12 +631,12 @@ static void backward_impl(Runner& run, const LayerDims& d, const pf_layer_config
                          ldg);
       return hipGetLastError();
     });
-    // dW_g = dG^T [X | Delta]: dG is transposed once for both halves
-    float* dwg = reinterpret_cast<float*>(gr->gate.dw);
-    wgrad<T>(run, "head_gate_wgrad_gemm", WT(W.dgh), ldg, xp, df, d.nh, df, BL, dwg, 2 * df, tra, trb, false,
-             reinterpret_cast<float*>(gr->gate.db), part, part2);
-    wgrad<T>(run, "head_gate_wgrad_gemm", WT(W.dgh), ldg, S(A.delta), df, d.nh, df, BL, dwg ? dwg + df : nullptr,
-             2 * df, tra, trb, dwg != nullptr);
+    // dW_g = dG^T [X | Delta]
+    float* dwg = F(gr->gate.dw);
+    const WgradItem<T> items[2] = {
+        {WT(W.dgh), ldg, xp, df, d.nh, df, dwg, 2 * df, F(gr->gate.db)},
+        {WT(W.dgh), ldg, S(A.delta), df, d.nh, df, dwg ? dwg + df : nullptr, 2 * df, nullptr}};
+    wgrads("head_gate_wgrad_gemm", items, 2, BL);
   } else if (!add_inject) {
     run.launch("gate_bwd_prep", [&] {
       const int64_t n8 = BL * df / 8;
@@ -592,12 +647,11 @@ static void backward_impl(Runner& run, const LayerDims& d, const pf_layer_config
     });
     dgrad<T>(run, "gate_dgrad_gemm", WT(W.dg), df, w->gate.w, 2 * df, BL, 2 * df, df,
              EpiGateDgrad<T>{dyp, S(A.g), WF(W.dx32), WT(W.ddelta), df}, trw);
-    float* dwg = reinterpret_cast<float*>(gr->gate.dw);
-    // dG is transposed once for both halves of dW_g
-    wgrad<T>(run, "gate_wgrad_gemm", WT(W.dg), df, xp, df, df, df, BL, dwg, 2 * df, tra, trb, false,
-             reinterpret_cast<float*>(gr->gate.db), part, part2);
-    wgrad<T>(run, "gate_wgrad_gemm", WT(W.dg), df, S(A.delta), df, df, df, BL, dwg ? dwg + df : nullptr, 2 * df, tra,
-             trb, dwg != nullptr);
+    float* dwg = F(gr->gate.dw);
+    const WgradItem<T> items[2] = {
+        {WT(W.dg), df, xp, df, df, df, dwg, 2 * df, F(gr->gate.db)},
+        {WT(W.dg), df, S(A.delta), df, df, df, dwg ? dwg + df : nullptr, 2 * df, nullptr}};
+    wgrads("gate_wgrad_gemm", items, 2, BL);
   }
 
   // 2. decompression levels 1..M (reverse of Eq. 17)
@@ -607,9 +661,8 @@ static void backward_impl(Runner& run, const LayerDims& d, const pf_layer_config
     const int kd = d.k[j] * d.d[j];
     const int dn = d.d[j + 1];
     const T* u_in = j == d.M - 1 ? S(A.s) : S(A.u[j + 1]);
-    wgrad<T>(run, "decompress_wgrad_gemm", dT, kd, u_in, dn, kd, dn, rows,
-             reinterpret_cast<float*>(gr->decompress[j].dw), dn, tra, trb, false,
-             reinterpret_cast<float*>(gr->decompress[j].db), part, part2);
+    const WgradItem<T> item{dT, kd, u_in, dn, kd, dn, F(gr->decompress[j].dw), dn, F(gr->decompress[j].db)};
+    wgrads("decompress_wgrad_gemm", &item, 1, rows);
     if (j == d.M - 1) {
       dgrad<T>(run, "decompress_dgrad_gemm", dT, kd, w->decompress[j].w, dn, rows, dn, kd,
                EpiUnshift<T>{WT(W.dhbar), (int)d.m, dp, cfg->mask == PF_TOKEN_CAUSAL ? 1 : 0}, trw);
@@ -627,9 +680,6 @@ static void backward_impl(Runner& run, const LayerDims& d, const pf_layer_config
   }
   dgrad<T>(run, "o_dgrad_gemm", WT(W.dhbar), dp, w->o.w, dp, Bm, dp, dp,
            EpiHeads<T>{WT(W.dO), WT(W.dOt), nullptr, (int)d.m, d.dh, d.nh, d.ld_t}, trw);
-  wgrad<T>(run, "o_wgrad_gemm", WT(W.dhbar), dp, S(A.o), dp, dp, dp, Bm, reinterpret_cast<float*>(gr->o.dw), dp, tra,
-           trb, false, reinterpret_cast<float*>(gr->o.db), part, part2);
-
   // 4. attention (Eq. 9)
   AttnBwdParams ap{};
   ap.q = S(A.q);
@@ -659,9 +709,13 @@ static void backward_impl(Runner& run, const LayerDims& d, const pf_layer_config
   const T* dqkv[3] = {WT(W.dq), WT(W.dk), WT(W.dv)};
   const pf_linear* maps[3] = {&w->q, &w->k, &w->v};
   const pf_linear_grad* grads[3] = {&gr->q, &gr->k, &gr->v};
-  for (int i = 0; i < 3; ++i) {
-    wgrad<T>(run, "qkv_wgrad_gemm", dqkv[i], dp, S(A.h), dp, dp, dp, Bm, reinterpret_cast<float*>(grads[i]->dw), dp,
-             tra, trb, false, reinterpret_cast<float*>(grads[i]->db), part, part2);
+  {
+    WgradItem<T> items[4];
+    for (int i = 0; i < 3; ++i)
+      items[i] = {dqkv[i], dp, S(A.h), dp, dp, dp, F(grads[i]->dw), dp, F(grads[i]->db)};
+    // with the output map's, so the four small products share a launch
+    items[3] = {WT(W.dhbar), dp, S(A.o), dp, dp, dp, F(gr->o.dw), dp, F(gr->o.db)};
+    wgrads("qkvo_wgrad_gemm", items, 4, Bm);
   }
   for (int i = 0; i < 3; ++i) {
     EpiAccum<T> e{WF(W.dh32), dp, reinterpret_cast<const T*>(dh_out), i == 0, i == 2 ? WT(W.dh) : nullptr,
@@ -676,9 +730,8 @@ static void backward_impl(Runner& run, const LayerDims& d, const pf_layer_config
     const int kd = d.k[j] * d.d[j];
     const int dn = d.d[j + 1];
     const T* v_in = j == 0 ? xp : S(A.z[j]);
-    wgrad<T>(run, "compress_wgrad_gemm", dz, dn, v_in, kd, dn, kd, rows,
-             reinterpret_cast<float*>(gr->compress[j].dw), kd, tra, trb, false,
-             reinterpret_cast<float*>(gr->compress[j].db), part, part2);
+    const WgradItem<T> item{dz, dn, v_in, kd, dn, kd, F(gr->compress[j].dw), kd, F(gr->compress[j].db)};
+    wgrads("compress_wgrad_gemm", &item, 1, rows);
     if (j == 0) {
       // dX = (dY + dG W_gx, in dx32) or dY, plus this level's data gradient
       EpiAccum<T> e = add_inject ? EpiAccum<T>{WF(W.dx32), kd, dyp, 1, reinterpret_cast<T*>(dx), nullptr}

@@ -347,7 +347,8 @@ LayerWs layer_ws_layout(const LayerDims& d, bool bwd) {
     auto tp = [&](int64_t rows, int64_t cols) {
       if (wgrad_transposes(rows, es)) part = std::max(part, (size_t)((rows + 63) / 64 * cols));
     };
-    tp((int64_t)d.B * d.L, d.d_f);
+    const int64_t wide = d.inject == PF_INJECT_AFFINE ? 2 * (int64_t)d.d_f : d.d_f;  // [dS | dT] is one operand
+    tp((int64_t)d.B * d.L, wide);
     for (int j = 0; j < d.M; ++j) {
       tp((int64_t)d.B * d.R[j + 1], (int64_t)d.k[j] * d.d[j]);
       tp((int64_t)d.B * d.R[j + 1], d.d[j + 1]);
@@ -362,7 +363,7 @@ LayerWs layer_ws_layout(const LayerDims& d, bool bwd) {
       if (wgrad_transposes(rows, es)) tr = std::max(tr, (size_t)(round8(rows) * cols) * es);
     };
     auto wt = [&](int64_t out, int64_t in) { trw = std::max(trw, (size_t)(out * in) * es); };
-    op((int64_t)d.B * d.L, d.d_f);
+    op((int64_t)d.B * d.L, wide);
     wt(d.d_f, 2 * (int64_t)d.d_f);
     for (int j = 0; j < d.M; ++j) {
       const int64_t rows = (int64_t)d.B * d.R[j + 1];
@@ -467,6 +468,8 @@ static void forward_impl(Runner& run, const LayerDims& d, const pf_layer_config*
   // the low parts of Q and K are kept for the backward; the forward
   // attention reads the fp8 correction rows
   T* outs_lo[3] = {split && saving ? P(A.q_lo) : nullptr, split && saving ? P(A.k_lo) : nullptr, nullptr};
+  GemmProblem qkv[3];
+  EpiHeads<T> qkv_e[3];
   for (int i = 0; i < 3; ++i) {
     GemmProblem pr{};
     pr.a = hbuf;
@@ -495,8 +498,10 @@ static void forward_impl(Runner& run, const LayerDims& d, const pf_layer_config*
       e.outx = reinterpret_cast<uint8_t*>(act + (i == 0 ? A.qx : A.kx));
       e.xmode = i == 0 ? 1 : 2;
     }
-    run.gemm<T, LAYOUT_K, LAYOUT_K>("qkv_gemm", pr, e);
+    qkv[i] = pr;
+    qkv_e[i] = e;
   }
+  run.gemm_group<T, LAYOUT_K, LAYOUT_K>("qkv_gemm", qkv, qkv_e, 3);
 
   // 3. attention over the proxies (Eq. 9)
   AttnParams ap{};

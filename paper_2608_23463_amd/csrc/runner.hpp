@@ -24,31 +24,46 @@ struct Runner {
   // the plan asks for it. `label` names the launch for tracing.
   template <typename T, int LA, int LB, class Epi>
   void gemm(const char* label, const GemmProblem& pr, const Epi& epi) {
-    if (!ok() || pr.M <= 0 || pr.N <= 0) return;
-    GemmPlan pl = plan_gemm<T>(pr, kPlanCUsGemm);
+    gemm_group<T, LA, LB>(label, &pr, &epi, 1);
+  }
+
+  // Up to kGemmGroup independent products in one launch (and one reduction
+  // when K is split): small products leave most of the chip idle on their own
+  // and pay a launch and a pipeline fill each. `plan`: made by the caller.
+  template <typename T, int LA, int LB, class Epi>
+  void gemm_group(const char* label, const GemmProblem* prs, const Epi* epis, int count,
+                  const GemmPlan* plan = nullptr) {
+    if (!ok() || count <= 0) return;
+    for (int i = 0; i < count; ++i)
+      if (prs[i].M <= 0 || prs[i].N <= 0) return;
+    GemmPlan pl = plan ? *plan : plan_gemm<T>(prs, count, kPlanCUsGemm);
     if (dry) {
       if (pl.splits > 1) {
-        const size_t need = (size_t)pl.splits * pr.M * pr.N * sizeof(float);
+        size_t need = 0;
+        for (int i = 0; i < count; ++i) need += plan_partials(prs[i], pl) * sizeof(float);
         if (need > gemm_need) gemm_need = need;
       }
       return;
     }
     if (pl.splits <= 1 || gemm_ws == nullptr) {
       pl.splits = 1;
-      pl.k_slice = std::max(pl.bk, ((pr.K + pl.bk - 1) / pl.bk) * pl.bk);
-      timed(label, [&] { return launch_gemm_plan<T, LA, LB>(pr, pl, epi, stream); });
+      timed(label, [&] { return launch_gemm_plan<T, LA, LB>(prs, count, pl, epis, stream); });
       return;
     }
-    EpiPartial part{gemm_ws, pr.N, (int64_t)pr.M * pr.N};
-    timed(label, [&] { return launch_gemm_plan<T, LA, LB>(pr, pl, part, stream); });
+    EpiPartial part[kGemmGroup];
+    GemmProblem sl[kGemmGroup];
+    float* parts[kGemmGroup];
+    float* at = gemm_ws;
+    for (int i = 0; i < count; ++i) {
+      sl[i] = prs[i];
+      if (sl[i].colsum) sl[i].colsum = prs[i].cs_part;  // per-slice sums, joined by the reduction
+      parts[i] = at;
+      part[i] = EpiPartial{at, prs[i].N, (int64_t)prs[i].M * prs[i].N};
+      at += plan_partials(prs[i], pl);
+    }
+    timed(label, [&] { return launch_gemm_plan<T, LA, LB>(sl, count, pl, part, stream); });
     if (!ok()) return;
-    const int64_t total = (int64_t)pr.M * pr.N;
-    const int blocks = (int)std::min<int64_t>((total + 255) / 256, 8192);
-    timed("splitk_reduce", [&] {
-      hipLaunchKernelGGL((splitk_reduce_kernel<Epi>), dim3(blocks), dim3(256), 0, stream, gemm_ws, pl.splits, pr.M,
-                         pr.N, epi);
-      return hipGetLastError();
-    });
+    timed("splitk_reduce", [&] { return launch_splitk_reduce(prs, count, pl, parts, epis, stream); });
   }
 
   template <class F>

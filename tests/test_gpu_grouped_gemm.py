@@ -1,0 +1,86 @@
+"""Grouped GEMM launches, bias gradients formed inside the weight-gradient
+GEMM, and the split-K reduction over lanes, at the sizes where they can go
+wrong: widths at and just past the 128 and 256 tiles, one to a few proxies
+against long reductions (many slices of few chunks), token counts that are no
+multiple of the K step, and gradient sets with members left out."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2608_23463_amd import synth
+from paper_2608_23463_amd.synth import LayerShape
+from helpers import dev, dev_weights
+from test_gpu_backward import compare, run_gpu_backward
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = {
+    # 128-wide operands: one tile per product, the narrowest fused bias sums
+    "d128_rows37": LayerShape(1, 16 * 37, 128, 128, 2, 64, (16,)),
+    # one chunk past a tile edge: the last tile holds 8 rows and 8 columns
+    "d136_dp192": LayerShape(2, 8 * 61, 136, 192, 3, 64, (8,)),
+    # past two 128 tiles, ragged tokens, a compression of 3 rows over K = 16,896
+    "d264_dp256_m3": LayerShape(1, 64 * 2 + 5, 264, 256, 4, 64, (64,)),
+    # the 256 tiles of long reductions: 16,640 token rows
+    "d256_rows16k": LayerShape(1, 32 * 520, 256, 256, 2, 128, (32,), mask=synth.BLOCK_CAUSAL),
+    # under the tiles: the register-path kernel and the column-sum passes
+    "d72_dp64": LayerShape(2, 8 * 33, 72, 64, 1, 64, (8,)),
+    "affine_d144": LayerShape(1, 8 * 130, 144, 128, 2, 64, (8,), injection=synth.INJECT_AFFINE),
+    "fp32_d136": LayerShape(1, 8 * 70, 136, 128, 2, 64, (8,), dtype="fp32"),
+    "fp32_affine_rows8k": LayerShape(1, 16 * 520, 40, 64, 1, 64, (16,), dtype="fp32", injection=synth.INJECT_AFFINE),
+}
+
+
+@pytest.mark.parametrize("name", SHAPES)
+def test_gradients_at_tile_edges(gpu, name):
+    shape = SHAPES[name]
+    print(f"[case {name}] {shape}", flush=True)
+    inp = synth.layer_inputs(shape, 4100 + sorted(SHAPES).index(name), with_dy=True)
+    res = run_gpu_backward(shape, inp)
+    ref = oracle.layer_backward(inp["x"], inp["weights"], shape.factors, shape.n_heads, inp["dy"], shape.mask,
+                                injection=shape.injection)
+    compare(shape, inp, res, ref, name)
+
+
+@pytest.mark.parametrize("missing", ["q", "k v o", "gate", "compress decompress"])
+def test_gradients_left_out(gpu, missing):
+    """A NULL dw skips that gradient; the others (and every bias gradient)
+    equal the full call's bit for bit, within the workspace the size query gave."""
+    import torch
+    B = gpu
+    shape = LayerShape(1, 64 * 20, 256, 256, 4, 64, (64,))
+    print(f"[left out: {missing}]", flush=True)
+    inp = synth.layer_inputs(shape, 4200, with_dy=True)
+    cfg = B.config_from_shape(shape)
+    w, x, dy = dev_weights(inp["weights"], "bf16"), dev(inp["x"], "bf16"), dev(inp["dy"], "bf16")
+    _, _, saved = B.layer_forward(cfg, w, x, save=True)
+    dx, _, full = B.layer_backward(cfg, w, x, None, saved, dy)
+
+    def fresh(pair, drop):
+        return tuple(None if drop and i == 0 else torch.full_like(t, float("nan")) for i, t in enumerate(pair))
+
+    some = {}
+    for key, val in full.items():
+        drop = key in missing.split()
+        some[key] = [fresh(p, drop) for p in val] if isinstance(val, list) else (fresh(val, drop) if val else None)
+    dx2 = torch.full_like(dx, float("nan"))
+    ws = torch.full((B.layer_workspace_size(cfg, True),), 255, dtype=torch.uint8, device="cuda")
+    st = B.load().proxy_layer_backward(ctypes.byref(cfg), ctypes.byref(B.layer_weights(w)), x.data_ptr(), None,
+                                       saved.data_ptr(), dy.data_ptr(), None, dx2.data_ptr(), None,
+                                       ctypes.byref(B.layer_grads(some)), ws.data_ptr(), ws.numel(),
+                                       torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert st == B.PF_OK, B.last_error()
+    assert torch.equal(dx, dx2)
+    for key, val in full.items():
+        for a, b in zip(val if isinstance(val, list) else [val or ()], some[key] if isinstance(val, list) else [some[key] or ()]):
+            for i, (p, q) in enumerate(zip(a, b)):
+                if q is None:
+                    continue
+                if i == 1 and key in missing.split():  # formed by its own column-sum pass
+                    err = float((p - q).abs().max() / p.abs().max().clamp_min(1e-30))
+                    assert np.isfinite(err) and (key == "k" or err <= 1e-4), (key, err)
+                else:
+                    assert torch.equal(p, q), (key, i)

@@ -13,6 +13,9 @@ namespace pf {
 // Epilogues whose GEMMs are also launched in groups (a kernel variant each).
 template <class Epi>
 struct GemmGrouped : std::false_type {};
+// Epilogues with arrays they index: kept in the kernel arguments.
+template <class Epi>
+struct EpiByRef : std::false_type {};
 
 typedef __bf16 bf16;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));

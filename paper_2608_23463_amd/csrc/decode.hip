@@ -532,6 +532,8 @@ struct EpiCache {
 
 template <typename T>
 struct GemmGrouped<EpiCache<T>> : std::true_type {};
+template <typename T>
+struct EpiByRef<EpiCache<T>> : std::true_type {};
 
 // ---- launch sequences ---------------------------------------------------------
 

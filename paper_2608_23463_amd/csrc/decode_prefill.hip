@@ -505,7 +505,7 @@ PrefillWs prefill_ws(const DecodeDims& d, int64_t T, int64_t n_cap) {
   w.alpha = take(rows * d.nh * 4);
   w.vct = take(vrow ? 0 : (size_t)d.B * d.nh * d.dh * w.ld_c * es);
   const int64_t nblk = T / d.P;
-  w.xc = take(nblk > 0 && T % d.P != 0 ? (size_t)d.B * nblk * d.P * d.d * es : 0);
+  w.xc = take(nblk > 0 && T % d.P != 0 && d.B > 1 ? (size_t)d.B * nblk * d.P * d.d * es : 0);
   w.gemm = off;
   w.bytes = off + align256(prefill_gemm_need(d, T, w));
   return w;
@@ -537,10 +537,6 @@ static void prefill_impl(Runner& run, const DecodeDims& d, const pf_decode_weigh
   // 2. projections: Q, K per head (row tensors), V per head (bf16) or
   //    token-contiguous (fp32), alpha
   constexpr bool vrow = sizeof(T) == 2;
-  if (!vrow && W.ld_t != Tn) {  // padding columns of V^T must read as zero
-    const size_t tb = (size_t)d.B * d.nh * d.dh * W.ld_t * sizeof(T);
-    run.launch("fill_zero", [&] { return fill_zero(vt, tb, run.stream); });
-  }
   const pf_linear* proj[3] = {&w->q, &w->k, &w->v};
   // Q goes to the attention pre-scaled by log2(e)/sqrt(d_head): scores in
   // exp2 units
@@ -583,11 +579,9 @@ static void prefill_impl(Runner& run, const DecodeDims& d, const pf_decode_weigh
   const int64_t nblk = n_tok / d.P;
   if (!run.dry && nblk > 0 && run.ok()) {
     const void* xb = x;
-    if (n_tok % d.P != 0) {  // gather the complete blocks into one [B, nblk*P, d] view
-      const size_t width = (size_t)nblk * d.P * d.d * sizeof(T);
+    if (n_tok % d.P != 0 && d.B > 1) {  // gather the complete blocks into one [B, nblk*P, d] view
       run.launch("prefill_gather", [&] {
-        return hipMemcpy2DAsync(ws + W.xc, width, x, (size_t)n_tok * d.d * sizeof(T), width, d.B,
-                                hipMemcpyDeviceToDevice, run.stream);
+        return pad_rows(x, ws + W.xc, d.B, n_tok, nblk * d.P, (int64_t)d.d * sizeof(T), run.stream);
       });
       xb = ws + W.xc;
     }

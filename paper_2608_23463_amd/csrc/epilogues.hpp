@@ -83,6 +83,10 @@ struct EpiLinear {
 
 // Splits a [B*m, h*dh] projection into per-head tensors: row r = b*m + i,
 // column c = head*dh + e. `out` is [B, h, m, dh], `out_t` is [B, h, dh, ld_t].
+// The columns m .. ld_t-1 of `out_t` are written as zeros by the last rows of
+// the sequence (row i clears m + (m - 1 - i), and every m columns after it),
+// which costs those rows a few 2-byte stores instead of a fill launch per
+// tensor.
 // Optionally also a scaled copy (v * scale) in the row layout, `outs`.
 template <typename T>
 struct EpiHeads {
@@ -108,7 +112,10 @@ struct EpiHeads {
     const int hd = c / dh, e = c - hd * dh;
     const int64_t bh = (int64_t)b * n_heads + hd;
     if (out) out[(bh * m + i) * dh + e] = o;
-    if (out_t) out_t[(bh * dh + e) * ld_t + i] = o;
+    if (out_t) {
+      out_t[(bh * dh + e) * ld_t + i] = o;
+      for (int p = 2 * m - 1 - i; p < ld_t; p += m) out_t[(bh * dh + e) * ld_t + p] = (T)0.0f;
+    }
     if (out_lo) out_lo[(bh * m + i) * dh + e] = from_f32<T>(split_lo(v));
     if (outs) outs[(bh * m + i) * dh + e] = from_f32<T>(v * scale);
     if (outx) {
@@ -162,6 +169,9 @@ struct EpiHeads {
     if (out_t) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) out_t[(bh * dh + e0 + e) * ld_t + i] = from_f32<T>(v[e]);
+      for (int p = 2 * m - 1 - i; p < ld_t; p += m)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) out_t[(bh * dh + e0 + e) * ld_t + p] = (T)0.0f;
     }
     if (outx) {
       float hi[8], lo[8];

@@ -54,6 +54,9 @@ struct GemmParams {
   const void* b2;
   int64_t ldb2;
   int b_ksplit;        // K index where B2 starts (>= K: unused)
+  const void* a3;      // a third source of both from K index ksplit3 on (>= K: unused; direct
+  const void* b3;      // kernel with an M/N-major operand only)
+  int ksplit3;
   int M, N, K;
   int k_slice;         // reduction length per gridDim.z slice (multiple of BK)
   int tiles_m, tiles_n;
@@ -86,6 +89,13 @@ struct GemmShape {
   static_assert(kTM % 32 == 0 && kTN % 32 == 0, "wave tile must be whole 32x32 MFMA tiles");
   static_assert((BM * BK) % (kThreads * kVec) == 0, "A tile must split evenly");
   static_assert((BN * BK) % (kThreads * kVec) == 0, "B tile must split evenly");
+};
+
+// How a kernel holds its epilogue: a copy, or (EpiByRef) a reference into the
+// kernel arguments for one with arrays that it indexes.
+template <class Epi>
+struct EpiArg {
+  typedef typename std::conditional<EpiByRef<Epi>::value, const Epi&, const Epi>::type type;
 };
 
 // ---- tile loaders: global -> registers -> LDS ------------------------------
@@ -671,8 +681,10 @@ __global__ void __launch_bounds__(WM* WN* kWave)
     __attribute__((amdgpu_waves_per_eu(WM* WN / 4, (BM >= 256 ? 1 : 2) * WM * WN / 4)))
     gemm_direct_kernel(const GemmArgs<Epi, G> args) {
   const int prob = G == 1 ? 0 : (int)blockIdx.y;
-  const GemmParams& p = args.p[prob];
-  const Epi& epi = args.e[prob];
+  // a copy, so that the choice of the problem is made once (with an indexed
+  // reference the compiler kept the argument arrays in scratch memory)
+  const GemmParams p = args.p[prob];
+  typename EpiArg<Epi>::type epi = args.e[prob];
   if (G > 1 && (int)blockIdx.x >= p.tiles_m * p.tiles_n) return;  // a smaller problem of the group
   if (G > 1 && (int)blockIdx.z * p.k_slice >= p.K && blockIdx.z > 0) return;
   typedef DirectShape<T, BM, BN, BK, WM, WN, NS, LA, LB> D;
@@ -729,6 +741,11 @@ __global__ void __launch_bounds__(WM* WN* kWave)
                    (OB::kMN ? n0 * (int64_t)sizeof(T) : n0 * ldb_b);
   const char* b2 = p.b2 ? reinterpret_cast<const char*>(p.b2) + (OB::kMN ? n0 * (int64_t)sizeof(T) : n0 * ldb_b)
                         : nullptr;
+  // distances to the second and third sources (0 when absent), the third from
+  // the second
+  const int64_t a_to2 = p.a2 ? a2 - a1 : 0, b_to2 = p.b2 ? b2 - b1 : 0;
+  const int64_t a_to3 = p.a3 ? (const char*)p.a3 - (const char*)p.a2 : 0;
+  const int64_t b_to3 = p.b3 ? (const char*)p.b3 - (const char*)p.b2 : 0;
   const uint32_t a_rows = (uint32_t)(max(0, min(BM, p.M - m0)) * lda_b);
   const uint32_t b_rows = (uint32_t)(max(0, min(BN, p.N - n0)) * ldb_b);
   const int a_cols = max(0, min(BM, p.M - m0)), b_cols = max(0, min(BN, p.N - n0));
@@ -738,16 +755,18 @@ __global__ void __launch_bounds__(WM* WN* kWave)
   auto issue_range = [&](int k0, int stage, int i0, int i1) {
     const bool tail = k0 + BK > kend;
     T* st = smem + stage * D::kStage;
+    const bool third = (OA::kMN || OB::kMN) && k0 >= p.ksplit3;
     if (i0 < OA::kInsts) {
       const bool second = k0 >= p.a_ksplit;
-      const int krel = second ? k0 - p.a_ksplit : k0;
+      const int krel = k0 - (second ? p.a_ksplit : 0) - (third ? p.ksplit3 - p.a_ksplit : 0);
+      const char* src = a1 + (second ? a_to2 : 0) + (third ? a_to3 : 0);
       rsrc_t rs;
       if constexpr (OA::kMN) {
         const int rows = min(BK, kend - k0);
-        rs = make_rsrc_uniform((second ? a2 : a1) + (int64_t)krel * lda_b,
+        rs = make_rsrc_uniform(src + (int64_t)krel * lda_b,
                                (uint32_t)((int64_t)(rows - 1) * lda_b + a_cols * (int64_t)sizeof(T)));
       } else {
-        rs = make_rsrc_uniform((second ? a2 : a1) + (int64_t)krel * sizeof(T), a_rows - (uint32_t)(krel * sizeof(T)));
+        rs = make_rsrc_uniform(src + (int64_t)krel * sizeof(T), a_rows - (uint32_t)(krel * sizeof(T)));
       }
 #pragma unroll
       for (int i = 0; i < OA::kInsts; ++i)
@@ -758,14 +777,15 @@ __global__ void __launch_bounds__(WM* WN* kWave)
     }
     if (i1 > OA::kInsts) {
       const bool second = k0 >= p.b_ksplit;
-      const int krel = second ? k0 - p.b_ksplit : k0;
+      const int krel = k0 - (second ? p.b_ksplit : 0) - (third ? p.ksplit3 - p.b_ksplit : 0);
+      const char* src = b1 + (second ? b_to2 : 0) + (third ? b_to3 : 0);
       rsrc_t rs;
       if constexpr (OB::kMN) {
         const int rows = min(BK, kend - k0);
-        rs = make_rsrc_uniform((second ? b2 : b1) + (int64_t)krel * ldb_b,
+        rs = make_rsrc_uniform(src + (int64_t)krel * ldb_b,
                                (uint32_t)((int64_t)(rows - 1) * ldb_b + b_cols * (int64_t)sizeof(T)));
       } else {
-        rs = make_rsrc_uniform((second ? b2 : b1) + (int64_t)krel * sizeof(T), b_rows - (uint32_t)(krel * sizeof(T)));
+        rs = make_rsrc_uniform(src + (int64_t)krel * sizeof(T), b_rows - (uint32_t)(krel * sizeof(T)));
       }
 #pragma unroll
       for (int i = 0; i < OB::kInsts; ++i)
@@ -1062,6 +1082,10 @@ struct GemmProblem {
   const void* b2 = nullptr;
   int64_t ldb2 = 0;
   int b_ksplit = 1 << 30;
+  // third sources of A and B (same row strides) from K index ksplit3 on
+  const void* a3 = nullptr;
+  const void* b3 = nullptr;
+  int ksplit3 = 1 << 30;
   int M, N, K;
   // batched problem (direct kernel only, A2/B2 unused): `batch` independent
   // products, batch z reading A at z * batch_a and B at z * batch_b
@@ -1155,9 +1179,10 @@ template <typename T, int BM, int BN, int BK, int LA, int LB>
 inline bool gemm_runs_direct(const GemmProblem& pr, int k_slice) {
   const bool aligned_split = (pr.a_ksplit >= pr.K || pr.a_ksplit % BK == 0) &&
                              (pr.b_ksplit >= pr.K || pr.b_ksplit % BK == 0) &&
-                             (!pr.a2 || pr.lda2 == pr.lda) && (!pr.b2 || pr.ldb2 == pr.ldb);
+                             (!pr.a2 || pr.lda2 == pr.lda) && (!pr.b2 || pr.ldb2 == pr.ldb) &&
+                             (pr.ksplit3 >= pr.K || pr.ksplit3 % BK == 0);
   if (!aligned_split || k_slice % BK != 0) return false;
-  if (LA == LAYOUT_K && LB == LAYOUT_K) return true;
+  if (LA == LAYOUT_K && LB == LAYOUT_K) return pr.ksplit3 >= pr.K;
   // M/N-major operands through LDS transpose reads: rows of such an
   // operand start 16-byte aligned and hold at least one tile width
   return sizeof(T) == 2 && BM >= 128 && BN >= 128 && (LA == LAYOUT_K || (pr.lda % 8 == 0 && pr.lda >= BM)) &&
@@ -1176,6 +1201,9 @@ inline GemmParams gemm_params(const GemmProblem& pr, int BM, int BN, int BK, int
   p.b2 = pr.b2;
   p.ldb2 = pr.ldb2;
   p.b_ksplit = pr.b_ksplit;
+  p.a3 = pr.a3;
+  p.b3 = pr.b3;
+  p.ksplit3 = pr.ksplit3;
   p.M = pr.M;
   p.N = pr.N;
   p.K = pr.K;

@@ -111,7 +111,8 @@ inline bool wgrad_transposes(int64_t rows, int64_t esize) {
 inline int64_t round8(int64_t v) { return (v + 7) / 8 * 8; }
 
 // dst[b, t] = t < L_in ? src[b, t] : 0 for t < L_pad, rows of row_bytes (a
-// multiple of 16) with per-sequence strides L_in and L_pad rows.
+// multiple of 16) with per-sequence strides L_in and L_pad rows (L_pad may be
+// the shorter: the first L_pad rows are copied).
 hipError_t pad_rows(const void* src, void* dst, int B, int64_t L_in, int64_t L_pad, int64_t row_bytes,
                     hipStream_t stream);
 // dst[b, t] = src[b, t] for t < L_in (the first L_in of L_pad rows per sequence).

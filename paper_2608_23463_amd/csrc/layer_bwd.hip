@@ -674,10 +674,6 @@ static void backward_impl(Runner& run, const LayerDims& d, const pf_layer_config
   }
 
   // 3. output map of the interaction
-  if (d.ld_t != d.m) {
-    const size_t tb = (size_t)d.B * d.nh * d.dh * d.ld_t * sizeof(T);
-    run.launch("fill_zero", [&] { return fill_zero(WT(W.dOt), tb, run.stream); });
-  }
   dgrad<T>(run, "o_dgrad_gemm", WT(W.dhbar), dp, w->o.w, dp, Bm, dp, dp,
            EpiHeads<T>{WT(W.dO), WT(W.dOt), nullptr, (int)d.m, d.dh, d.nh, d.ld_t}, trw);
   // 4. attention (Eq. 9)
@@ -717,10 +713,34 @@ static void backward_impl(Runner& run, const LayerDims& d, const pf_layer_config
     items[3] = {WT(W.dhbar), dp, S(A.o), dp, dp, dp, F(gr->o.dw), dp, F(gr->o.db)};
     wgrads("qkvo_wgrad_gemm", items, 4, Bm);
   }
-  for (int i = 0; i < 3; ++i) {
-    EpiAccum<T> e{WF(W.dh32), dp, reinterpret_cast<const T*>(dh_out), i == 0, i == 2 ? WT(W.dh) : nullptr,
-                  i == 2 ? reinterpret_cast<T*>(dh_in) : nullptr};
-    dgrad<T>(run, "qkv_dgrad_gemm", dqkv[i], dp, maps[i]->w, dp, Bm, dp, dp, e, trw);
+  {
+    // dH = dH_out + [dQ | dK | dV] [W_q; W_k; W_v]: one product over the
+    // concatenated reduction where the direct kernel takes the weights as they
+    // are; over many rows, and in fp32, one product per map added up in dh32
+    GemmProblem pr{};
+    pr.a = dqkv[0];
+    pr.a2 = dqkv[1];
+    pr.a3 = dqkv[2];
+    pr.b = w->q.w;
+    pr.b2 = w->k.w;
+    pr.b3 = w->v.w;
+    pr.lda = pr.lda2 = pr.ldb = pr.ldb2 = dp;
+    pr.a_ksplit = pr.b_ksplit = dp;
+    pr.ksplit3 = 2 * dp;
+    pr.M = (int)Bm;
+    pr.N = dp;
+    pr.K = 3 * dp;
+    const GemmPlan plan = plan_gemm<T>(&pr, 1, Runner::kPlanCUsGemm);
+    if (sizeof(T) == 2 && Bm < kTransposeMinRows && gemm_plan_direct<T, LAYOUT_K, LAYOUT_MN>(&pr, 1, plan)) {
+      const EpiAccum<T> e{WF(W.dh32), dp, reinterpret_cast<const T*>(dh_out), 1, WT(W.dh), reinterpret_cast<T*>(dh_in)};
+      run.gemm<T, LAYOUT_K, LAYOUT_MN>("qkv_dgrad_gemm", pr, e);
+    } else {
+      for (int i = 0; i < 3; ++i) {
+        EpiAccum<T> e{WF(W.dh32), dp, reinterpret_cast<const T*>(dh_out), i == 0, i == 2 ? WT(W.dh) : nullptr,
+                      i == 2 ? reinterpret_cast<T*>(dh_in) : nullptr};
+        dgrad<T>(run, "qkv_dgrad_gemm", dqkv[i], dp, maps[i]->w, dp, Bm, dp, dp, e, trw);
+      }
+    }
   }
 
   // 6. compression levels M..1 (reverse of Eq. 16)

@@ -26,19 +26,6 @@
 
 namespace pf {
 
-__global__ void fill_zero_kernel(u32x4* p, size_t n16) {
-  const size_t stride = (size_t)gridDim.x * blockDim.x;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += stride) p[i] = u32x4{0u, 0u, 0u, 0u};
-}
-
-hipError_t fill_zero(void* p, size_t bytes, hipStream_t stream) {
-  if (bytes == 0) return hipSuccess;
-  const size_t n16 = bytes / 16;  // every buffer here is a multiple of 16 bytes
-  const int blocks = (int)std::min<size_t>((n16 + 255) / 256, 4096);
-  hipLaunchKernelGGL(fill_zero_kernel, dim3(blocks), dim3(256), 0, stream, reinterpret_cast<u32x4*>(p), n16);
-  return hipGetLastError();
-}
-
 // b'[p][n] = b_g[n] (or 0) for every position p: the fused gate's bias when
 // the decompression has no bias.
 template <typename T>
@@ -71,8 +58,7 @@ hipError_t pad_rows(const void* src, void* dst, int B, int64_t L_in, int64_t L_p
 
 hipError_t unpad_rows(const void* src, void* dst, int B, int64_t L_in, int64_t L_pad, int64_t row_bytes,
                       hipStream_t stream) {
-  return hipMemcpy2DAsync(dst, (size_t)(L_in * row_bytes), src, (size_t)(L_pad * row_bytes),
-                          (size_t)(L_in * row_bytes), (size_t)B, hipMemcpyDeviceToDevice, stream);
+  return pad_rows(src, dst, B, L_pad, L_in, row_bytes, stream);  // the first L_in of L_pad rows
 }
 
 __global__ void permute_patches_kernel(const u32x4* __restrict__ src, u32x4* __restrict__ dst, int64_t L, int w,
@@ -450,15 +436,6 @@ static void forward_impl(Runner& run, const LayerDims& d, const pf_layer_config*
   // 2. projections of H into per-head Q, K (row layout, hi and lo parts) and
   //    V (key-contiguous); Q and K read H as [hi | lo]
   const T* hbuf = reinterpret_cast<const T*>(h_out);
-  if (d.ld_t != d.m) {
-    // padding columns of the transposed tensors must read as zero
-    const size_t tb = (size_t)d.B * d.nh * d.dh * d.ld_t * sizeof(T);
-    run.launch("fill_zero", [&] { return fill_zero(P(A.vt), tb, run.stream); });
-    if (saving) {
-      run.launch("fill_zero", [&] { return fill_zero(P(A.qt), tb, run.stream); });
-      run.launch("fill_zero", [&] { return fill_zero(P(A.kt), tb, run.stream); });
-    }
-  }
   const pf_linear* proj[3] = {&w->q, &w->k, &w->v};
   // Q goes to the attention pre-scaled by log2(e)/sqrt(d_head) (scores in
   // exp2 units); the unscaled Q is kept only for the backward

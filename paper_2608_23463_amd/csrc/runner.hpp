@@ -83,8 +83,4 @@ struct Runner {
   static constexpr int kPlanCUsGemm = 256;
 };
 
-// Zero-fill of a device byte range with a kernel (no memset nodes, so the
-// sequence stays valid inside a captured HIP graph).
-hipError_t fill_zero(void* p, size_t bytes, hipStream_t stream);
-
 }  // namespace pf

@@ -24,9 +24,14 @@
 // written to LDS, so LDS always holds rows contiguous along K and every lane
 // reads its MFMA fragment with 16-byte LDS reads. Rows are padded by 16 bytes
 // so that the 32 rows a fragment read touches fall in distinct banks.
-// Workgroups are dealt to the 8 XCDs round-robin; the tile index is remapped
-// so that each XCD works on a contiguous band of tiles (shared L2), and
-// within the band GROUP_M row tiles are visited per column sweep.
+// Workgroups are dealt to the 8 XCDs round-robin; the work index (K slice,
+// then problem, then tile) is remapped so that each XCD works on a contiguous
+// band of it (shared L2), and within the band GROUP_M row tiles are visited
+// per column sweep. With K split, an XCD thus runs the tiles of its own slices
+// and their operands come to one L2 only; with the tiles of a slice spread
+// over the XCDs every L2 fetched its own copy and the split products ran at
+// the rate of that traffic (the compression of 65,536 tokens at d = 1024:
+// 150 us so, 141 us now).
 #pragma once
 
 #include <algorithm>
@@ -91,11 +96,37 @@ struct GemmShape {
   static_assert((BN * BK) % (kThreads * kVec) == 0, "B tile must split evenly");
 };
 
-// How a kernel holds its epilogue: a copy, or (EpiByRef) a reference into the
-// kernel arguments for one with arrays that it indexes.
+// Epilogue writing split-K partials ws[z][M][N] of K slice z.
+struct EpiPartial {
+  float* ws;
+  int N;
+  int64_t slice_stride;
+  int z;
+  __device__ __forceinline__ void operator()(int r, int c, float v) const {
+    ws[(int64_t)z * slice_stride + (int64_t)r * N + c] = v;
+  }
+  __device__ __forceinline__ void vec8(int r, int c, const float* v) const {
+    if ((N & 7) == 0) {
+      store8(ws + (int64_t)z * slice_stride + (int64_t)r * N + c, v);
+    } else {
+      for (int e = 0; e < 8; ++e) (*this)(r, c + e, v[e]);
+    }
+  }
+};
+template <>
+struct GemmGrouped<EpiPartial> : std::true_type {};
 template <class Epi>
-struct EpiArg {
-  typedef typename std::conditional<EpiByRef<Epi>::value, const Epi&, const Epi>::type type;
+constexpr bool kGemmGrouped = GemmGrouped<Epi>::value;
+
+// How a kernel holds its epilogue: a copy (told its K slice where it asks for
+// it), or (EpiByRef) a reference into the kernel arguments for one with arrays
+// that it indexes.
+template <class Epi>
+struct EpiHeld {
+  typename std::conditional<EpiByRef<Epi>::value, const Epi&, Epi>::type epi;
+  __device__ __forceinline__ EpiHeld(const Epi& e, int z) : epi(e) {
+    if constexpr (std::is_same<Epi, EpiPartial>::value) epi.z = z;
+  }
 };
 
 // ---- tile loaders: global -> registers -> LDS ------------------------------
@@ -256,13 +287,16 @@ template <typename T, int ROWS, int BK, int NT, bool IS_A, int LAYOUT>
 using Loader = typename std::conditional<LAYOUT == LAYOUT_K, LoaderK<T, ROWS, BK, NT, IS_A>,
                                          LoaderMN<T, ROWS, BK, NT, IS_A>>::type;
 
-// Tile index remap: contiguous bands per XCD, GROUP_M-row column sweeps.
-__device__ __forceinline__ void tile_coords(const GemmParams& p, int& tm, int& tn) {
-  const int T = p.tiles_m * p.tiles_n;
-  const int wg = blockIdx.x;
-  const int q = T / kNumXcd, rem = T % kNumXcd;
-  const int xcd = wg % kNumXcd, local = wg / kNumXcd;
-  const int t = (xcd < rem ? xcd * (q + 1) : rem * (q + 1) + (xcd - rem) * q) + local;
+// Workgroups go to the 8 XCDs round-robin by linear index. Work items are
+// renumbered so that each XCD takes a contiguous band of them.
+__device__ __forceinline__ int xcd_band(int item, int total) {
+  const int q = total / kNumXcd, rem = total % kNumXcd;
+  const int xcd = item % kNumXcd, local = item / kNumXcd;
+  return (xcd < rem ? xcd * (q + 1) : rem * (q + 1) + (xcd - rem) * q) + local;
+}
+
+// Tile t of a problem: GROUP_M-row column sweeps.
+__device__ __forceinline__ void tile_coords(const GemmParams& p, int t, int& tm, int& tn) {
   const int gsz = p.group_m * p.tiles_n;
   const int g = t / gsz;
   const int first_m = g * p.group_m;
@@ -503,17 +537,21 @@ __device__ __forceinline__ void pin_kstep_schedule() {
 template <typename T, int BM, int BN, int BK, int WM, int WN, int LA, int LB, class Epi>
 __global__ void __launch_bounds__(WM* WN* kWave)
     __attribute__((amdgpu_waves_per_eu(1, (BM >= 256 ? 1 : 2))))
-    gemm_kernel(const GemmParams p, const Epi epi) {
+    gemm_kernel(const GemmParams p, const Epi epi_arg) {
   typedef GemmShape<T, BM, BN, BK, WM, WN> S;
   typedef Loader<T, BM, BK, S::kThreads, true, LA> LdA;
   typedef Loader<T, BN, BK, S::kThreads, false, LB> LdB;
   typedef Mma<T> MM;
   __shared__ __attribute__((aligned(16))) T smem[2 * S::kStageElems];
 
+  const int work = xcd_band(blockIdx.x + gridDim.x * blockIdx.z, gridDim.x * gridDim.z);
+  const int z = work / (int)gridDim.x;
+  EpiHeld<Epi> held(epi_arg, z);
+  const Epi& epi = held.epi;
   int tm, tn;
-  tile_coords(p, tm, tn);
+  tile_coords(p, work % (int)gridDim.x, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
-  const int kbeg = blockIdx.z * p.k_slice;
+  const int kbeg = z * p.k_slice;
   const int kend = min(p.K, kbeg + p.k_slice);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WN, wn = wave % WN;
@@ -607,7 +645,7 @@ struct DirectOp {
   static constexpr int kInsts = kTileRows / (kRowsPerInst * WAVES);  // loads per thread per stage
   static constexpr int kElems = kTileRows * kRowElems;
   static_assert(!kMN || sizeof(T) == 2, "transpose reads take 16-bit elements");
-  static_assert(kMN ? kCpr >= 16 : (kCpr == 8 || kCpr == 4), "swizzle covers these row widths");
+  static_assert(kMN ? kCpr >= 8 : (kCpr == 8 || kCpr == 4), "swizzle covers these row widths");
   static_assert(kInsts >= 1 && kTileRows % (kRowsPerInst * WAVES) == 0, "tile rows split evenly over waves");
   // Physical chunk of logical chunk c in row r is c ^ key(r). K-major: a
   // 16-byte read pass serves 16 lanes (16 consecutive rows at one logical
@@ -616,9 +654,10 @@ struct DirectOp {
   // the 16 rows land on 16 distinct slots (a key of r & 7 would put rows r
   // and r + 8 on one slot). M/N-major: a transpose-read pass touches 4
   // consecutive rows (k) at 4 consecutive chunks; the key moves each row by
-  // 64 bytes.
+  // 64 bytes, or, with 128-byte rows (two rows span all banks), every second
+  // row.
   static __device__ __forceinline__ int key(int r) {
-    if constexpr (kMN) return (r & 3) * 4;
+    if constexpr (kMN) return kCpr == 8 ? (r & 2) * 2 : (r & 3) * 4;
     return kCpr == 8 ? ((r >> 1) & 7) : ((r >> 2) & 3);
   }
 };
@@ -680,13 +719,18 @@ template <typename T, int BM, int BN, int BK, int WM, int WN, int NS, class Epi,
 __global__ void __launch_bounds__(WM* WN* kWave)
     __attribute__((amdgpu_waves_per_eu(WM* WN / 4, (BM >= 256 ? 1 : 2) * WM * WN / 4)))
     gemm_direct_kernel(const GemmArgs<Epi, G> args) {
-  const int prob = G == 1 ? 0 : (int)blockIdx.y;
+  // work index: K slice, then problem (a batch with G = 1 keeps its own
+  // grid dimension), then tile
+  const int nx = gridDim.x, ny = G == 1 ? 1 : (int)gridDim.y;
+  const int work = xcd_band(blockIdx.x + nx * ((G == 1 ? 0 : (int)blockIdx.y) + ny * (int)blockIdx.z),
+                            nx * ny * (int)gridDim.z);
+  const int tile = work % nx, prob = G == 1 ? 0 : work / nx % ny, z = work / (nx * ny);
   // a copy, so that the choice of the problem is made once (with an indexed
   // reference the compiler kept the argument arrays in scratch memory)
   const GemmParams p = args.p[prob];
-  typename EpiArg<Epi>::type epi = args.e[prob];
-  if (G > 1 && (int)blockIdx.x >= p.tiles_m * p.tiles_n) return;  // a smaller problem of the group
-  if (G > 1 && (int)blockIdx.z * p.k_slice >= p.K && blockIdx.z > 0) return;
+  const EpiHeld<Epi> held(args.e[prob], z);
+  const Epi& epi = held.epi;
+  if (G > 1 && (tile >= p.tiles_m * p.tiles_n || (z > 0 && z * p.k_slice >= p.K))) return;  // a smaller problem
   typedef DirectShape<T, BM, BN, BK, WM, WN, NS, LA, LB> D;
   typedef typename D::S S;
   typedef typename D::OA OA;
@@ -697,9 +741,9 @@ __global__ void __launch_bounds__(WM* WN* kWave)
   T* smem = reinterpret_cast<T*>(smem_raw);
 
   int tm, tn;
-  tile_coords(p, tm, tn);
+  tile_coords(p, tile, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
-  const int kbeg = blockIdx.z * p.k_slice;
+  const int kbeg = z * p.k_slice;
   const int kend = min(p.K, kbeg + p.k_slice);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // scalar: LDS bases go to M0
@@ -960,7 +1004,7 @@ __global__ void __launch_bounds__(WM* WN* kWave)
     if (p.colsum && tn == 0 && wn < S::kFM) {
       csum += __shfl_xor(csum, 32);
       const int row = m0 + wm * S::kTM + rot * 32 + frow;
-      if (lane < 32 && row < p.M) p.colsum[(int64_t)blockIdx.z * p.M + row] = csum;
+      if (lane < 32 && row < p.M) p.colsum[(int64_t)z * p.M + row] = csum;
     }
   }
   gemm_store_wave<S, kRows>(acc, region, p, m0 + wm * S::kTM, n0 + wn * S::kTN, lane, epi, rot);
@@ -1047,28 +1091,6 @@ __global__ void __launch_bounds__(256) splitk_reduce_kernel(const ReduceArgs<Epi
   }
 }
 
-// Epilogue writing split-K partials.
-struct EpiPartial {
-  float* ws;
-  int N;
-  int64_t slice_stride;
-  __device__ __forceinline__ void operator()(int r, int c, float v) const {
-    ws[(int64_t)blockIdx.z * slice_stride + (int64_t)r * N + c] = v;
-  }
-  __device__ __forceinline__ void vec8(int r, int c, const float* v) const {
-    if ((N & 7) == 0) {
-      store8(ws + (int64_t)blockIdx.z * slice_stride + (int64_t)r * N + c, v);
-    } else {
-      for (int e = 0; e < 8; ++e) (*this)(r, c + e, v[e]);
-    }
-  }
-};
-
-template <>
-struct GemmGrouped<EpiPartial> : std::true_type {};
-template <class Epi>
-constexpr bool kGemmGrouped = GemmGrouped<Epi>::value;
-
 // ---- host side --------------------------------------------------------------
 
 struct GemmProblem {
@@ -1113,37 +1135,35 @@ struct GemmPlan {
 template <typename T>
 inline GemmPlan plan_gemm(const GemmProblem* prs, int count, int num_cu) {
   GemmPlan pl;
-  int64_t mn = 0, t256 = 0;
-  int min_m = prs[0].M, min_n = prs[0].N, max_mn = 0, max_k = 0;
+  int64_t mn = 0, t256 = 0, t128 = 0;
+  int min_m = prs[0].M, min_n = prs[0].N, max_k = 0;
   for (int i = 0; i < count; ++i) {
     const GemmProblem& q = prs[i];
     mn += (int64_t)q.M * q.N;
     t256 += (int64_t)((q.M + 255) / 256) * ((q.N + 255) / 256);
+    t128 += (int64_t)((q.M + 127) / 128) * ((q.N + 127) / 128) * q.batch;
     min_m = std::min(min_m, q.M);
     min_n = std::min(min_n, q.N);
-    max_mn = std::max(max_mn, std::max(q.M, q.N));
     max_k = std::max(max_k, q.K);
   }
+  pl.bk = sizeof(T) == 4 ? 32 : 64;
+  // 64x64 tiles where 128x128 ones, split along K into slices of eight steps,
+  // would still leave CUs without work: a product of that size waits on its
+  // operand loads, and four times the workgroups with four stages in flight
+  // instead of two wait a quarter as long.
+  const int64_t kb = (max_k + pl.bk - 1) / pl.bk;
+  const int max_dim_tile = t128 * std::max<int64_t>(1, kb / 8) < num_cu ? TILE_64x64 : TILE_128x128;
   if (sizeof(T) == 4) {
-    pl.tile = TILE_128x128;
-    pl.bm = pl.bn = 128;
-    pl.bk = 32;
+    pl.tile = max_dim_tile;
   } else if (min_m >= 256 && min_n >= 256 &&
              (mn >= (int64_t)256 * 256 * num_cu ||
               // long reductions: 256x256 tiles split along K still fill the chip
               (int64_t)max_k * t256 >= (int64_t)num_cu * 64 * 64)) {
     pl.tile = TILE_256x256;
-    pl.bm = pl.bn = 256;
-    pl.bk = 64;
-  } else if (mn >= (int64_t)128 * 128 * num_cu / 2 || max_mn > 64) {
-    pl.tile = TILE_128x128;
-    pl.bm = pl.bn = 128;
-    pl.bk = 64;
   } else {
-    pl.tile = TILE_64x64;
-    pl.bm = pl.bn = 64;
-    pl.bk = 64;
+    pl.tile = max_dim_tile;
   }
+  pl.bm = pl.bn = pl.tile == TILE_256x256 ? 256 : pl.tile == TILE_128x128 ? 128 : 64;
   int64_t tiles = 0;
   int batch = 1;
   for (int i = 0; i < count; ++i) {
@@ -1153,8 +1173,15 @@ inline GemmPlan plan_gemm(const GemmProblem* prs, int count, int num_cu) {
   const int kblocks = (max_k + pl.bk - 1) / pl.bk;
   int splits = 1;
   // Deterministic split-K when the tile grid cannot fill the chip and the
-  // reduction is long enough for each slice to stay efficient.
-  while (batch == 1 && tiles * splits < num_cu && kblocks / (splits * 2) >= 8) splits *= 2;
+  // reduction is long enough for each slice to stay efficient: eight K steps
+  // up to one workgroup per CU, sixteen up to the two 128x128 ones that fit a
+  // CU (beyond that the partials cost more than the second workgroup hides).
+  auto more = [&](int s) {
+    if (batch != 1) return false;
+    if (tiles * s < num_cu) return kblocks / (s * 2) >= 8;
+    return pl.tile == TILE_128x128 && tiles * s < 2 * num_cu && kblocks / (s * 2) >= 16;
+  };
+  while (more(splits)) splits *= 2;
   const int kb_per = (kblocks + splits - 1) / splits;
   pl.k_slice = kb_per * pl.bk;
   pl.splits = (kblocks + kb_per - 1) / kb_per;
@@ -1185,7 +1212,7 @@ inline bool gemm_runs_direct(const GemmProblem& pr, int k_slice) {
   if (LA == LAYOUT_K && LB == LAYOUT_K) return pr.ksplit3 >= pr.K;
   // M/N-major operands through LDS transpose reads: rows of such an
   // operand start 16-byte aligned and hold at least one tile width
-  return sizeof(T) == 2 && BM >= 128 && BN >= 128 && (LA == LAYOUT_K || (pr.lda % 8 == 0 && pr.lda >= BM)) &&
+  return sizeof(T) == 2 && (LA == LAYOUT_K || (pr.lda % 8 == 0 && pr.lda >= BM)) &&
          (LB == LAYOUT_K || (pr.ldb % 8 == 0 && pr.ldb >= BN));
 }
 
@@ -1239,7 +1266,8 @@ inline hipError_t launch_gemm_tile(const GemmProblem* prs, int count, const Gemm
   // 256x256 tiles run as 8 waves of 128x64: two waves per SIMD, so one
   // wave's MFMAs cover the other's load issue and barrier waits.
   constexpr int DWN = (BM == 256 && BN == 256) ? 4 : WN;
-  constexpr bool kCanDirect = (LA == LAYOUT_K && LB == LAYOUT_K) || (sizeof(T) == 2 && BM >= 128 && BN >= 128);
+  constexpr bool kCanDirect = (LA == LAYOUT_K && LB == LAYOUT_K) || sizeof(T) == 2;
+  constexpr int NS = BM * BN * (int)sizeof(T) <= 64 * 64 * 4 ? 4 : 2;  // stages of the operand ring
   if constexpr (kCanDirect) {
     if (direct) {
       auto go = [&](auto group) {
@@ -1252,12 +1280,12 @@ inline hipError_t launch_gemm_tile(const GemmProblem* prs, int count, const Gemm
         const dim3 grid(tiles, G == 1 ? prs[0].batch : count, splits), block(WM * DWN * kWave);
         if constexpr (LA == LAYOUT_K && LB == LAYOUT_K) {
           if (whole) {
-            hipLaunchKernelGGL((gemm_direct_kernel<T, BM, BN, BK, WM, DWN, 2, Epi, LAYOUT_K, LAYOUT_K, true, G>), grid,
+            hipLaunchKernelGGL((gemm_direct_kernel<T, BM, BN, BK, WM, DWN, NS, Epi, LAYOUT_K, LAYOUT_K, true, G>), grid,
                                block, 0, stream, args);
             return hipGetLastError();
           }
         }
-        hipLaunchKernelGGL((gemm_direct_kernel<T, BM, BN, BK, WM, DWN, 2, Epi, LA, LB, false, G>), grid, block, 0,
+        hipLaunchKernelGGL((gemm_direct_kernel<T, BM, BN, BK, WM, DWN, NS, Epi, LA, LB, false, G>), grid, block, 0,
                            stream, args);
         return hipGetLastError();
       };
@@ -1286,7 +1314,8 @@ inline bool gemm_plan_direct(const GemmProblem* prs, int count, const GemmPlan& 
     const int ks = plan_k_slice(prs[i], pl);
     bool ok;
     if constexpr (sizeof(T) == 4)
-      ok = gemm_runs_direct<T, 128, 128, 32, LA, LB>(prs[i], ks);
+      ok = pl.tile == TILE_64x64 ? gemm_runs_direct<T, 64, 64, 32, LA, LB>(prs[i], ks)
+                                 : gemm_runs_direct<T, 128, 128, 32, LA, LB>(prs[i], ks);
     else if (pl.tile == TILE_256x256)
       ok = gemm_runs_direct<T, 256, 256, 64, LA, LB>(prs[i], ks);
     else if (pl.tile == TILE_128x128)
@@ -1302,6 +1331,7 @@ template <typename T, int LA, int LB, class Epi>
 inline hipError_t launch_gemm_plan(const GemmProblem* prs, int count, const GemmPlan& pl, const Epi* epis,
                                    hipStream_t stream) {
   if constexpr (sizeof(T) == 4) {
+    if (pl.tile == TILE_64x64) return launch_gemm_tile<T, 64, 64, 32, 2, 2, LA, LB>(prs, count, pl, epis, stream);
     return launch_gemm_tile<T, 128, 128, 32, 2, 2, LA, LB>(prs, count, pl, epis, stream);
   } else {
     switch (pl.tile) {

@@ -58,7 +58,7 @@ struct Runner {
       sl[i] = prs[i];
       if (sl[i].colsum) sl[i].colsum = prs[i].cs_part;  // per-slice sums, joined by the reduction
       parts[i] = at;
-      part[i] = EpiPartial{at, prs[i].N, (int64_t)prs[i].M * prs[i].N};
+      part[i] = EpiPartial{at, prs[i].N, (int64_t)prs[i].M * prs[i].N, 0};
       at += plan_partials(prs[i], pl);
     }
     timed(label, [&] { return launch_gemm_plan<T, LA, LB>(sl, count, pl, part, stream); });

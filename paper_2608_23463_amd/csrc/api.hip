@@ -387,7 +387,8 @@ int proxy_decode_step_static(const pf_decode_config* cfg, const pf_decode_weight
     n_max = 0;
     for (int b = 0; b < d.B; ++b) n_max = std::max<int64_t>(n_max, st->n_seq[b]);
   }
-  const DecodeWs W = decode_step_ws(d, n_max);
+  DecodeWs W = decode_step_ws(d, n_max, false);
+  if (W.bytes > kStaticScratchBytes) W = decode_step_ws(d, n_max, true);
   if (W.bytes > kStaticScratchBytes)
     return fail(PF_ERR_UNSUPPORTED,
                 "proxy_decode_step_static: this step needs %zu bytes of scratch, the static scratch holds %zu "

@@ -1,6 +1,7 @@
 // Proxy-KV-cache decode step and block-triggered append (Eq. 19-21, Sec. 3.8).
 //
-// Step (one token per sequence, the batch in lockstep), four launches:
+// Step (one token per sequence, the batch in lockstep), four launches (three
+// for up to four sequences over few slices, see decode_gemv_out_kernel):
 //  1. decode_proj_kernel: u = RMSNorm(x) * gamma formed on the fly and
 //     multiplied by W_q, W_k, W_v and W_alpha (one 32-column block of the
 //     concatenated outputs per workgroup, MFMA over 32 batch rows): q to
@@ -323,21 +324,19 @@ struct DecodeAttnParams {
   DecodePos pos;       // per-sequence n and j when pos.ragged
 };
 
-// A[b, h, c] = A_x + alpha * A_h from the partials of one (sequence, head):
-// cache slices merged in a fixed order with a running maximum (A_h, zero
-// without cached rows), local slice normalised (A_x). A lane takes channels
-// c0, c0 + 64, ... (kC of them); the loads of up to kBatch slices, the local
-// part and alpha go out together before any is used, so a step with up to
-// kBatch slices waits for memory once.
-template <typename T, int DH>
-__device__ __forceinline__ void combine_partials(const DecodeAttnParams& p, int bh, int b, int h, int c0) {
-  constexpr int kC = DH / 64, kBatch = 32;
+// out[u] = A[b, h, c0 + u * kStride] = A_x + alpha * A_h from the partials of
+// one (sequence, head): cache slices merged in a fixed order with a running
+// maximum (A_h, zero without cached rows), local slice normalised (A_x). The
+// loads of up to kBatch slices, the local part and alpha go out together
+// before any is used, so a step with up to kBatch slices waits for memory once.
+template <int DH, int kC, int kStride, int kBatch>
+__device__ __forceinline__ void merge_partials(const DecodeAttnParams& p, int bh, int c0, float (&out)[kC]) {
   const int64_t base = (int64_t)bh * (p.splits + 1);
-  const float al = p.alpha[(int64_t)b * p.nh + h];
+  const float al = p.alpha[bh];  // alpha is [B, h] as the partials are
   const float lx = p.part_l[base + p.splits];
   float ax[kC];
 #pragma unroll
-  for (int u = 0; u < kC; ++u) ax[u] = p.part_acc[(base + p.splits) * DH + c0 + 64 * u];
+  for (int u = 0; u < kC; ++u) ax[u] = p.part_acc[(base + p.splits) * DH + c0 + kStride * u];
   float mrun = -INFINITY, lrun = 0.0f, arun[kC];
 #pragma unroll
   for (int u = 0; u < kC; ++u) arun[u] = 0.0f;
@@ -349,7 +348,7 @@ __device__ __forceinline__ void combine_partials(const DecodeAttnParams& p, int 
       m[i] = p.part_m[base + s];
       l[i] = p.part_l[base + s];
 #pragma unroll
-      for (int u = 0; u < kC; ++u) a[i][u] = p.part_acc[(base + s) * DH + c0 + 64 * u];
+      for (int u = 0; u < kC; ++u) a[i][u] = p.part_acc[(base + s) * DH + c0 + kStride * u];
     }
 #pragma unroll
     for (int i = 0; i < kBatch; ++i) {
@@ -362,12 +361,8 @@ __device__ __forceinline__ void combine_partials(const DecodeAttnParams& p, int 
       mrun = mn;
     }
   }
-  T* out = reinterpret_cast<T*>(p.attn) + (int64_t)b * p.nh * DH + h * DH;
 #pragma unroll
-  for (int u = 0; u < kC; ++u) {
-    const float ah = mrun == -INFINITY ? 0.0f : arun[u] / lrun;
-    out[c0 + 64 * u] = from_f32<T>(ax[u] / lx + al * ah);
-  }
+  for (int u = 0; u < kC; ++u) out[u] = ax[u] / lx + al * (mrun == -INFINITY ? 0.0f : arun[u] / lrun);
 }
 
 template <typename T, int DH>
@@ -451,24 +446,40 @@ __global__ void __launch_bounds__(256) decode_attn_kernel(const DecodeAttnParams
     }
   }
 
-  // merge the 4 * RPW row slots of the workgroup (fixed order)
-  __shared__ float sm[4 * RPW];
-  __shared__ float sl[4 * RPW];
-  __shared__ float sacc[4 * RPW][DH];
-  const int slot = wave * RPW + rslot;
-  if (sub == 0) {
-    sm[slot] = mrun;
-    sl[slot] = lrun;
-  }
+  // Merge of the row slots (fixed order): a butterfly over the RPW slots of a
+  // wave, then the four waves through LDS. (Through LDS alone, 4 * RPW slots
+  // one after the other, the tail took longer than a 128-row slice's reads.)
 #pragma unroll
-  for (int i = 0; i < kVec; ++i) sacc[slot][sub * kVec + i] = acc[i];
+  for (int off = LPR; off < kWave; off <<= 1) {
+    const float mo = __shfl_xor(mrun, off), lo = __shfl_xor(lrun, off);
+    const float mn = fmaxf(mrun, mo);
+    const float f0 = mrun == -INFINITY ? 0.0f : fast_exp2(mrun - mn);
+    const float f1 = mo == -INFINITY ? 0.0f : fast_exp2(mo - mn);
+    lrun = lrun * f0 + lo * f1;
+#pragma unroll
+    for (int i = 0; i < kVec; ++i) acc[i] = acc[i] * f0 + __shfl_xor(acc[i], off) * f1;
+    mrun = mn;
+  }
+  __shared__ float sm[4];
+  __shared__ float sl[4];
+  __shared__ float sacc[4][DH];
+  if (lane == 0) {
+    sm[wave] = mrun;
+    sl[wave] = lrun;
+  }
+  if (rslot == 0) {
+#pragma unroll
+    for (int i = 0; i < kVec; ++i) sacc[wave][sub * kVec + i] = acc[i];
+  }
   __syncthreads();
   if (tid < DH) {
     float mx = -INFINITY;
-    for (int i = 0; i < 4 * RPW; ++i) mx = fmaxf(mx, sm[i]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) mx = fmaxf(mx, sm[i]);
     float l = 0.0f, a = 0.0f;
     if (mx != -INFINITY) {
-      for (int i = 0; i < 4 * RPW; ++i) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
         const float f = fast_exp2(sm[i] - mx);
         l += sl[i] * f;
         a += sacc[i][tid] * f;
@@ -484,13 +495,180 @@ __global__ void __launch_bounds__(256) decode_attn_kernel(const DecodeAttnParams
 }
 
 // Merge of the partials of every (sequence, head): one wave per (sequence,
-// head), DH / 64 channels per lane; see combine_partials.
+// head), DH / 64 channels per lane; see merge_partials.
 template <typename T, int DH>
 __global__ void __launch_bounds__(256) decode_combine_kernel(const DecodeAttnParams p, int nbh) {
   const int bh = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (bh >= nbh) return;
   const int b = bh / p.nh, h = bh % p.nh, lane = threadIdx.x & 63;
-  combine_partials<T, DH>(p, bh, b, h, lane);
+  float v[DH / 64];
+  merge_partials<DH, DH / 64, 64, 32>(p, bh, lane, v);
+  T* out = reinterpret_cast<T*>(p.attn) + (int64_t)b * p.nh * DH + h * DH;
+#pragma unroll
+  for (int u = 0; u < DH / 64; ++u) out[lane + 64 * u] = from_f32<T>(v[u]);
+}
+
+// ---- projections of one to four sequences ---------------------------------------
+//
+// With a few rows the matrix kernel above spends its time on 32 staged rows,
+// most of them copies, and on the 1,400 instructions before its first product
+// (8.8 us for one sequence at d = 512, the weights a 2 us read; 4.6 us so, a
+// step of 4 sequences at d = 1024 over 1,000 rows 26.7 -> 22.7 us). Here a wave
+// takes four output columns and every row: its weights (16-byte loads along
+// a row), the rows and gamma are requested at once, the row norms and the
+// dot products are butterflies over the wave, and there is no LDS or barrier.
+constexpr int kGemvRows = 4;      // sequences
+constexpr int kGemvCols = 4;      // output columns per wave
+
+template <int N>
+__device__ __forceinline__ void wave_sums(float (&v)[N]) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] += __shfl_xor(v[i], off);
+}
+
+// Step 1 (see DecodeProjParams): q, k, v, alpha of the new token, and x into
+// its block slot.
+template <typename T, int NB, int CPL>
+__global__ void __launch_bounds__(256) decode_gemv_proj_kernel(const DecodeProjParams p) {
+  constexpr int kV = 16 / sizeof(T);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int cpr = p.d / kV;
+  const int c0 = (blockIdx.x * 4 + wave) * kGemvCols;
+  const int seg = min(c0 / p.d, 3), cs = c0 - seg * p.d, width = p.width[seg];
+  if (cs >= width) return;
+  const T* x = reinterpret_cast<const T*>(p.x);
+  const T* w = reinterpret_cast<const T*>(p.w[seg]);
+  u32x4 wr[kGemvCols][CPL], xr[NB][CPL], gr[CPL];
+#pragma unroll
+  for (int i = 0; i < CPL; ++i) {
+    const int ci = min(lane + 64 * i, cpr - 1) * kV;  // lanes past the row repeat its end, masked below
+#pragma unroll
+    for (int b = 0; b < NB; ++b) xr[b][i] = ld16(x + (int64_t)min(b, p.B - 1) * p.d + ci);
+    gr[i] = ld16(reinterpret_cast<const T*>(p.gamma) + ci);
+#pragma unroll
+    for (int u = 0; u < kGemvCols; ++u) wr[u][i] = ld16(w + (int64_t)min(cs + u, width - 1) * p.d + ci);
+  }
+  const int ob = lane / kGemvCols, oc = cs + lane % kGemvCols;  // this lane's output
+  const T* bias = reinterpret_cast<const T*>(p.bias[seg]);
+  const float bv = bias ? to_f32(bias[min(oc, width - 1)]) : 0.0f;
+  if (blockIdx.x == 0) {  // x into block slot j, one row per wave
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+      if (wave == b % 4 && b < p.B)
+#pragma unroll
+        for (int i = 0; i < CPL; ++i)
+          if (lane + 64 * i < cpr)
+            st16(reinterpret_cast<T*>(p.x_blk) + ((int64_t)b * p.P + p.slot(b)) * p.d + (lane + 64 * i) * kV, xr[b][i]);
+  }
+  float ss[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    ss[b] = 0.0f;
+#pragma unroll
+    for (int i = 0; i < CPL; ++i) {
+      const T* v = reinterpret_cast<const T*>(&xr[b][i]);
+      if (lane + 64 * i < cpr)
+#pragma unroll
+        for (int e = 0; e < kV; ++e) ss[b] += to_f32(v[e]) * to_f32(v[e]);
+    }
+  }
+  wave_sums(ss);
+  float acc[NB * kGemvCols];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const float inv = 1.0f / sqrtf(ss[b] / (float)p.d + p.eps);
+#pragma unroll
+    for (int u = 0; u < kGemvCols; ++u) acc[b * kGemvCols + u] = 0.0f;
+#pragma unroll
+    for (int i = 0; i < CPL; ++i) {
+      const T* xv = reinterpret_cast<const T*>(&xr[b][i]);
+      const T* gv = reinterpret_cast<const T*>(&gr[i]);
+      const bool ok = lane + 64 * i < cpr;
+#pragma unroll
+      for (int e = 0; e < kV; ++e) {  // u rounded to the activation type, as a stored u would be
+        const float uv = ok ? to_f32(from_f32<T>(to_f32(xv[e]) * inv * to_f32(gv[e]))) : 0.0f;
+#pragma unroll
+        for (int u = 0; u < kGemvCols; ++u)
+          acc[b * kGemvCols + u] = fmaf(uv, to_f32(reinterpret_cast<const T*>(&wr[u][i])[e]), acc[b * kGemvCols + u]);
+      }
+    }
+  }
+  wave_sums(acc);
+  float v = bv;
+#pragma unroll
+  for (int k = 0; k < NB * kGemvCols; ++k)
+    if (lane == k) v += acc[k];
+  if (ob >= p.B || ob >= NB || oc >= width) return;
+  if (seg == 0) {
+    reinterpret_cast<T*>(p.q)[(int64_t)ob * p.d + oc] = from_f32<T>(v);
+  } else if (seg < 3) {
+    T* dst = reinterpret_cast<T*>(seg == 1 ? p.k_loc : p.v_loc);
+    const int hd = oc / p.dh, e = oc - hd * p.dh;
+    dst[(((int64_t)ob * p.nh + hd) * p.P + p.slot(ob)) * p.dh + e] = from_f32<T>(v);
+  } else {
+    p.alpha[(int64_t)ob * p.nh + oc] = sigmoidf(v);
+  }
+}
+
+// Steps 3 and 4 in one launch: every workgroup merges the slice partials of
+// all rows into A (rounded to the activation type, as a stored A would be) in
+// LDS while its weights are on their way, then y = x + A W_o^T + b_o for its
+// sixteen columns. The partials are read by every workgroup, so this pays
+// while they are few (see step_impl).
+template <typename T, int DH, int NB, int CPL>
+__global__ void __launch_bounds__(256) decode_gemv_out_kernel(const DecodeProjParams p, const DecodeAttnParams ap) {
+  constexpr int kV = 16 / sizeof(T);
+  __shared__ __attribute__((aligned(16))) T a_s[NB * CPL * 64 * kV];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int cpr = p.d / kV;
+  const int c0 = (blockIdx.x * 4 + wave) * kGemvCols;  // d is a multiple of 64: no partial group
+  const T* w = reinterpret_cast<const T*>(p.w[0]);
+  u32x4 wr[kGemvCols][CPL];
+#pragma unroll
+  for (int i = 0; i < CPL; ++i)
+#pragma unroll
+    for (int u = 0; u < kGemvCols; ++u)
+      wr[u][i] = ld16(w + (int64_t)(c0 + u) * p.d + min(lane + 64 * i, cpr - 1) * kV);
+  const int ob = lane / kGemvCols, oc = c0 + lane % kGemvCols;
+  const T* bias = reinterpret_cast<const T*>(p.bias[0]);
+  const float bv = bias ? to_f32(bias[oc]) : 0.0f;
+  const float xv = to_f32(reinterpret_cast<const T*>(p.x)[(int64_t)min(ob, p.B - 1) * p.d + oc]);
+  for (int it = tid; it < p.B * p.d / 2; it += 256) {
+    const int b = it / (p.d / 2), c = 2 * (it - b * (p.d / 2));
+    float v[2];
+    merge_partials<DH, 2, 1, 16>(ap, b * ap.nh + c / DH, c % DH, v);
+    a_s[b * p.d + c] = from_f32<T>(v[0]);
+    a_s[b * p.d + c + 1] = from_f32<T>(v[1]);
+  }
+  __syncthreads();
+  float acc[NB * kGemvCols];
+#pragma unroll
+  for (int k = 0; k < NB * kGemvCols; ++k) acc[k] = 0.0f;
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    if (b >= p.B) break;
+#pragma unroll
+    for (int i = 0; i < CPL; ++i) {
+      const bool ok = lane + 64 * i < cpr;
+      const u32x4 raw = ld16(a_s + b * p.d + min(lane + 64 * i, cpr - 1) * kV);
+      const T* av = reinterpret_cast<const T*>(&raw);
+#pragma unroll
+      for (int e = 0; e < kV; ++e) {
+        const float a = ok ? to_f32(av[e]) : 0.0f;
+#pragma unroll
+        for (int u = 0; u < kGemvCols; ++u)
+          acc[b * kGemvCols + u] = fmaf(a, to_f32(reinterpret_cast<const T*>(&wr[u][i])[e]), acc[b * kGemvCols + u]);
+      }
+    }
+  }
+  wave_sums(acc);
+  float v = bv;
+#pragma unroll
+  for (int k = 0; k < NB * kGemvCols; ++k)
+    if (lane == k) v += acc[k];
+  if (ob < p.B && ob < NB) reinterpret_cast<T*>(p.y)[(int64_t)ob * p.d + oc] = from_f32<T>(xv + v);
 }
 
 // Proxy K/V rows into the cache: row rr = r0 + r is (sequence rr / nblk,
@@ -582,16 +760,16 @@ static void append_impl(Runner& run, const DecodeDims& d, const DecodeWs& W, con
   }
 }
 
-void split_plan(int64_t n, int* splits, int* chunk) {
-  if (n <= 0) {
-    *splits = 0;
-    *chunk = kDecodeRowsPerSplit;
-    return;
-  }
+// Rows per slice: 1,024, or less (down to the 128 rows that a workgroup reads
+// at once) while the slices of all (sequence, head) pairs are too few to give
+// every CU four workgroups: one sequence of 8 heads over 1,500 rows ran as 24
+// workgroups of eight dependent reads each. `lean`: never less than 1,024.
+void split_plan(int64_t n, int64_t pairs, bool lean, int* splits, int* chunk) {
   int64_t c = kDecodeRowsPerSplit;
+  while (!lean && c > 128 && pairs * ((n + c - 1) / c) < 1024) c /= 2;
   if ((n + c - 1) / c > kDecodeMaxSplits) c = (n + kDecodeMaxSplits - 1) / kDecodeMaxSplits;
   *chunk = (int)c;
-  *splits = (int)((n + c - 1) / c);
+  *splits = n <= 0 ? 0 : (int)((n + c - 1) / c);
 }
 
 // Lets a kernel use up to 160 KB of dynamic LDS, once per (kernel, device).
@@ -626,6 +804,59 @@ static hipError_t launch_small_gemm(dim3 grid, const DecodeProjParams& pp, hipSt
   return go(decode_small_gemm_kernel<T, PROJ, 4>);
 }
 
+// Instance by rows (1, 2 or up to 4) and 16-byte chunks per lane and row.
+template <class F>
+static hipError_t gemv_pick(int rows, int cpr, F&& go) {
+  auto by_rows = [&](auto cpl) {
+    if (rows <= 1) return go(std::integral_constant<int, 1>{}, cpl);
+    if (rows <= 2) return go(std::integral_constant<int, 2>{}, cpl);
+    return go(std::integral_constant<int, kGemvRows>{}, cpl);
+  };
+  if (cpr <= 64) return by_rows(std::integral_constant<int, 1>{});
+  if (cpr <= 128) return by_rows(std::integral_constant<int, 2>{});
+  return by_rows(std::integral_constant<int, 4>{});
+}
+
+template <typename T>
+static hipError_t launch_gemv_proj(const DecodeProjParams& pp, hipStream_t stream) {
+  const int cols = 3 * pp.d + (pp.nh + kGemvCols - 1) / kGemvCols * kGemvCols;
+  return gemv_pick(pp.B, pp.d * (int)sizeof(T) / 16, [&](auto nb, auto cpl) {
+    hipLaunchKernelGGL((decode_gemv_proj_kernel<T, decltype(nb)::value, decltype(cpl)::value>),
+                       dim3((cols + 4 * kGemvCols - 1) / (4 * kGemvCols)), dim3(256), 0, stream, pp);
+    return hipGetLastError();
+  });
+}
+
+// The merge joins the output map while a workgroup's copy of the partials is
+// at most kMergeInOutBytes and its threads merge at most two channel pairs
+// each, one after the other. Measured per step, merged against the merge of
+// its own launch: 8 heads x 200 rows 12.8 us, 16 heads x 2,000 rows (72 KB)
+// 16.6; past the first bound 16 heads x 8,000 rows (271 KB) 30.6 against 25.9,
+// past the second 4 sequences of 16 heads x 200 rows (eight pairs) 30.6
+// against 25.2 with the matrix kernels.
+constexpr int64_t kMergeInOutBytes = 128 << 10;
+constexpr int kMergeInOutChannels = 1024;
+
+template <typename T>
+static hipError_t launch_gemv_out(const DecodeProjParams& op, const DecodeAttnParams& ap, int dh, hipStream_t stream) {
+  const dim3 grid(op.d / (4 * kGemvCols));
+  auto go = [&](auto nb, auto cpl) {
+    constexpr int NB = decltype(nb)::value, CPL = decltype(cpl)::value;
+    if (dh == 64)
+      hipLaunchKernelGGL((decode_gemv_out_kernel<T, 64, NB, CPL>), grid, dim3(256), 0, stream, op, ap);
+    else
+      hipLaunchKernelGGL((decode_gemv_out_kernel<T, 128, NB, CPL>), grid, dim3(256), 0, stream, op, ap);
+    return hipGetLastError();
+  };
+  const int cpr = op.d * (int)sizeof(T) / 16;
+  typedef std::integral_constant<int, 1> one;
+  typedef std::integral_constant<int, 2> two;
+  typedef std::integral_constant<int, 4> four;
+  if (op.B > 1) return cpr <= 64 ? go(four{}, one{}) : go(four{}, two{});  // d <= 512
+  if (cpr <= 64) return go(one{}, one{});
+  return cpr <= 128 ? go(one{}, two{}) : go(one{}, four{});
+}
+
 template <typename T>
 static void step_impl(Runner& run, const DecodeDims& d, const DecodeWs& W, const pf_decode_weights* w,
                       const pf_decode_state& st, const DecodePos& pos, const void* x_t, void* y_t, char* ws) {
@@ -657,7 +888,9 @@ static void step_impl(Runner& run, const DecodeDims& d, const DecodeWs& W, const
   pp.x_blk = st.x_blk;
   pp.pos = pos;
   static_assert(decode_small_gemm_lds<T>(2048 * 2 / sizeof(T)) <= 160 * 1024, "staged rows fit the LDS");
+  const bool gemv = d.B <= kGemvRows;
   run.launch("decode_proj", [&] {
+    if (gemv) return launch_gemv_proj<T>(pp, run.stream);
     const dim3 grid(3 * d.d / 32 + (d.nh + 31) / 32, rblocks);
     return launch_small_gemm<T, true>(grid, pp, run.stream);
   });
@@ -668,7 +901,7 @@ static void step_impl(Runner& run, const DecodeDims& d, const DecodeWs& W, const
     for (int b = 0; b < d.B; ++b) n_max = std::max<int64_t>(n_max, pos.n[b]);
   }
   int splits, chunk;
-  split_plan(n_max, &splits, &chunk);
+  split_plan(n_max, (int64_t)d.B * d.nh, W.lean, &splits, &chunk);
   DecodeAttnParams ap{};
   ap.q = q;
   ap.kc = st.k_cache;
@@ -697,16 +930,6 @@ static void step_impl(Runner& run, const DecodeDims& d, const DecodeWs& W, const
       hipLaunchKernelGGL((decode_attn_kernel<T, 128>), grid, dim3(256), 0, run.stream, ap);
     return hipGetLastError();
   });
-  run.launch("decode_combine", [&] {
-    const int nbh = d.B * d.nh;
-    const dim3 grid((nbh + 3) / 4);
-    if (d.dh == 64)
-      hipLaunchKernelGGL((decode_combine_kernel<T, 64>), grid, dim3(256), 0, run.stream, ap, nbh);
-    else
-      hipLaunchKernelGGL((decode_combine_kernel<T, 128>), grid, dim3(256), 0, run.stream, ap, nbh);
-    return hipGetLastError();
-  });
-
   DecodeProjParams op{};
   op.x = x_t;
   op.a = attn;
@@ -716,6 +939,20 @@ static void step_impl(Runner& run, const DecodeDims& d, const DecodeWs& W, const
   op.B = d.B;
   op.d = d.d;
   op.y = y_t;
+  const int64_t part_bytes = (int64_t)d.B * d.nh * (splits + 1) * (d.dh + 2) * 4;
+  if (gemv && part_bytes <= kMergeInOutBytes && d.B * d.d <= kMergeInOutChannels) {
+    run.launch("decode_out", [&] { return launch_gemv_out<T>(op, ap, d.dh, run.stream); });
+    return;
+  }
+  run.launch("decode_combine", [&] {
+    const int nbh = d.B * d.nh;
+    const dim3 grid((nbh + 3) / 4);
+    if (d.dh == 64)
+      hipLaunchKernelGGL((decode_combine_kernel<T, 64>), grid, dim3(256), 0, run.stream, ap, nbh);
+    else
+      hipLaunchKernelGGL((decode_combine_kernel<T, 128>), grid, dim3(256), 0, run.stream, ap, nbh);
+    return hipGetLastError();
+  });
   run.launch("decode_out", [&] {
     const dim3 grid(d.d / 32, rblocks);
     return launch_small_gemm<T, false>(grid, op, run.stream);
@@ -770,12 +1007,14 @@ DecodeWs decode_ws(const DecodeDims& d) {
   return w;
 }
 
-DecodeWs decode_step_ws(const DecodeDims& d, int64_t n_max) {
+DecodeWs decode_step_ws(const DecodeDims& d, int64_t n_max, bool lean) {
   int splits, chunk;
-  split_plan(n_max, &splits, &chunk);
+  split_plan(n_max, (int64_t)d.B * d.nh, lean, &splits, &chunk);
   // the step appends at most one block per sequence: B rows
   DecodeWs w = decode_ws_layout(d, splits, (int)std::min<int64_t>(d.append_rows, d.B));
+  w.lean = lean;
   Runner dry(true);
+  dry.lean = lean;
   pf_decode_weights nw{};
   pf_decode_state ns{};
   ns.n_cap = 1;
@@ -797,6 +1036,7 @@ hipError_t decode_step_run(const DecodeDims& d, const DecodeWs& W, const pf_deco
                            const pf_decode_state& st, const DecodePos& pos, const void* x_t, void* y_t, char* ws,
                            hipStream_t stream) {
   Runner run(false, stream, reinterpret_cast<float*>(ws + W.gemm));
+  run.lean = W.lean;
   step_impl<T>(run, d, W, w, st, pos, x_t, y_t, ws);
   return run.err;
 }
@@ -806,6 +1046,7 @@ hipError_t cache_append_run(const DecodeDims& d, const DecodeWs& W, const pf_dec
                             const pf_decode_state& st, const DecodePos& pos, const void* x_blocks, int64_t nblk,
                             char* ws, hipStream_t stream) {
   Runner run(false, stream, reinterpret_cast<float*>(ws + W.gemm));
+  run.lean = W.lean;
   append_impl<T>(run, d, W, w, st, pos, x_blocks, nblk, ws);
   return run.err;
 }

@@ -43,6 +43,7 @@ struct DecodeWs {
   size_t z[PF_MAX_LEVELS];          // append: compression level outputs (j = 1..M)
   size_t gemm;
   size_t bytes;
+  bool lean;                        // the plans with the least scratch
 };
 
 int decode_dims(const pf_decode_config* c, DecodeDims* d, const char** why);
@@ -50,10 +51,13 @@ int decode_dims(const pf_decode_config* c, DecodeDims* d, const char** why);
 DecodeWs decode_ws(const DecodeDims& d);
 // Scratch of one decode step whose longest cache holds n_max rows: its own
 // slice partials and the append of one block per sequence (smaller than
-// decode_ws; the layout differs, the kernels are the same).
-DecodeWs decode_step_ws(const DecodeDims& d, int64_t n_max);
-// Cache slices the decode attention cuts n rows into, and their length.
-void split_plan(int64_t n, int* splits, int* chunk);
+// decode_ws; the layout differs, the kernels are the same). `lean`: the
+// plans with the least scratch (fewest slices and partials), for a caller
+// whose scratch is fixed.
+DecodeWs decode_step_ws(const DecodeDims& d, int64_t n_max, bool lean);
+// Cache slices the decode attention cuts n rows of each of `pairs`
+// (sequence, head) pairs into, and their length.
+void split_plan(int64_t n, int64_t pairs, bool lean, int* splits, int* chunk);
 
 // `pos` carries the per-sequence positions when st.n_seq / st.j_seq are set;
 // W is the scratch layout inside ws.

@@ -1131,12 +1131,14 @@ struct GemmPlan {
 };
 
 // One plan for a group of problems launched together (their tiles fill the
-// chip together; each has its own k_slice).
+// chip together; each has its own k_slice). `lean`: 128x128 tiles for all but
+// the smallest products and at most one workgroup per CU, which bounds the
+// split-K partials by 32 MiB.
 template <typename T>
-inline GemmPlan plan_gemm(const GemmProblem* prs, int count, int num_cu) {
+inline GemmPlan plan_gemm(const GemmProblem* prs, int count, int num_cu, bool lean = false) {
   GemmPlan pl;
   int64_t mn = 0, t256 = 0, t128 = 0;
-  int min_m = prs[0].M, min_n = prs[0].N, max_k = 0;
+  int min_m = prs[0].M, min_n = prs[0].N, max_mn = 0, max_k = 0;
   for (int i = 0; i < count; ++i) {
     const GemmProblem& q = prs[i];
     mn += (int64_t)q.M * q.N;
@@ -1144,6 +1146,7 @@ inline GemmPlan plan_gemm(const GemmProblem* prs, int count, int num_cu) {
     t128 += (int64_t)((q.M + 127) / 128) * ((q.N + 127) / 128) * q.batch;
     min_m = std::min(min_m, q.M);
     min_n = std::min(min_n, q.N);
+    max_mn = std::max(max_mn, std::max(q.M, q.N));
     max_k = std::max(max_k, q.K);
   }
   pl.bk = sizeof(T) == 4 ? 32 : 64;
@@ -1152,7 +1155,8 @@ inline GemmPlan plan_gemm(const GemmProblem* prs, int count, int num_cu) {
   // operand loads, and four times the workgroups with four stages in flight
   // instead of two wait a quarter as long.
   const int64_t kb = (max_k + pl.bk - 1) / pl.bk;
-  const int max_dim_tile = t128 * std::max<int64_t>(1, kb / 8) < num_cu ? TILE_64x64 : TILE_128x128;
+  const bool small = lean ? sizeof(T) == 2 && max_mn <= 64 : t128 * std::max<int64_t>(1, kb / 8) < num_cu;
+  const int max_dim_tile = small ? TILE_64x64 : TILE_128x128;
   if (sizeof(T) == 4) {
     pl.tile = max_dim_tile;
   } else if (min_m >= 256 && min_n >= 256 &&
@@ -1179,7 +1183,7 @@ inline GemmPlan plan_gemm(const GemmProblem* prs, int count, int num_cu) {
   auto more = [&](int s) {
     if (batch != 1) return false;
     if (tiles * s < num_cu) return kblocks / (s * 2) >= 8;
-    return pl.tile == TILE_128x128 && tiles * s < 2 * num_cu && kblocks / (s * 2) >= 16;
+    return !lean && pl.tile == TILE_128x128 && tiles * s < 2 * num_cu && kblocks / (s * 2) >= 16;
   };
   while (more(splits)) splits *= 2;
   const int kb_per = (kblocks + splits - 1) / splits;

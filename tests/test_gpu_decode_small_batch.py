@@ -1,0 +1,87 @@
+"""Decode steps of one to five sequences (the wave-per-columns projections and
+the merge inside the output map take up to four) and short cache slices, at
+the sizes where they can go wrong: widths of one to four 16-byte chunks per
+lane, head counts that are no multiple of four, caches at and around the slice
+edges, empty caches, positions per sequence, and steps across an append."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2608_23463_amd import synth
+from helpers import TOL, dev, dev_weights, host
+
+pytestmark = pytest.mark.gpu
+
+CASES = {
+    # name: (batch, n_heads, head_dim, dtype, cached rows)
+    "B1_d128_empty": (1, 2, 64, "bf16", 0),
+    "B1_d64_n1": (1, 1, 64, "bf16", 1),
+    "B1_d576_n127": (1, 9, 64, "bf16", 127),
+    "B2_d512_n128": (2, 8, 64, "bf16", 128),
+    "B3_d640_n129_dh128": (3, 5, 128, "bf16", 129),
+    "B4_d1024_n700": (4, 16, 64, "bf16", 700),
+    "B4_d2048_n300_dh128": (4, 16, 128, "bf16", 300),   # four chunks per lane
+    "B2_d512_n700_merged": (2, 8, 64, "bf16", 700),      # two rows in the merged output map
+    "B4_d256_fp32_n90": (4, 4, 64, "fp32", 90),
+    "B4_d1024_n3000_combine": (4, 16, 64, "bf16", 3000),  # partials past the merge's bound
+    "B5_d512_n500": (5, 8, 64, "bf16", 500),            # one past the small-batch kernels
+    "B1_d1024_fp32_n260": (1, 16, 64, "fp32", 260),     # four chunks per lane in fp32
+    "B3_d192_fp32_n1100": (3, 3, 64, "fp32", 1100),
+}
+
+
+def weights_of(inp, dtype):
+    """The drawn weights with sharper queries and a larger output map, so that
+    the cached read moves y by more than its tolerance."""
+    w = dict(inp["weights"])
+    w["q"] = (w["q"][0] * 4, w["q"][1])
+    w["o"] = (w["o"][0] * 16, w["o"][1])
+    return w
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_small_batch_steps(gpu, name):
+    import torch
+    B = gpu
+    batch, heads, dh, dt, n0 = CASES[name]
+    steps, p = 6, 4
+    shape = synth.DecodeShape(batch, heads * dh, heads, dh, (p,), n0=n0, steps=steps, dtype=dt)
+    print(f"[case {name}] {shape}", flush=True)
+    inp = synth.decode_inputs(shape, 900 + sorted(CASES).index(name))
+    w = weights_of(inp, dt)
+    cfg = B.decode_config(batch, shape.d_model, heads, dh, (p,), dtype=dt)
+    sess = B.DecodeSession(cfg, dev_weights(w, dt), dev(inp["k_cache"], dt), dev(inp["v_cache"], dt), n=n0)
+    st = oracle.DecodeState.empty(batch, heads, dh, p, shape.capacity, shape.d_model)
+    st.k_cache[:], st.v_cache[:], st.n = inp["k_cache"], inp["v_cache"], n0
+    for t in range(steps):
+        y = sess.step(dev(inp["x"][t], dt))
+        ref = oracle.decode_step(st, w, (p,), inp["x"][t])
+        torch.cuda.synchronize()
+        x = inp["x"][t].astype(np.float64)
+        # y, and the sublayer's share y - x against its own size (bf16 also rounds
+        # the x it is added to: half a unit of y)
+        err = oracle.max_rel_err(host(y), ref)
+        sub = np.abs((host(y) - x) - (ref - x)).max() / np.abs(ref - x).max()
+        slack = 2.0 ** -8 * np.abs(ref).max() / np.abs(ref - x).max() if dt == "bf16" else 0.0
+        print(f"  step {t}: y {err:.2e}, y - x {sub:.2e}", flush=True)
+        assert err <= TOL[dt] and sub <= TOL[dt] + slack
+    assert (sess.n, sess.j) == (st.n, st.j)
+    rows = slice(n0, st.n)
+    assert oracle.max_rel_err(host(sess.k_cache)[:, :, rows], st.k_cache[:, :, rows]) <= TOL[dt]
+
+
+@pytest.mark.parametrize("batch", [1, 4])
+def test_small_batch_ragged_equals_lockstep(gpu, batch):
+    """Equal per-sequence positions give the lockstep result bit for bit."""
+    import torch
+    B = gpu
+    shape = synth.DecodeShape(batch, 256, 4, 64, (4,), n0=140, steps=5)
+    inp = synth.decode_inputs(shape, 950)
+    cfg = B.decode_config(batch, 256, 4, 64, (4,))
+    out = []
+    for ragged in (False, True):
+        sess = B.DecodeSession(cfg, dev_weights(inp["weights"], "bf16"), dev(inp["k_cache"], "bf16"),
+                               dev(inp["v_cache"], "bf16"), n=140, ragged=ragged)
+        out.append(torch.stack([sess.step(dev(inp["x"][t], "bf16")) for t in range(5)]))
+    torch.cuda.synchronize()
+    assert torch.equal(*out)

@@ -135,23 +135,22 @@ int proxy_layer_forward(const pf_layer_config* cfg, const pf_layer_weights* w, c
   char* acts = saved ? reinterpret_cast<char*>(saved) : ws + W.acts;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   // partial last block: run on a zero-padded copy; 2-D partition: on a
-  // patch-ordered copy
-  const int64_t row_bytes = (int64_t)d.d_f * d.esize;
+  // patch-ordered copy (kept with the activations when they are saved). The
+  // gated and additive injections store X_out through the row map; the others
+  // leave it in workspace order and it is copied back.
   const void* xk = x;
   void* yk = x_out;
   hipError_t e = hipSuccess;
+  const bool copy_out = d.staged() && (d.fused_gate || (d.inject != PF_INJECT_GATED && d.inject != PF_INJECT_ADD));
   if (d.staged()) {
-    xk = ws + W.x_pad;
-    yk = ws + W.y_pad;
-    e = d.img_w ? permute_patches(x, ws + W.x_pad, d.B, d.L, d.img_w, d.patch, row_bytes, false, s)
-                : pad_rows(x, ws + W.x_pad, d.B, d.L_in, d.L, row_bytes, s);
-    if (e != hipSuccess) return hip_status(e, "proxy_layer_forward staging");
+    char* xs = saved ? acts + layer_acts(d, true).x_st : ws + W.x_pad;
+    if ((e = stage_rows(d, x, xs, s)) != hipSuccess) return hip_status(e, "proxy_layer_forward staging");
+    xk = xs;
+    if (copy_out) yk = ws + W.y_pad;
   }
   e = cfg->dtype == PF_BF16 ? layer_forward_run<bf16>(d, cfg, w, xk, h_in, yk, h_out, acts, saved != nullptr, ws, s)
                             : layer_forward_run<float>(d, cfg, w, xk, h_in, yk, h_out, acts, saved != nullptr, ws, s);
-  if (e == hipSuccess && d.staged())
-    e = d.img_w ? permute_patches(yk, x_out, d.B, d.L, d.img_w, d.patch, row_bytes, true, s)
-                : unpad_rows(yk, x_out, d.B, d.L_in, d.L, row_bytes, s);
+  if (e == hipSuccess && copy_out) e = unstage_rows(d, yk, x_out, s);
   return hip_status(e, "proxy_layer_forward launch");
 }
 
@@ -178,32 +177,12 @@ int proxy_layer_backward(const pf_layer_config* cfg, const pf_layer_weights* w, 
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const char* sv = reinterpret_cast<const char*>(saved);
   char* ws = reinterpret_cast<char*>(workspace);
-  // partial last block: the padding has dY = 0 and its dX is dropped;
-  // 2-D partition: X and dY gathered into patch order, dX scattered back
-  const int64_t row_bytes = (int64_t)d.d_f * d.esize;
-  const void* xk = x;
-  const void* dyk = dy;
-  void* dxk = dx;
-  hipError_t e = hipSuccess;
-  if (d.staged()) {
-    xk = ws + W.x_pad;
-    dyk = ws + W.dy_pad;
-    dxk = ws + W.y_pad;
-    if (d.img_w) {
-      e = permute_patches(x, ws + W.x_pad, d.B, d.L, d.img_w, d.patch, row_bytes, false, s);
-      if (e == hipSuccess) e = permute_patches(dy, ws + W.dy_pad, d.B, d.L, d.img_w, d.patch, row_bytes, false, s);
-    } else {
-      e = pad_rows(x, ws + W.x_pad, d.B, d.L_in, d.L, row_bytes, s);
-      if (e == hipSuccess) e = pad_rows(dy, ws + W.dy_pad, d.B, d.L_in, d.L, row_bytes, s);
-    }
-    if (e != hipSuccess) return hip_status(e, "proxy_layer_backward staging");
-  }
-  e = cfg->dtype == PF_BF16
-          ? layer_backward_run<bf16>(d, cfg, w, xk, h_in, sv, dyk, dh_out, dxk, dh_in, grads, ws, s)
-          : layer_backward_run<float>(d, cfg, w, xk, h_in, sv, dyk, dh_out, dxk, dh_in, grads, ws, s);
-  if (e == hipSuccess && d.staged())
-    e = d.img_w ? permute_patches(dxk, dx, d.B, d.L, d.img_w, d.patch, row_bytes, true, s)
-                : unpad_rows(dxk, dx, d.B, d.L_in, d.L, row_bytes, s);
+  // partial last block: the padding has dY = 0 and its dX is dropped; 2-D
+  // partition: patch order inside (see backward_impl)
+  const hipError_t e =
+      cfg->dtype == PF_BF16
+          ? layer_backward_run<bf16>(d, cfg, w, x, h_in, sv, dy, dh_out, dx, dh_in, grads, ws, s)
+          : layer_backward_run<float>(d, cfg, w, x, h_in, sv, dy, dh_out, dx, dh_in, grads, ws, s);
   return hip_status(e, "proxy_layer_backward launch");
 }
 

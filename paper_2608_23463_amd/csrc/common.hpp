@@ -13,6 +13,9 @@ namespace pf {
 // Epilogues whose GEMMs are also launched in groups (a kernel variant each).
 template <class Epi>
 struct GemmGrouped : std::false_type {};
+// Epilogues whose products have a multiple of 8 columns (no scalar form).
+template <class Epi>
+struct EpiWhole : std::false_type {};
 // Epilogues with arrays they index: kept in the kernel arguments.
 template <class Epi>
 struct EpiByRef : std::false_type {};
@@ -111,6 +114,25 @@ __device__ __forceinline__ uint32_t pack_bf8x4(float a, float b, float c, float 
   w = __builtin_amdgcn_cvt_pk_bf8_f32(sat(c), sat(d), w, true);
   return (uint32_t)w;
 }
+
+// Where a token of the padded or patch-ordered copy that the kernels work on
+// sits in the caller's tensor (Sec. 3.1 padding, Sec. 3.9 patches): the row
+// there, or -1 for a padding token. The epilogues that write a token tensor
+// store through this map, so no copy pass follows them (instances of their
+// own: the test alone cost the million-token layer 0.8 %).
+struct RowMap {
+  int mode = 0;        // 0: the same rows; 1: L tokens of which L_in are real; 2: p x p patches
+  int L = 0, L_in = 0;
+  int w = 0, p = 0, P = 0, pw = 0;  // image width, patch side, p * p, patches per row of them
+  __device__ __forceinline__ int64_t operator()(int r) const {
+    if (mode == 0) return r;
+    const int b = r / L, t = r - b * L;
+    if (mode == 1) return t < L_in ? (int64_t)b * L_in + t : -1;
+    const int blk = t / P, u = t - blk * P;
+    const int by = blk / pw, bx = blk - by * pw, uy = u / p, ux = u - uy * p;
+    return (int64_t)b * L + (int64_t)(by * p + uy) * w + bx * p + ux;
+  }
+};
 
 // Eight consecutive elements <-> fp32 (16-byte aligned for bf16, two
 // 16-byte accesses for fp32).

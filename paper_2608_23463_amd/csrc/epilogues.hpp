@@ -8,7 +8,7 @@ namespace pf {
 
 // out[r, c] = acc + bias[c] (+ add[r, c]); optional second copy out2.
 // out_lo (bf16 only, optional): low part of the two-term split of the result.
-template <typename T>
+template <typename T, bool MAP = false>
 struct EpiLinear {
   T* out;
   int64_t ldo;
@@ -17,10 +17,20 @@ struct EpiLinear {
   int64_t ld_add;
   T* out2;
   T* out_lo;
+  // with a map, `out` holds tokens: row r of the product is k of them, d wide
+  // (only `out` then)
+  RowMap map{};
+  int k = 1, d = 0;
   __device__ __forceinline__ void operator()(int r, int c, float v) const {
     if (bias) v += to_f32(bias[c]);
     if (add) v += to_f32(add[(int64_t)r * ld_add + c]);
     const T o = from_f32<T>(v);
+    if constexpr (MAP) {
+      const int t = c / d;
+      const int64_t row = map(r * k + t);
+      if (row >= 0) out[row * d + c - t * d] = o;
+      return;
+    }
     out[(int64_t)r * ldo + c] = o;
     if (out2) out2[(int64_t)r * ldo + c] = o;
     if (out_lo) out_lo[(int64_t)r * ldo + c] = from_f32<T>(split_lo(v));
@@ -71,6 +81,12 @@ struct EpiLinear {
   }
   __device__ __forceinline__ void finish(int r, int c, const float* v) const {
     float t[8];
+    if constexpr (MAP) {
+      const int q = c / d;
+      const int64_t row = map(r * k + q);
+      if (row >= 0) store8(out + row * d + c - q * d, v);
+      return;
+    }
     store8(out + (int64_t)r * ldo + c, v);
     if (out2) store8(out2 + (int64_t)r * ldo + c, v);
     if (out_lo) {
@@ -105,26 +121,21 @@ struct EpiHeads {
   // 256 (Ql Kh + Qh Kl).
   uint8_t* outx = nullptr;
   int xmode = 0;
-  __device__ __forceinline__ void operator()(int r, int c, float v) const {
-    if (bias) v += to_f32(bias[c]);
-    const T o = from_f32<T>(v);
-    const int b = r / m, i = r - b * m;
+  // The transposed store takes 16 bytes along the rows of a column where a run
+  // of eight rows lies inside one sequence and starts 16-byte aligned: one
+  // sequence, or m a multiple of 8. Otherwise 2-byte stores
+  // (Q, K and V of 16,384 proxies at d = 512: 88 us so, 80 with the runs).
+  __device__ __forceinline__ bool cols() const { return out_t && sizeof(T) == 2 && (single || m % 8 == 0); }
+  int single = 0;  // one sequence (rows == m)
+  __device__ __forceinline__ void col8(int r0, int c, const float* v, int rows) const {
+    const float bc = bias ? to_f32(bias[c]) : 0.0f;
+    const int b = single ? 0 : r0 / m, i = r0 - b * m;
     const int hd = c / dh, e = c - hd * dh;
-    const int64_t bh = (int64_t)b * n_heads + hd;
-    if (out) out[(bh * m + i) * dh + e] = o;
-    if (out_t) {
-      out_t[(bh * dh + e) * ld_t + i] = o;
-      for (int p = 2 * m - 1 - i; p < ld_t; p += m) out_t[(bh * dh + e) * ld_t + p] = (T)0.0f;
-    }
-    if (out_lo) out_lo[(bh * m + i) * dh + e] = from_f32<T>(split_lo(v));
-    if (outs) outs[(bh * m + i) * dh + e] = from_f32<T>(v * scale);
-    if (outx) {
-      const float x = xmode == 1 ? v * scale : v;
-      const float hi = (float)(bf16)x, lo = (x - hi) * 256.0f;
-      uint8_t* row = outx + (bh * m + i) * 2 * dh;
-      row[e] = (uint8_t)pack_bf8x4(xmode == 1 ? lo : hi, 0.0f, 0.0f, 0.0f);
-      row[dh + e] = (uint8_t)pack_bf8x4(xmode == 1 ? hi : lo, 0.0f, 0.0f, 0.0f);
-    }
+    T* dst = out_t + (((int64_t)b * n_heads + hd) * dh + e) * ld_t + i;
+    float t[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) t[k] = r0 + k < rows ? v[k] + bc : 0.0f;  // past the last row: a zero padding column
+    store8(dst, t);  // i + 8 <= ld_t: both are multiples of 8
   }
   struct Col {
     Raw8<T> b;
@@ -134,22 +145,23 @@ struct EpiHeads {
     if (bias) raw_load8(bias + c, k.b);
   }
   __device__ __forceinline__ void pre(int, int, Pre&) const {}
-  __device__ __forceinline__ void vec8(int r, int c, const float* v0, const Col& k, const Pre&) const {
+  __device__ __forceinline__ void vec8(int r, int c, const float* v0, const Col& k, const Pre&,
+                                       bool rowwise = true) const {
     float v[8], t[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     if (bias) raw_to_f32(k.b, t);
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = v0[e] + t[e];
-    finish(r, c, v);
+    finish(r, c, v, rowwise);
   }
   __device__ __forceinline__ void vec8(int r, int c, const float* v0) const {
     float v[8], t[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     if (bias) load8(bias + c, t);
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = v0[e] + t[e];
-    finish(r, c, v);
+    finish(r, c, v, true);
   }
   // 8 consecutive channels stay inside one head (dh is a multiple of 8)
-  __device__ __forceinline__ void finish(int r, int c, const float* v) const {
+  __device__ __forceinline__ void finish(int r, int c, const float* v, bool rowwise) const {
     const int b = r / m, i = r - b * m;
     const int hd = c / dh, e0 = c - hd * dh;
     const int64_t bh = (int64_t)b * n_heads + hd;
@@ -167,10 +179,12 @@ struct EpiHeads {
       store8(outs + (bh * m + i) * dh + e0, s);
     }
     if (out_t) {
+      if (rowwise)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) out_t[(bh * dh + e0 + e) * ld_t + i] = from_f32<T>(v[e]);
+        for (int e = 0; e < 8; ++e) out_t[(bh * dh + e0 + e) * ld_t + i] = from_f32<T>(v[e]);
+#pragma unroll 1
       for (int p = 2 * m - 1 - i; p < ld_t; p += m)
-#pragma unroll
+#pragma unroll 1
         for (int e = 0; e < 8; ++e) out_t[(bh * dh + e0 + e) * ld_t + p] = (T)0.0f;
     }
     if (outx) {
@@ -195,6 +209,8 @@ struct EpiHeads {
 
 template <typename T>
 struct GemmGrouped<EpiHeads<T>> : std::true_type {};
+template <typename T>
+struct EpiWhole<EpiHeads<T>> : std::true_type {};  // n_heads * head_dim columns
 
 // Output map of the interaction with the token-causal shift folded in: row
 // r = b*m + i of H-bar goes to row r + 1 of S (the proxy block i + 1 receives);
@@ -247,7 +263,7 @@ struct EpiShift {
 };
 
 // Gated injection (Eq. 12): G = acc + b_g; Y = X + sigmoid(G) * Delta.
-template <typename T>
+template <typename T, bool MAP = false>
 struct EpiGate {
   const T* x;
   const T* delta;
@@ -255,12 +271,14 @@ struct EpiGate {
   T* y;
   T* gsave;
   int64_t ld;
+  RowMap map{};  // of y
   __device__ __forceinline__ void operator()(int r, int c, float v) const {
     if (bias) v += to_f32(bias[c]);
     const int64_t i = (int64_t)r * ld + c;
     const float xv = to_f32(x[i]);
     const float dv = to_f32(delta[i]);
-    y[i] = from_f32<T>(xv + sigmoidf(v) * dv);
+    const int64_t row = MAP ? map(r) : (int64_t)r;
+    if (!MAP || row >= 0) y[row * ld + c] = from_f32<T>(xv + sigmoidf(v) * dv);
     if (gsave) gsave[i] = from_f32<T>(v);
   }
   // Two-phase form: col() reads the bias, pre() the 8 values of X and Delta.
@@ -302,7 +320,8 @@ struct EpiGate {
       g[e] = v0[e] + bv[e];
       yv[e] = xv[e] + sigmoidf(g[e]) * dv[e];
     }
-    store8(y + i, yv);
+    const int64_t row = MAP ? map(r) : (int64_t)r;
+    if (!MAP || row >= 0) store8(y + row * ld + c, yv);
     if (gsave) store8(gsave + i, g);
   }
 };

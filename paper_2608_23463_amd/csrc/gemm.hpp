@@ -417,12 +417,23 @@ __device__ __forceinline__ void gemm_store(f32x16 (&acc)[S::kFM][S::kFN], float*
         if (full[u]) {
           epi_vec8(epi, row, col, v, colv, pre[u]);
         } else {
-          for (int e = 0; col + e < p.N; ++e) epi(row, col + e, v[e]);
+          if constexpr (!EpiWhole<Epi>::value)
+            for (int e = 0; col + e < p.N; ++e) epi(row, col + e, v[e]);
         }
       }
     }
   }
 }
+
+// An epilogue that also stores its result transposed may define
+//   cols() const          whether it takes runs of rows (uniform), and
+//   col8(r0, c, v)        the eight results of rows r0 .. r0+7 at column c,
+// and then gets those from the wave's LDS region, where a run of rows is as
+// near as a run of columns; vec8(..., false) leaves the transposed store out.
+template <class Epi, class = void>
+struct EpiTakesCols : std::false_type {};
+template <class Epi>
+struct EpiTakesCols<Epi, std::void_t<decltype(std::declval<const Epi&>().cols())>> : std::true_type {};
 
 // Wave-local epilogue of the direct kernel: each wave writes its own
 // kTM x kTN tile, kRows rows per step, through a private LDS region, with
@@ -475,6 +486,21 @@ __device__ __forceinline__ void gemm_store_wave(f32x16 (&acc)[S::kFM][S::kFN], f
     asm volatile("" ::: "memory");
     wait_lgkmcnt0();
     asm volatile("" ::: "memory");
+    bool rowwise = true;  // the row stores include the transposed copy
+    if constexpr (EpiTakesCols<Epi>::value) {
+      if (epi.cols()) {
+        rowwise = false;
+#pragma unroll 1
+        for (int it = 0; it < kTN * kRows / 8; it += kWave) {
+          const int cc = (it + lane) % kTN, rh = (it + lane) / kTN * 8;
+          const int r0 = step_row(step) + rh, c = col0 + cc;
+          float t[8];
+#pragma unroll
+          for (int k = 0; k < 8; ++k) t[k] = region[(rh + k) * kSRow + cc];
+          if (r0 < p.M && c < p.N) epi.col8(r0, c, t, p.M);
+        }
+      }
+    }
     float v[kPer][8];
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
@@ -495,9 +521,13 @@ __device__ __forceinline__ void gemm_store_wave(f32x16 (&acc)[S::kFM][S::kFN], f
       const int row = step_row(step) + rl0 + u * kRowsPerPass;
       if (row >= p.M || col >= p.N) continue;
       if (col + 8 <= p.N) {
-        epi_vec8(epi, row, col, v[u], colv, pre[step % (kAhead + 1)][u]);
+        if constexpr (EpiTakesCols<Epi>::value)
+          epi.vec8(row, col, v[u], colv, pre[step % (kAhead + 1)][u], rowwise);
+        else
+          epi_vec8(epi, row, col, v[u], colv, pre[step % (kAhead + 1)][u]);
       } else {
-        for (int e = 0; col + e < p.N; ++e) epi(row, col + e, v[u][e]);
+        if constexpr (!EpiWhole<Epi>::value)
+          for (int e = 0; col + e < p.N; ++e) epi(row, col + e, v[u][e]);
       }
     }
   }
@@ -1082,12 +1112,14 @@ __global__ void __launch_bounds__(256) splitk_reduce_kernel(const ReduceArgs<Epi
     }
     return;
   }
-  const int64_t stride = (int64_t)args.blocks * blockDim.x;
-  for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total; idx += stride) {
-    float s = 0.0f;
+  if constexpr (!EpiWhole<Epi>::value) {
+    const int64_t stride = (int64_t)args.blocks * blockDim.x;
+    for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total; idx += stride) {
+      float s = 0.0f;
 #pragma unroll 8
-    for (int z = 0; z < splits; ++z) s += ws[(int64_t)z * total + idx];
-    epi((int)(idx / N), (int)(idx % N), s);
+      for (int z = 0; z < splits; ++z) s += ws[(int64_t)z * total + idx];
+      epi((int)(idx / N), (int)(idx % N), s);
+    }
   }
 }
 
@@ -1155,19 +1187,31 @@ inline GemmPlan plan_gemm(const GemmProblem* prs, int count, int num_cu, bool le
   // operand loads, and four times the workgroups with four stages in flight
   // instead of two wait a quarter as long.
   const int64_t kb = (max_k + pl.bk - 1) / pl.bk;
-  const bool small = lean ? sizeof(T) == 2 && max_mn <= 64 : t128 * std::max<int64_t>(1, kb / 8) < num_cu;
+  const bool small = lean ? sizeof(T) == 2 && max_mn <= 64
+                          : t128 * std::max<int64_t>(1, kb / 8) < num_cu || (min_n <= 64 && max_k <= 2 * pl.bk);
   const int max_dim_tile = small ? TILE_64x64 : TILE_128x128;
+  // Without a split, 256x256 tiles (one per CU) against 128x128 (two per CU)
+  // by the share of the chip's rounds that the result fills; a 256x256 tile
+  // moves fewer operand bytes, worth about a seventh. 316 tiles of 256x256
+  // (20,224 x 1,024, K = 512) take two rounds for 1.23: 53 us against 44 in
+  // 128x128; 256 of them over a result of [316, 32768] 26 against 33.
+  auto fill = [&](int64_t t, int64_t slots, int64_t edge) {
+    return (double)mn / (double)((t + slots - 1) / slots * slots * edge * edge);
+  };
+  const bool wide_fills = lean ? mn >= (int64_t)256 * 256 * num_cu
+                               : t256 * 10 >= num_cu * 9 && fill(t256, num_cu, 256) * 1.15 >= fill(t128, 2 * num_cu, 128);
   if (sizeof(T) == 4) {
     pl.tile = max_dim_tile;
   } else if (min_m >= 256 && min_n >= 256 &&
-             (mn >= (int64_t)256 * 256 * num_cu ||
+             (wide_fills ||
               // long reductions: 256x256 tiles split along K still fill the chip
-              (int64_t)max_k * t256 >= (int64_t)num_cu * 64 * 64)) {
+              (t256 < num_cu && (int64_t)max_k * t256 >= (int64_t)num_cu * 64 * 64))) {
     pl.tile = TILE_256x256;
   } else {
     pl.tile = max_dim_tile;
   }
   pl.bm = pl.bn = pl.tile == TILE_256x256 ? 256 : pl.tile == TILE_128x128 ? 128 : 64;
+  const bool one_pass = pl.tile == TILE_256x256 && wide_fills && !lean;
   int64_t tiles = 0;
   int batch = 1;
   for (int i = 0; i < count; ++i) {
@@ -1181,11 +1225,15 @@ inline GemmPlan plan_gemm(const GemmProblem* prs, int count, int num_cu, bool le
   // up to one workgroup per CU, sixteen up to the two 128x128 ones that fit a
   // CU (beyond that the partials cost more than the second workgroup hides).
   auto more = [&](int s) {
-    if (batch != 1) return false;
+    if (batch != 1 || one_pass) return false;
     if (tiles * s < num_cu) return kblocks / (s * 2) >= 8;
     return !lean && pl.tile == TILE_128x128 && tiles * s < 2 * num_cu && kblocks / (s * 2) >= 16;
   };
   while (more(splits)) splits *= 2;
+  // a split pays its partials and the reduction's launch (5 us and more), so
+  // it has to take enough steps off the longest chain: ten of a 64x64 tile's
+  // (0.35 us each, and up to 1 us with an M/N-major operand)
+  if (!lean && pl.tile == TILE_64x64 && kblocks - kblocks / splits < 10) splits = 1;
   const int kb_per = (kblocks + splits - 1) / splits;
   pl.k_slice = kb_per * pl.bk;
   pl.splits = (kblocks + kb_per - 1) / kb_per;
@@ -1271,11 +1319,11 @@ inline hipError_t launch_gemm_tile(const GemmProblem* prs, int count, const Gemm
   // wave's MFMAs cover the other's load issue and barrier waits.
   constexpr int DWN = (BM == 256 && BN == 256) ? 4 : WN;
   constexpr bool kCanDirect = (LA == LAYOUT_K && LB == LAYOUT_K) || sizeof(T) == 2;
-  constexpr int NS = BM * BN * (int)sizeof(T) <= 64 * 64 * 4 ? 4 : 2;  // stages of the operand ring
   if constexpr (kCanDirect) {
     if (direct) {
-      auto go = [&](auto group) {
+      auto go = [&](auto group, auto stages) {
         constexpr int G = decltype(group)::value;
+        constexpr int NS = decltype(stages)::value;
         GemmArgs<Epi, G> args;
         for (int i = 0; i < count; ++i) {
           args.p[i] = gemm_params(prs[i], BM, BN, BK, plan_k_slice(prs[i], pl), sizeof(T));
@@ -1293,8 +1341,21 @@ inline hipError_t launch_gemm_tile(const GemmProblem* prs, int count, const Gemm
                            stream, args);
         return hipGetLastError();
       };
-      if (count == 1) return go(std::integral_constant<int, 1>{});
-      if constexpr (kGemmGrouped<Epi>) return go(std::integral_constant<int, kGemmGroup>{});
+      // Stages of the operand ring: two, and four (64 KB) on 64x64 tiles, which
+      // wait on their loads, unless no slice has more K steps than two or the
+      // launch has more workgroups than fit at two per CU: then five with two
+      // stages fit a CU and cover each other's loads (token-long gate of a
+      // 64-wide stream, K = 128: 136 us in 128x128 tiles, 127 with four
+      // stages, 131 with two).
+      typedef std::integral_constant<int, 2> two;
+      typedef std::integral_constant<int, BM == 64 ? 4 : 2> many;
+      bool brief = true;
+      for (int i = 0; i < count; ++i) brief = brief && plan_k_slice(prs[i], pl) <= 2 * BK;
+      brief = brief || (int64_t)tiles * count * splits * prs[0].batch > 512;
+      typedef std::integral_constant<int, 1> single;
+      typedef std::integral_constant<int, kGemmGroup> grouped;
+      if (count == 1) return brief ? go(single{}, two{}) : go(single{}, many{});
+      if constexpr (kGemmGrouped<Epi>) return brief ? go(grouped{}, two{}) : go(grouped{}, many{});
     }
   }
   if (count > 1) {

@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 
 #include "../../include/proxyformer.h"
+#include "common.hpp"
 
 namespace pf {
 
@@ -32,7 +33,8 @@ struct LayerDims {
   bool split;       // bf16 low parts on the proxy path (PF_PRECISION_EXTENDED in bf16 mode)
   bool fused_gate;  // level-1 decompression and the gate run as one kernel (bf16, gated injection)
   // the caller's token tensors go through workspace copies (padded or patch-ordered)
-  bool staged() const { return L_in != L || img_w > 0; }
+  bool staged() const { return map.mode != 0; }
+  RowMap map;       // token rows of those copies -> the caller's
 };
 
 // Byte offsets of every activation inside the region that holds them
@@ -66,6 +68,7 @@ struct LayerActs {
   size_t rstd;                // Eq. 13: 1 / RMS of every X row, fp32 [B*L]
   size_t gh;                  // per-head gate pre-activation, fp32 [B*L, n_heads]
   size_t aff_w, aff_b;        // Eq. 13: W_a, b_a with s and t rows interleaved [2 d_f, d_f], [2 d_f]
+  size_t x_st;                // staged calls: X as the kernels read it, kept for the backward [B*L, d_f]
   size_t bytes;
 };
 
@@ -90,8 +93,8 @@ struct LayerWs {
   size_t tr_w;                // a transposed weight [in, out] for the large data gradients
   // staged token tensors (L_in < L: zero-padded to L tokens; 2-D partition:
   // in patch order)
-  size_t x_pad;               // X with zero padding [B*L, d_f]
-  size_t y_pad;               // forward: X_out; backward: dX [B*L, d_f]
+  size_t x_pad;               // forward without saved activations: X with zero padding [B*L, d_f]
+  size_t y_pad;               // forward: X_out, for the injections without a mapped store [B*L, d_f]
   size_t dy_pad;              // backward: dY with zero padding [B*L, d_f]
   size_t dst;                 // Eq. 13 backward: [dS | dT] [B*L, 2 d_f]
   size_t dgh;                 // per-head gate backward: dG [B*L, round8(n_heads)]
@@ -124,6 +127,11 @@ hipError_t unpad_rows(const void* src, void* dst, int B, int64_t L_in, int64_t L
 // dst[b, j] = src[b, perm(j)]; scatter: dst[b, perm(j)] = src[b, j].
 hipError_t permute_patches(const void* src, void* dst, int B, int64_t L, int w, int p, int64_t row_bytes,
                            bool scatter, hipStream_t stream);
+
+// The caller's token tensor as the kernels read it (zero-padded or in patch
+// order), and back.
+hipError_t stage_rows(const LayerDims& d, const void* src, void* dst, hipStream_t stream);
+hipError_t unstage_rows(const LayerDims& d, const void* src, void* dst, hipStream_t stream);
 
 // Validates cfg; on failure returns a status and writes a message.
 int layer_dims(const pf_layer_config* cfg, LayerDims* d, const char** why);

@@ -33,13 +33,25 @@
 namespace pf {
 
 // dG = dY * Delta * s * (1 - s), s = sigmoid(G); 8 elements per thread.
-template <typename T>
+// With a map, dY is the caller's tensor: it is read through the map (padding
+// tokens are zeros) and its copy for the GEMMs is left in dy_out.
+template <typename T, bool MAP>
 __global__ void __launch_bounds__(256) gate_bwd_prep_kernel(const T* __restrict__ dy, const T* __restrict__ delta,
-                                                            const T* __restrict__ g, T* __restrict__ dg, int64_t n8) {
+                                                            const T* __restrict__ g, T* __restrict__ dg, int64_t n8,
+                                                            const RowMap map, int d8, T* __restrict__ dy_out) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < n8; c += stride) {
     float a[8], b[8], z[8], o[8];
-    load8(dy + c * 8, a);
+    if constexpr (MAP) {
+      const int r = (int)(c / d8);
+      const int64_t row = map(r);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) a[e] = 0.0f;
+      if (row >= 0) load8(dy + (row * d8 + c - (int64_t)r * d8) * 8, a);
+      store8(dy_out + c * 8, a);
+    } else {
+      load8(dy + c * 8, a);
+    }
     load8(delta + c * 8, b);
     load8(g + c * 8, z);
 #pragma unroll
@@ -337,7 +349,7 @@ struct EpiUnshift {
 // fp32 accumulation across several GEMMs into `acc`; the first may start from
 // `add` (dtype T) instead of the accumulator, the last writes the rounded sum
 // to `out` (and `out2`) instead of the accumulator.
-template <typename T>
+template <typename T, bool MAP = false>
 struct EpiAccum {
   float* acc;
   int64_t ld;
@@ -345,10 +357,17 @@ struct EpiAccum {
   int first;
   T* out;
   T* out2;
+  // with a map, `out` holds tokens: row r of the product is k of them, d wide
+  RowMap map{};
+  int k = 1, d = 0;
   __device__ __forceinline__ void operator()(int r, int c, float v) const {
     const int64_t i = (int64_t)r * ld + c;
     const float t = v + (first ? (add ? to_f32(add[i]) : 0.0f) : acc[i]);
-    if (out) {
+    if (MAP && out) {
+      const int q = c / d;
+      const int64_t row = map(r * k + q);
+      if (row >= 0) out[row * d + c - q * d] = from_f32<T>(t);
+    } else if (out) {
       out[i] = from_f32<T>(t);
       if (out2) out2[i] = from_f32<T>(t);
     } else {
@@ -381,7 +400,11 @@ struct EpiAccum {
   }
   __device__ __forceinline__ void finish(int r, int c, const float* t) const {
     const int64_t i = (int64_t)r * ld + c;
-    if (out) {
+    if (MAP && out) {
+      const int q = c / d;
+      const int64_t row = map(r * k + q);
+      if (row >= 0) store8(out + row * d + c - q * d, t);
+    } else if (out) {
       store8(out + i, t);
       if (out2) store8(out2 + i, t);
     } else {
@@ -403,12 +426,7 @@ struct EpiAccum {
     }
 #pragma unroll
     for (int e = 0; e < 8; ++e) t[e] = v[e] + b[e];
-    if (out) {
-      store8(out + i, t);
-      if (out2) store8(out2 + i, t);
-    } else {
-      store8(acc + i, t);
-    }
+    finish(r, c, t);
   }
 };
 
@@ -582,8 +600,8 @@ static void dgrad(Runner& run, const char* label, const T* g, int64_t ldg, const
 
 template <typename T>
 static void backward_impl(Runner& run, const LayerDims& d, const pf_layer_config* cfg, const pf_layer_weights* w,
-                          const void* x, const char* saved, const void* dy, const void* dh_out, void* dx, void* dh_in,
-                          const pf_layer_grads* gr, char* ws) {
+                          const void* x, const char* saved, const void* dy_in, const void* dh_out, void* dx,
+                          void* dh_in, const pf_layer_grads* gr, char* ws) {
   const LayerActs A = layer_acts(d, true);
   const LayerWs W = layer_ws_layout(d, true);
   auto S = [&](size_t off) { return reinterpret_cast<const T*>(saved + off); };
@@ -604,8 +622,13 @@ static void backward_impl(Runner& run, const LayerDims& d, const pf_layer_config
   const int64_t BL = (int64_t)d.B * d.L;
   const int64_t Bm = (int64_t)d.B * d.m;
   const int df = d.d_f, dp = d.d_p;
-  const T* dyp = reinterpret_cast<const T*>(dy);
-  const T* xp = reinterpret_cast<const T*>(x);
+  // staged calls: X is the copy that the forward saved, dY gets one in
+  // workspace (for the gated injection the first kernel writes it), and dX
+  // is stored through the map
+  const T* dyp = d.map.mode ? WT(W.dy_pad) : reinterpret_cast<const T*>(dy_in);
+  const T* xp = d.map.mode ? S(A.x_st) : reinterpret_cast<const T*>(x);
+  if (d.map.mode && cfg->injection != PF_INJECT_GATED)
+    run.launch("stage_dy", [&] { return stage_rows(d, dy_in, WT(W.dy_pad), run.stream); });
 
   // 1. injection: gated (Eq. 12), affine (Eq. 13) or residual add (Eq. 11:
   //    dDelta = dX = dY)
@@ -641,8 +664,13 @@ static void backward_impl(Runner& run, const LayerDims& d, const pf_layer_config
     run.launch("gate_bwd_prep", [&] {
       const int64_t n8 = BL * df / 8;
       const int blocks = (int)std::min<int64_t>((n8 + 255) / 256, 16384);
-      hipLaunchKernelGGL((gate_bwd_prep_kernel<T>), dim3(blocks), dim3(256), 0, run.stream, dyp, S(A.delta), S(A.g),
-                         WT(W.dg), n8);
+      if (d.map.mode)  // the copy of dY is made here
+        hipLaunchKernelGGL((gate_bwd_prep_kernel<T, true>), dim3(blocks), dim3(256), 0, run.stream,
+                           reinterpret_cast<const T*>(dy_in), S(A.delta), S(A.g), WT(W.dg), n8, d.map, df / 8,
+                           WT(W.dy_pad));
+      else
+        hipLaunchKernelGGL((gate_bwd_prep_kernel<T, false>), dim3(blocks), dim3(256), 0, run.stream, dyp, S(A.delta),
+                           S(A.g), WT(W.dg), n8, d.map, df / 8, (T*)nullptr);
       return hipGetLastError();
     });
     dgrad<T>(run, "gate_dgrad_gemm", WT(W.dg), df, w->gate.w, 2 * df, BL, 2 * df, df,
@@ -674,8 +702,10 @@ static void backward_impl(Runner& run, const LayerDims& d, const pf_layer_config
   }
 
   // 3. output map of the interaction
+  EpiHeads<T> dO_epi{WT(W.dO), WT(W.dOt), nullptr, (int)d.m, d.dh, d.nh, d.ld_t};
+  dO_epi.single = d.B == 1;
   dgrad<T>(run, "o_dgrad_gemm", WT(W.dhbar), dp, w->o.w, dp, Bm, dp, dp,
-           EpiHeads<T>{WT(W.dO), WT(W.dOt), nullptr, (int)d.m, d.dh, d.nh, d.ld_t}, trw);
+           dO_epi, trw);
   // 4. attention (Eq. 9)
   AttnBwdParams ap{};
   ap.q = S(A.q);
@@ -754,9 +784,21 @@ static void backward_impl(Runner& run, const LayerDims& d, const pf_layer_config
     wgrads("compress_wgrad_gemm", &item, 1, rows);
     if (j == 0) {
       // dX = (dY + dG W_gx, in dx32) or dY, plus this level's data gradient
-      EpiAccum<T> e = add_inject ? EpiAccum<T>{WF(W.dx32), kd, dyp, 1, reinterpret_cast<T*>(dx), nullptr}
-                                 : EpiAccum<T>{WF(W.dx32), kd, nullptr, 0, reinterpret_cast<T*>(dx), nullptr};
-      dgrad<T>(run, "compress_dgrad_gemm", dz, dn, w->compress[j].w, kd, rows, kd, dn, e, trw);
+      auto last = [&](auto e) {
+        e.acc = WF(W.dx32);
+        e.ld = kd;
+        e.add = add_inject ? dyp : nullptr;
+        e.first = add_inject;
+        e.out = reinterpret_cast<T*>(dx);
+        e.map = d.map;
+        e.k = d.k[0];
+        e.d = df;
+        dgrad<T>(run, "compress_dgrad_gemm", dz, dn, w->compress[j].w, kd, rows, kd, dn, e, trw);
+      };
+      if (d.map.mode)
+        last(EpiAccum<T, true>{});
+      else
+        last(EpiAccum<T>{});
     } else {
       dgrad<T>(run, "compress_dgrad_gemm", dz, dn, w->compress[j].w, kd, rows, kd, dn,
                EpiLinear<T>{WT(W.dz[j]), kd, nullptr, nullptr, 0, nullptr}, trw);

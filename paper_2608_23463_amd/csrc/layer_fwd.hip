@@ -87,6 +87,18 @@ hipError_t permute_patches(const void* src, void* dst, int B, int64_t L, int w, 
   return hipGetLastError();
 }
 
+hipError_t stage_rows(const LayerDims& d, const void* src, void* dst, hipStream_t stream) {
+  const int64_t row_bytes = (int64_t)d.d_f * d.esize;
+  return d.img_w ? permute_patches(src, dst, d.B, d.L, d.img_w, d.patch, row_bytes, false, stream)
+                 : pad_rows(src, dst, d.B, d.L_in, d.L, row_bytes, stream);
+}
+
+hipError_t unstage_rows(const LayerDims& d, const void* src, void* dst, hipStream_t stream) {
+  const int64_t row_bytes = (int64_t)d.d_f * d.esize;
+  return d.img_w ? permute_patches(src, dst, d.B, d.L, d.img_w, d.patch, row_bytes, true, stream)
+                 : unpad_rows(src, dst, d.B, d.L_in, d.L, row_bytes, stream);
+}
+
 // Eq. 13: rstd[r] = 1 / sqrt(mean(x[r]^2) + eps), one wave per row (fp32
 // sum of squares: per-lane runs of 8, then a butterfly over the wave).
 template <typename T>
@@ -202,6 +214,11 @@ int layer_dims(const pf_layer_config* c, LayerDims* d, const char** why) {
     d->img_w = c->image_width;
     d->patch = p;
   }
+  d->map = RowMap{};
+  if (d->img_w)
+    d->map = RowMap{2, (int)d->L, (int)d->L_in, d->img_w, d->patch, (int)d->P, d->img_w / d->patch};
+  else if (d->L != d->L_in)
+    d->map = RowMap{1, (int)d->L, (int)d->L_in, 0, 0, 0, 0};
   d->d[0] = d->d_f;
   for (int j = 1; j < d->M; ++j) d->d[j] = c->level_dims[j - 1] > 0 ? c->level_dims[j - 1] : d->d_p;
   d->d[d->M] = d->d_p;
@@ -289,6 +306,7 @@ LayerActs layer_acts(const LayerDims& d, bool bwd) {
   a.gh = take(d.inject == PF_INJECT_GATED_HEAD ? (size_t)d.B * d.L * d.nh * 4 : 0);
   a.aff_w = take(affine ? (size_t)2 * d.d_f * d.d_f * es : 0);
   a.aff_b = take(affine ? (size_t)2 * d.d_f * es : 0);
+  a.x_st = take(bwd && d.staged() ? (size_t)d.B * d.L * d.d_f * es : 0);
   a.bytes = off;
   return a;
 }
@@ -366,8 +384,8 @@ LayerWs layer_ws_layout(const LayerDims& d, bool bwd) {
   if (bwd && d.inject == PF_INJECT_AFFINE) w.dst = take(2 * tok);
   if (bwd && d.inject == PF_INJECT_GATED_HEAD) w.dgh = take((size_t)d.B * d.L * round8(d.nh) * es);
   if (d.staged()) {
-    w.x_pad = take(tok);
-    w.y_pad = take(tok);
+    w.x_pad = bwd ? 0 : take(tok);
+    w.y_pad = bwd ? 0 : take(tok);
     w.dy_pad = bwd ? take(tok) : 0;
   }
   w.gemm = off;
@@ -467,6 +485,7 @@ static void forward_impl(Runner& run, const LayerDims& d, const pf_layer_config*
     }
     EpiHeads<T> e{outs[i], outs_t[i], reinterpret_cast<const T*>(proj[i]->b), (int)d.m, d.dh, d.nh, d.ld_t,
                   outs_lo[i]};
+    e.single = d.B == 1;
     if (i == 0) {
       e.outs = P(A.qs);
       e.scale = qscale;
@@ -530,8 +549,20 @@ static void forward_impl(Runner& run, const LayerDims& d, const pf_layer_config*
     pr.K = d.d[j + 1];
     const T* bias = reinterpret_cast<const T*>(w->decompress[j].b);
     if (j == 0 && add_inject) {
-      EpiLinear<T> e{reinterpret_cast<T*>(x_out), pr.N, bias, reinterpret_cast<const T*>(x), pr.N, nullptr};
-      run.gemm<T, LAYOUT_K, LAYOUT_K>("decompress_gemm", pr, e);
+      auto go = [&](auto e) {
+        e.out = reinterpret_cast<T*>(x_out);
+        e.ldo = e.ld_add = pr.N;
+        e.bias = bias;
+        e.add = reinterpret_cast<const T*>(x);
+        e.map = d.map;
+        e.k = d.k[0];
+        e.d = d.d_f;
+        run.gemm<T, LAYOUT_K, LAYOUT_K>("decompress_gemm", pr, e);
+      };
+      if (d.map.mode)
+        go(EpiLinear<T, true>{});
+      else
+        go(EpiLinear<T>{});
       continue;
     }
     T* out = j == 0 ? P(A.delta) : P(A.u[j]);
@@ -677,9 +708,20 @@ static void forward_impl(Runner& run, const LayerDims& d, const pf_layer_config*
     pr.M = (int)(d.B * d.L);
     pr.N = d.d_f;
     pr.K = 2 * d.d_f;
-    EpiGate<T> e{reinterpret_cast<const T*>(x), P(A.delta), reinterpret_cast<const T*>(w->gate.b),
-                 reinterpret_cast<T*>(x_out), saving ? P(A.g) : nullptr, d.d_f};
-    run.gemm<T, LAYOUT_K, LAYOUT_K>("gate_gemm", pr, e);
+    auto go = [&](auto e) {
+      e.x = reinterpret_cast<const T*>(x);
+      e.delta = P(A.delta);
+      e.bias = reinterpret_cast<const T*>(w->gate.b);
+      e.y = reinterpret_cast<T*>(x_out);
+      e.gsave = saving ? P(A.g) : nullptr;
+      e.ld = d.d_f;
+      e.map = d.map;
+      run.gemm<T, LAYOUT_K, LAYOUT_K>("gate_gemm", pr, e);
+    };
+    if (d.map.mode)
+      go(EpiGate<T, true>{});
+    else
+      go(EpiGate<T>{});
   }
 }
 

@@ -1,4 +1,4 @@
-"""Grouped GEMM launches, bias gradients formed inside the weight-gradient
+"""GEMM launches and their epilogues: grouped launches, bias gradients formed inside the weight-gradient
 GEMM, and the split-K reduction over lanes, at the sizes where they can go
 wrong: widths at and just past the 128 and 256 tiles, one to a few proxies
 against long reductions (many slices of few chunks), token counts that are no
@@ -27,6 +27,14 @@ SHAPES = {
     "d256_rows16k": LayerShape(1, 32 * 520, 256, 256, 2, 128, (32,), mask=synth.BLOCK_CAUSAL),
     # under the tiles: the register-path kernel and the column-sum passes
     "d72_dp64": LayerShape(2, 8 * 33, 72, 64, 1, 64, (8,)),
+    # transposed per-head stores: runs of rows (m a multiple of 8, or one sequence)
+    # with padding columns, and 2-byte stores (two sequences of 21 proxies)
+    "cols_m24_B2": LayerShape(2, 8 * 24, 128, 128, 2, 64, (8,)),
+    "cols_m37_B1": LayerShape(1, 8 * 37, 128, 128, 1, 128, (8,), mask=synth.BIDIRECTIONAL),
+    "cols_m21_B2": LayerShape(2, 8 * 21, 128, 128, 2, 64, (8,)),
+    # stores through the row map: a real tail of one token, patches of an odd grid
+    "pad_tail1_B3": LayerShape(3, 8 * 9 + 1, 136, 128, 2, 64, (8,)),
+    "pad_tail1_add": LayerShape(2, 8 * 9 + 1, 72, 64, 1, 64, (4, 2), injection=synth.INJECT_ADD),
     "affine_d144": LayerShape(1, 8 * 130, 144, 128, 2, 64, (8,), injection=synth.INJECT_AFFINE),
     "fp32_d136": LayerShape(1, 8 * 70, 136, 128, 2, 64, (8,), dtype="fp32"),
     "fp32_affine_rows8k": LayerShape(1, 16 * 520, 40, 64, 1, 64, (16,), dtype="fp32", injection=synth.INJECT_AFFINE),

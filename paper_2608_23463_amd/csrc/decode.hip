@@ -1,7 +1,7 @@
 // Proxy-KV-cache decode step and block-triggered append (Eq. 19-21, Sec. 3.8).
 //
 // Step (one token per sequence, the batch in lockstep), four launches (three
-// for up to four sequences over few slices, see decode_gemv_out_kernel):
+// for one or two sequences over few slices, see decode_gemv_out_kernel):
 //  1. decode_proj_kernel: u = RMSNorm(x) * gamma formed on the fly and
 //     multiplied by W_q, W_k, W_v and W_alpha (one 32-column block of the
 //     concatenated outputs per workgroup, MFMA over 32 batch rows): q to
@@ -516,16 +516,17 @@ __global__ void __launch_bounds__(256) decode_combine_kernel(const DecodeAttnPar
   for (int u = 0; u < DH / 64; ++u) out[lane + 64 * u] = from_f32<T>(v[u]);
 }
 
-// ---- projections of one to four sequences ---------------------------------------
+// ---- projections of one and two sequences ---------------------------------------
 //
-// With a few rows the matrix kernel above spends its time on 32 staged rows,
-// most of them copies, and on the 1,400 instructions before its first product
-// (8.8 us for one sequence at d = 512, the weights a 2 us read; 4.6 us so, a
-// step of 4 sequences at d = 1024 over 1,000 rows 26.7 -> 22.7 us). Here a wave
-// takes four output columns and every row: its weights (16-byte loads along
-// a row), the rows and gamma are requested at once, the row norms and the
-// dot products are butterflies over the wave, and there is no LDS or barrier.
-constexpr int kGemvRows = 4;      // sequences
+// With one or two rows the matrix kernel above is mostly what precedes its
+// products: staged copies, the row norms, a barrier, and a sum through LDS.
+// Here a wave takes four output columns and every row: its weights (16-byte
+// loads along a row), the rows and gamma are requested at once, the row norms
+// and the dot products are butterflies over the wave, and there is no LDS or
+// barrier. One sequence at d = 512: 8.8 us with 32 staged rows, 4.6 so; a step
+// of two at d = 512 over 200 rows 18.6 -> 16.8 us; three and four are level or
+// slower (four at d = 2048: 28.5 us on the matrix kernel, 31.7 here).
+constexpr int kGemvRows = 2;      // sequences
 constexpr int kGemvCols = 4;      // output columns per wave
 
 template <int N>
@@ -818,12 +819,11 @@ static hipError_t launch_small_gemm(dim3 grid, const DecodeProjParams& pp, hipSt
   return by_rows(std::integral_constant<int, 4>{});
 }
 
-// Instance by rows (1, 2 or up to 4) and 16-byte chunks per lane and row.
+// Instance by rows (1 or 2) and 16-byte chunks per lane and row.
 template <class F>
 static hipError_t gemv_pick(int rows, int cpr, F&& go) {
   auto by_rows = [&](auto cpl) {
     if (rows <= 1) return go(std::integral_constant<int, 1>{}, cpl);
-    if (rows <= 2) return go(std::integral_constant<int, 2>{}, cpl);
     return go(std::integral_constant<int, kGemvRows>{}, cpl);
   };
   if (cpr <= 64) return by_rows(std::integral_constant<int, 1>{});
@@ -846,8 +846,7 @@ static hipError_t launch_gemv_proj(const DecodeProjParams& pp, hipStream_t strea
 // each, one after the other. Measured per step, merged against the merge of
 // its own launch: 8 heads x 200 rows 12.8 us, 16 heads x 2,000 rows (72 KB)
 // 16.6; past the first bound 16 heads x 8,000 rows (271 KB) 30.6 against 25.9,
-// past the second 4 sequences of 16 heads x 200 rows (eight pairs) 30.6
-// against 25.2 with the matrix kernels.
+// past the second 2 sequences of 16 heads x 4,000 rows 34.2 against 24.9.
 constexpr int64_t kMergeInOutBytes = 128 << 10;
 constexpr int kMergeInOutChannels = 1024;
 
@@ -866,7 +865,7 @@ static hipError_t launch_gemv_out(const DecodeProjParams& op, const DecodeAttnPa
   typedef std::integral_constant<int, 1> one;
   typedef std::integral_constant<int, 2> two;
   typedef std::integral_constant<int, 4> four;
-  if (op.B > 1) return cpr <= 64 ? go(four{}, one{}) : go(four{}, two{});  // d <= 512
+  if (op.B > 1) return cpr <= 64 ? go(two{}, one{}) : go(two{}, two{});  // d <= 512
   if (cpr <= 64) return go(one{}, one{});
   return cpr <= 128 ? go(one{}, two{}) : go(one{}, four{});
 }

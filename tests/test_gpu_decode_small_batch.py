@@ -1,5 +1,5 @@
 """Decode steps of one to seventeen sequences (the wave-per-columns projections and
-the merge inside the output map take up to four, the matrix kernels stage 8, 16
+the merge inside the output map take up to two, the matrix kernels stage 8, 16
 or 32 rows) and short cache slices, at
 the sizes where they can go wrong: widths of one to four 16-byte chunks per
 lane, head counts that are no multiple of four, caches at and around the slice
@@ -22,6 +22,8 @@ CASES = {
     "B3_d640_n129_dh128": (3, 5, 128, "bf16", 129),
     "B4_d1024_n700": (4, 16, 64, "bf16", 700),
     "B4_d2048_n300_dh128": (4, 16, 128, "bf16", 300),   # four chunks per lane
+    "B2_d2048_n40": (2, 32, 64, "bf16", 40),            # two rows of four chunks
+    "B2_d512_fp32_n150": (2, 8, 64, "fp32", 150),
     "B2_d512_n700_merged": (2, 8, 64, "bf16", 700),      # two rows in the merged output map
     "B4_d256_fp32_n90": (4, 4, 64, "fp32", 90),
     "B4_d1024_n3000_combine": (4, 16, 64, "bf16", 3000),  # partials past the merge's bound
@@ -29,7 +31,7 @@ CASES = {
     "B9_d512_n200": (9, 8, 64, "bf16", 200),            # four
     "B16_d1024_n60_dh128": (16, 8, 128, "bf16", 60),
     "B17_d256_fp32_n33": (17, 4, 64, "fp32", 33),       # eight
-    "B5_d512_n500": (5, 8, 64, "bf16", 500),            # one past the small-batch kernels
+    "B5_d512_n500": (5, 8, 64, "bf16", 500),
     "B1_d1024_fp32_n260": (1, 16, 64, "fp32", 260),     # four chunks per lane in fp32
     "B3_d192_fp32_n1100": (3, 3, 64, "fp32", 1100),
 }

@@ -553,7 +553,7 @@ static void prefill_impl(Runner& run, const DecodeDims& d, const pf_decode_weigh
     pr.M = rows;
     pr.N = d.d;
     pr.K = d.d;
-    EpiHeads<T> e{outs[i], outs_t[i], reinterpret_cast<const T*>(proj[i]->b), Tn, d.dh, d.nh, (int)W.ld_t, nullptr};
+    EpiHeads<T> e{outs[i], outs_t[i], reinterpret_cast<const T*>(proj[i]->b), FastDiv(Tn), d.dh, d.nh, (int)W.ld_t, nullptr};
     if (i == 0) {
       e.outs = q;
       e.scale = (float)(1.4426950408889634 / std::sqrt((double)d.dh));

@@ -20,15 +20,16 @@ struct EpiLinear {
   // with a map, `out` holds tokens: row r of the product is k of them, d wide
   // (only `out` then)
   RowMap map{};
-  int k = 1, d = 0;
+  int k = 1;
+  FastDiv d;
   __device__ __forceinline__ void operator()(int r, int c, float v) const {
     if (bias) v += to_f32(bias[c]);
     if (add) v += to_f32(add[(int64_t)r * ld_add + c]);
     const T o = from_f32<T>(v);
     if constexpr (MAP) {
-      const int t = c / d;
+      const int t = d.div(c);
       const int64_t row = map(r * k + t);
-      if (row >= 0) out[row * d + c - t * d] = o;
+      if (row >= 0) out[row * d.d + c - t * d.d] = o;
       return;
     }
     out[(int64_t)r * ldo + c] = o;
@@ -82,9 +83,9 @@ struct EpiLinear {
   __device__ __forceinline__ void finish(int r, int c, const float* v) const {
     float t[8];
     if constexpr (MAP) {
-      const int q = c / d;
+      const int q = d.div(c);
       const int64_t row = map(r * k + q);
-      if (row >= 0) store8(out + row * d + c - q * d, v);
+      if (row >= 0) store8(out + row * d.d + c - q * d.d, v);
       return;
     }
     store8(out + (int64_t)r * ldo + c, v);
@@ -109,7 +110,8 @@ struct EpiHeads {
   T* out;
   T* out_t;
   const T* bias;
-  int m, dh, n_heads, ld_t;
+  FastDiv m;  // rows per sequence
+  int dh, n_heads, ld_t;
   T* out_lo;  // optional low part of the split, row layout
   T* outs = nullptr;
   float scale = 1.0f;
@@ -125,12 +127,13 @@ struct EpiHeads {
   // of eight rows lies inside one sequence and starts 16-byte aligned: one
   // sequence, or m a multiple of 8. Otherwise 2-byte stores
   // (Q, K and V of 16,384 proxies at d = 512: 88 us so, 80 with the runs).
-  __device__ __forceinline__ bool cols() const { return out_t && sizeof(T) == 2 && (single || m % 8 == 0); }
+  __device__ __forceinline__ bool cols() const { return out_t && sizeof(T) == 2 && (single || m.d % 8 == 0); }
   int single = 0;  // one sequence (rows == m)
+  __device__ __forceinline__ int head(int c) const { return dh == 64 ? c >> 6 : c >> 7; }  // dh is 64 or 128
   __device__ __forceinline__ void col8(int r0, int c, const float* v, int rows) const {
     const float bc = bias ? to_f32(bias[c]) : 0.0f;
-    const int b = single ? 0 : r0 / m, i = r0 - b * m;
-    const int hd = c / dh, e = c - hd * dh;
+    const int b = single ? 0 : m.div(r0), i = r0 - b * m.d;
+    const int hd = head(c), e = c - hd * dh;
     T* dst = out_t + (((int64_t)b * n_heads + hd) * dh + e) * ld_t + i;
     float t[8];
 #pragma unroll
@@ -162,28 +165,28 @@ struct EpiHeads {
   }
   // 8 consecutive channels stay inside one head (dh is a multiple of 8)
   __device__ __forceinline__ void finish(int r, int c, const float* v, bool rowwise) const {
-    const int b = r / m, i = r - b * m;
-    const int hd = c / dh, e0 = c - hd * dh;
+    const int b = m.div(r), i = r - b * m.d;
+    const int hd = head(c), e0 = c - hd * dh;
     const int64_t bh = (int64_t)b * n_heads + hd;
-    if (out) store8(out + (bh * m + i) * dh + e0, v);
+    if (out) store8(out + (bh * m.d + i) * dh + e0, v);
     if (out_lo) {
       float t[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) t[e] = split_lo(v[e]);
-      store8(out_lo + (bh * m + i) * dh + e0, t);
+      store8(out_lo + (bh * m.d + i) * dh + e0, t);
     }
     if (outs) {
       float s[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) s[e] = v[e] * scale;
-      store8(outs + (bh * m + i) * dh + e0, s);
+      store8(outs + (bh * m.d + i) * dh + e0, s);
     }
     if (out_t) {
       if (rowwise)
 #pragma unroll
         for (int e = 0; e < 8; ++e) out_t[(bh * dh + e0 + e) * ld_t + i] = from_f32<T>(v[e]);
 #pragma unroll 1
-      for (int p = 2 * m - 1 - i; p < ld_t; p += m)
+      for (int p = 2 * m.d - 1 - i; p < ld_t; p += m.d)
 #pragma unroll 1
         for (int e = 0; e < 8; ++e) out_t[(bh * dh + e0 + e) * ld_t + p] = (T)0.0f;
     }
@@ -197,7 +200,7 @@ struct EpiHeads {
       }
       const float* first = xmode == 1 ? lo : hi;
       const float* second = xmode == 1 ? hi : lo;
-      uint8_t* row = outx + (bh * m + i) * 2 * dh;
+      uint8_t* row = outx + (bh * m.d + i) * 2 * dh;
       typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
       *reinterpret_cast<u32x2_t*>(row + e0) =
           u32x2_t{pack_bf8x4(first[0], first[1], first[2], first[3]), pack_bf8x4(first[4], first[5], first[6], first[7])};
@@ -220,11 +223,12 @@ template <typename T>
 struct EpiShift {
   T* out;
   const T* bias;
-  int m, ld;
+  FastDiv m;  // rows per sequence
+  int ld;
   __device__ __forceinline__ void operator()(int r, int c, float v) const {
     if (bias) v += to_f32(bias[c]);
-    const int i = r % m;
-    if (i < m - 1)
+    const int i = r - m.div(r) * m.d;
+    if (i < m.d - 1)
       out[(int64_t)(r + 1) * ld + c] = from_f32<T>(v);
     else
       out[(int64_t)(r - i) * ld + c] = from_f32<T>(0.0f);
@@ -252,8 +256,8 @@ struct EpiShift {
     finish(r, c, v);
   }
   __device__ __forceinline__ void finish(int r, int c, const float* v) const {
-    const int i = r % m;
-    if (i < m - 1) {
+    const int i = r - m.div(r) * m.d;
+    if (i < m.d - 1) {
       store8(out + (int64_t)(r + 1) * ld + c, v);
     } else {
       const float z[8] = {0, 0, 0, 0, 0, 0, 0, 0};

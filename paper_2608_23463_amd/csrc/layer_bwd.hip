@@ -38,16 +38,17 @@ namespace pf {
 template <typename T, bool MAP>
 __global__ void __launch_bounds__(256) gate_bwd_prep_kernel(const T* __restrict__ dy, const T* __restrict__ delta,
                                                             const T* __restrict__ g, T* __restrict__ dg, int64_t n8,
-                                                            const RowMap map, int d8, T* __restrict__ dy_out) {
+                                                            const RowMap map, const FastDiv d8,
+                                                            T* __restrict__ dy_out) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < n8; c += stride) {
     float a[8], b[8], z[8], o[8];
     if constexpr (MAP) {
-      const int r = (int)(c / d8);
+      const int r = n8 < ((int64_t)1 << 31) ? d8.div((int)c) : (int)(c / d8.d);
       const int64_t row = map(r);
 #pragma unroll
       for (int e = 0; e < 8; ++e) a[e] = 0.0f;
-      if (row >= 0) load8(dy + (row * d8 + c - (int64_t)r * d8) * 8, a);
+      if (row >= 0) load8(dy + (row * d8.d + c - (int64_t)r * d8.d) * 8, a);
       store8(dy_out + c * 8, a);
     } else {
       load8(dy + c * 8, a);
@@ -319,29 +320,30 @@ struct EpiGateDgrad {
 template <typename T>
 struct EpiUnshift {
   T* out;
-  int m, ld, shift;
+  FastDiv m;  // rows per sequence
+  int ld, shift;
   __device__ __forceinline__ void operator()(int r, int c, float v) const {
     if (!shift) {
       out[(int64_t)r * ld + c] = from_f32<T>(v);
       return;
     }
-    const int i = r % m;
+    const int i = r - m.div(r) * m.d;
     if (i > 0)
       out[(int64_t)(r - 1) * ld + c] = from_f32<T>(v);
     else
-      out[(int64_t)(r + m - 1) * ld + c] = from_f32<T>(0.0f);
+      out[(int64_t)(r + m.d - 1) * ld + c] = from_f32<T>(0.0f);
   }
   __device__ __forceinline__ void vec8(int r, int c, const float* v) const {
     if (!shift) {
       store8(out + (int64_t)r * ld + c, v);
       return;
     }
-    const int i = r % m;
+    const int i = r - m.div(r) * m.d;
     if (i > 0) {
       store8(out + (int64_t)(r - 1) * ld + c, v);
     } else {
       const float z[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-      store8(out + (int64_t)(r + m - 1) * ld + c, z);
+      store8(out + (int64_t)(r + m.d - 1) * ld + c, z);
     }
   }
 };
@@ -359,14 +361,15 @@ struct EpiAccum {
   T* out2;
   // with a map, `out` holds tokens: row r of the product is k of them, d wide
   RowMap map{};
-  int k = 1, d = 0;
+  int k = 1;
+  FastDiv d;
   __device__ __forceinline__ void operator()(int r, int c, float v) const {
     const int64_t i = (int64_t)r * ld + c;
     const float t = v + (first ? (add ? to_f32(add[i]) : 0.0f) : acc[i]);
     if (MAP && out) {
-      const int q = c / d;
+      const int q = d.div(c);
       const int64_t row = map(r * k + q);
-      if (row >= 0) out[row * d + c - q * d] = from_f32<T>(t);
+      if (row >= 0) out[row * d.d + c - q * d.d] = from_f32<T>(t);
     } else if (out) {
       out[i] = from_f32<T>(t);
       if (out2) out2[i] = from_f32<T>(t);
@@ -401,9 +404,9 @@ struct EpiAccum {
   __device__ __forceinline__ void finish(int r, int c, const float* t) const {
     const int64_t i = (int64_t)r * ld + c;
     if (MAP && out) {
-      const int q = c / d;
+      const int q = d.div(c);
       const int64_t row = map(r * k + q);
-      if (row >= 0) store8(out + row * d + c - q * d, t);
+      if (row >= 0) store8(out + row * d.d + c - q * d.d, t);
     } else if (out) {
       store8(out + i, t);
       if (out2) store8(out2 + i, t);
@@ -576,7 +579,11 @@ static void wgrad_group(Runner& run, const char* label, const WgradItem<float>* 
 
 // dA [rows, N] = G [rows, K] W [K, N] for a weight W stored [K (out), N (in)]:
 // the weight is read contiguous along N (LAYOUT_MN), or, over many rows,
-// transposed once into tr_w ([N, K]) for the direct kernel.
+// transposed once into tr_w ([N, K]) for the direct kernel. In bf16, where the
+// direct kernel also reads the weight as it is, some 4 % slower, the
+// transpose's launch (5 us and more) pays from about 1.2e11 operations: the
+// gate's data gradient of 20,224 rows at d = 512 (2.1e10) 48.0 + 6.2 us
+// transposed, 49.9 as it is.
 template <typename T, class Epi>
 static void dgrad(Runner& run, const char* label, const T* g, int64_t ldg, const void* w, int64_t ldw, int64_t rows,
                   int N, int K, const Epi& epi, T* tr_w) {
@@ -586,7 +593,8 @@ static void dgrad(Runner& run, const char* label, const T* g, int64_t ldg, const
   pr.M = (int)rows;
   pr.N = N;
   pr.K = K;
-  if (rows >= kTransposeMinRows) {
+  const bool as_is = sizeof(T) == 2 && 2.0 * (double)rows * N * K < 1.2e11 && N >= 128;
+  if (rows >= kTransposeMinRows && !as_is) {
     transpose<T>(run, "transpose", reinterpret_cast<const T*>(w), ldw, K, N, tr_w, K);
     pr.b = tr_w;
     pr.ldb = K;
@@ -666,11 +674,11 @@ static void backward_impl(Runner& run, const LayerDims& d, const pf_layer_config
       const int blocks = (int)std::min<int64_t>((n8 + 255) / 256, 16384);
       if (d.map.mode)  // the copy of dY is made here
         hipLaunchKernelGGL((gate_bwd_prep_kernel<T, true>), dim3(blocks), dim3(256), 0, run.stream,
-                           reinterpret_cast<const T*>(dy_in), S(A.delta), S(A.g), WT(W.dg), n8, d.map, df / 8,
+                           reinterpret_cast<const T*>(dy_in), S(A.delta), S(A.g), WT(W.dg), n8, d.map, FastDiv(df / 8),
                            WT(W.dy_pad));
       else
         hipLaunchKernelGGL((gate_bwd_prep_kernel<T, false>), dim3(blocks), dim3(256), 0, run.stream, dyp, S(A.delta),
-                           S(A.g), WT(W.dg), n8, d.map, df / 8, (T*)nullptr);
+                           S(A.g), WT(W.dg), n8, d.map, FastDiv(df / 8), (T*)nullptr);
       return hipGetLastError();
     });
     dgrad<T>(run, "gate_dgrad_gemm", WT(W.dg), df, w->gate.w, 2 * df, BL, 2 * df, df,
@@ -693,7 +701,7 @@ static void backward_impl(Runner& run, const LayerDims& d, const pf_layer_config
     wgrads("decompress_wgrad_gemm", &item, 1, rows);
     if (j == d.M - 1) {
       dgrad<T>(run, "decompress_dgrad_gemm", dT, kd, w->decompress[j].w, dn, rows, dn, kd,
-               EpiUnshift<T>{WT(W.dhbar), (int)d.m, dp, cfg->mask == PF_TOKEN_CAUSAL ? 1 : 0}, trw);
+               EpiUnshift<T>{WT(W.dhbar), FastDiv((int)d.m), dp, cfg->mask == PF_TOKEN_CAUSAL ? 1 : 0}, trw);
     } else {
       dgrad<T>(run, "decompress_dgrad_gemm", dT, kd, w->decompress[j].w, dn, rows, dn, kd,
                EpiLinear<T>{WT(W.du[j + 1]), dn, nullptr, nullptr, 0, nullptr}, trw);
@@ -702,7 +710,7 @@ static void backward_impl(Runner& run, const LayerDims& d, const pf_layer_config
   }
 
   // 3. output map of the interaction
-  EpiHeads<T> dO_epi{WT(W.dO), WT(W.dOt), nullptr, (int)d.m, d.dh, d.nh, d.ld_t};
+  EpiHeads<T> dO_epi{WT(W.dO), WT(W.dOt), nullptr, FastDiv((int)d.m), d.dh, d.nh, d.ld_t};
   dO_epi.single = d.B == 1;
   dgrad<T>(run, "o_dgrad_gemm", WT(W.dhbar), dp, w->o.w, dp, Bm, dp, dp,
            dO_epi, trw);
@@ -792,7 +800,7 @@ static void backward_impl(Runner& run, const LayerDims& d, const pf_layer_config
         e.out = reinterpret_cast<T*>(dx);
         e.map = d.map;
         e.k = d.k[0];
-        e.d = df;
+        e.d = FastDiv(df);
         dgrad<T>(run, "compress_dgrad_gemm", dz, dn, w->compress[j].w, kd, rows, kd, dn, e, trw);
       };
       if (d.map.mode)

@@ -216,9 +216,10 @@ int layer_dims(const pf_layer_config* c, LayerDims* d, const char** why) {
   }
   d->map = RowMap{};
   if (d->img_w)
-    d->map = RowMap{2, (int)d->L, (int)d->L_in, d->img_w, d->patch, (int)d->P, d->img_w / d->patch};
+    d->map = RowMap{2, (int)d->L_in, d->img_w, FastDiv((int)d->L), FastDiv(d->patch), FastDiv((int)d->P),
+                    FastDiv(d->img_w / d->patch)};
   else if (d->L != d->L_in)
-    d->map = RowMap{1, (int)d->L, (int)d->L_in, 0, 0, 0, 0};
+    d->map = RowMap{1, (int)d->L_in, 0, FastDiv((int)d->L), FastDiv(), FastDiv(), FastDiv()};
   d->d[0] = d->d_f;
   for (int j = 1; j < d->M; ++j) d->d[j] = c->level_dims[j - 1] > 0 ? c->level_dims[j - 1] : d->d_p;
   d->d[d->M] = d->d_p;
@@ -483,7 +484,7 @@ static void forward_impl(Runner& run, const LayerDims& d, const pf_layer_config*
       pr.b_ksplit = d.d_p;
       pr.K = 2 * d.d_p;
     }
-    EpiHeads<T> e{outs[i], outs_t[i], reinterpret_cast<const T*>(proj[i]->b), (int)d.m, d.dh, d.nh, d.ld_t,
+    EpiHeads<T> e{outs[i], outs_t[i], reinterpret_cast<const T*>(proj[i]->b), FastDiv((int)d.m), d.dh, d.nh, d.ld_t,
                   outs_lo[i]};
     e.single = d.B == 1;
     if (i == 0) {
@@ -527,7 +528,7 @@ static void forward_impl(Runner& run, const LayerDims& d, const pf_layer_config*
     pr.K = d.d_p;
     const T* bo = reinterpret_cast<const T*>(w->o.b);
     if (cfg->mask == PF_TOKEN_CAUSAL) {
-      run.gemm<T, LAYOUT_K, LAYOUT_K>("o_gemm", pr, EpiShift<T>{P(A.s), bo, (int)d.m, d.d_p});
+      run.gemm<T, LAYOUT_K, LAYOUT_K>("o_gemm", pr, EpiShift<T>{P(A.s), bo, FastDiv((int)d.m), d.d_p});
     } else {
       run.gemm<T, LAYOUT_K, LAYOUT_K>("o_gemm", pr, EpiLinear<T>{P(A.s), d.d_p, bo, nullptr, 0, nullptr});
     }
@@ -556,7 +557,7 @@ static void forward_impl(Runner& run, const LayerDims& d, const pf_layer_config*
         e.add = reinterpret_cast<const T*>(x);
         e.map = d.map;
         e.k = d.k[0];
-        e.d = d.d_f;
+        e.d = FastDiv(d.d_f);
         run.gemm<T, LAYOUT_K, LAYOUT_K>("decompress_gemm", pr, e);
       };
       if (d.map.mode)

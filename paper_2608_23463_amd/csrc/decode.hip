@@ -1,7 +1,7 @@
 // Proxy-KV-cache decode step and block-triggered append (Eq. 19-21, Sec. 3.8).
 //
 // Step (one token per sequence, the batch in lockstep), four launches (three
-// for one or two sequences over few slices, see decode_gemv_out_kernel):
+// for up to four sequences over few slices, which merge in the fourth):
 //  1. decode_proj_kernel: u = RMSNorm(x) * gamma formed on the fly and
 //     multiplied by W_q, W_k, W_v and W_alpha (one 32-column block of the
 //     concatenated outputs per workgroup, MFMA over 32 batch rows): q to
@@ -138,6 +138,68 @@ struct DecodeProjParams {
   __device__ __forceinline__ int slot(int b) const { return pos.ragged ? pos.j[b] : j; }
 };
 
+struct DecodeAttnParams {
+  const void* q;       // [B, d]
+  const void* kc;      // [B, h, n_cap, dh]
+  const void* vc;
+  const void* kl;      // [B, h, P, dh]
+  const void* vl;
+  float* part_m;       // [B*h, S+1]
+  float* part_l;
+  float* part_acc;     // [B*h, S+1, dh]
+  const float* alpha;  // [B, h]
+  void* attn;          // [B, d] output A
+  int64_t n, n_cap, P;
+  int j;               // local slots 0..j are valid
+  int nh, splits, chunk;
+  bool lean;
+  float scale_log2;
+  DecodePos pos;       // per-sequence n and j when pos.ragged
+};
+
+// out[u] = A[b, h, c0 + u * kStride] = A_x + alpha * A_h from the partials of
+// one (sequence, head): cache slices merged in a fixed order with a running
+// maximum (A_h, zero without cached rows), local slice normalised (A_x). The
+// loads of up to kBatch slices, the local part and alpha go out together
+// before any is used, so a step with up to kBatch slices waits for memory once.
+// The multiply-adds are written out: every caller gets the same bits, so a
+// sequence's result does not depend on the batch it is decoded in.
+template <int DH, int kC, int kStride, int kBatch>
+__device__ __forceinline__ void merge_partials(const DecodeAttnParams& p, int bh, int c0, float (&out)[kC]) {
+  const int64_t base = (int64_t)bh * (p.splits + 1);
+  const float al = p.alpha[bh];  // alpha is [B, h] as the partials are
+  const float lx = p.part_l[base + p.splits];
+  float ax[kC];
+#pragma unroll
+  for (int u = 0; u < kC; ++u) ax[u] = p.part_acc[(base + p.splits) * DH + c0 + kStride * u];
+  float mrun = -INFINITY, lrun = 0.0f, arun[kC];
+#pragma unroll
+  for (int u = 0; u < kC; ++u) arun[u] = 0.0f;
+  for (int s0 = 0; s0 < p.splits; s0 += kBatch) {
+    float m[kBatch], l[kBatch], a[kBatch][kC];
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) {
+      const int s = min(s0 + i, p.splits - 1);
+      m[i] = p.part_m[base + s];
+      l[i] = p.part_l[base + s];
+#pragma unroll
+      for (int u = 0; u < kC; ++u) a[i][u] = p.part_acc[(base + s) * DH + c0 + kStride * u];
+    }
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) {
+      if (s0 + i >= p.splits || m[i] == -INFINITY) continue;
+      const float mn = fmaxf(mrun, m[i]);
+      const float f0 = fast_exp2(mrun - mn), f1 = fast_exp2(m[i] - mn);
+      lrun = fmaf(lrun, f0, l[i] * f1);
+#pragma unroll
+      for (int u = 0; u < kC; ++u) arun[u] = fmaf(arun[u], f0, a[i][u] * f1);
+      mrun = mn;
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < kC; ++u) out[u] = fmaf(al, mrun == -INFINITY ? 0.0f : arun[u] / lrun, ax[u] / lx);
+}
+
 // LDS of a workgroup that stages `rows` rows of A.
 template <typename T>
 constexpr size_t decode_small_gemm_lds(int d, int rows = 32) {
@@ -145,13 +207,18 @@ constexpr size_t decode_small_gemm_lds(int d, int rows = 32) {
 }
 
 // RPW: rows that each of the four waves stages, 8 for a full block of 32
-// sequences, 4 or 2 where the batch ends within 16 or 8: the rows past them
+// sequences, 4, 2 or 1 where the batch ends within 16, 8 or 4: the rows past them
 // would be copies of the last, and their loads, norms and instructions are
 // most of what precedes the first product (a step at d = 1024 over 500 rows: 8
-// sequences 27.8 -> 22.2 us, 12 sequences 29.6 -> 25.7). The matrix tile keeps 32
+// sequences 27.8 -> 22.2 us, 12 sequences 29.6 -> 25.7). A row's arithmetic is
+// the same in all. The matrix tile keeps 32
 // rows; those past the staged ones repeat them and are not stored.
-template <typename T, bool PROJ, int CPL, int RPW>
-__global__ void __launch_bounds__(256) decode_small_gemm_kernel(const DecodeProjParams p) {
+//
+// MERGE (the output map, head dimension MERGE): A is not read but merged here
+// from the slice partials, rounded to the activation type as the stored A
+// would be.
+template <typename T, bool PROJ, int CPL, int RPW, int MERGE>
+__global__ void __launch_bounds__(256) decode_small_gemm_kernel(const DecodeProjParams p, const DecodeAttnParams ap) {
   typedef Mma<T> MM;
   constexpr int kV = 16 / sizeof(T);  // elements per 16-byte chunk
   extern __shared__ __attribute__((aligned(16))) char dyn[];
@@ -185,7 +252,7 @@ __global__ void __launch_bounds__(256) decode_small_gemm_kernel(const DecodeProj
   const T* src = PROJ ? x : reinterpret_cast<const T*>(p.a);
   u32x4 raw[RPW][CPL];
 #pragma unroll
-  for (int rr = 0; rr < RPW; ++rr)
+  for (int rr = 0; rr < RPW && MERGE == 0; ++rr)
 #pragma unroll
     for (int i = 0; i < CPL; ++i) {
       const int b = min(b0 + wave * RPW + rr, p.B - 1), c = min(lane + 64 * i, cpr - 1);
@@ -219,40 +286,52 @@ __global__ void __launch_bounds__(256) decode_small_gemm_kernel(const DecodeProj
     bv[u] = bias ? braw : 0.0f;
     xr[u] = PROJ ? 0.0f : to_f32(x[(int64_t)b * p.d + c]);
   }
+  if constexpr (MERGE != 0) {
+    // rows past the batch keep what the LDS held: their results are not stored
+    for (int it = tid; it < p.B * (p.d / 2); it += 256) {
+      const int r = it / (p.d / 2), c = 2 * (it - r * (p.d / 2));
+      float v[2];
+      merge_partials<MERGE, 2, 1, 16>(ap, r * ap.nh + c / MERGE, c % MERGE, v);
+      T* slot = a_slot(r, c / kV) + c % kV;
+      slot[0] = from_f32<T>(v[0]);
+      slot[1] = from_f32<T>(v[1]);
+    }
+  } else {
 #pragma unroll
-  for (int rr = 0; rr < RPW; ++rr) {
-    const int r = wave * RPW + rr, b = b0 + r;
-    float inv = 1.0f;
-    if constexpr (PROJ) {
-      float ss = 0.0f;
+    for (int rr = 0; rr < RPW; ++rr) {
+      const int r = wave * RPW + rr, b = b0 + r;
+      float inv = 1.0f;
+      if constexpr (PROJ) {
+        float ss = 0.0f;
+#pragma unroll
+        for (int i = 0; i < CPL; ++i) {
+          const T* v = reinterpret_cast<const T*>(&raw[rr][i]);
+          if (lane + 64 * i < cpr)
+#pragma unroll
+            for (int e = 0; e < kV; ++e) ss += to_f32(v[e]) * to_f32(v[e]);
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
+        inv = 1.0f / sqrtf(ss / (float)p.d + p.eps);
+      }
 #pragma unroll
       for (int i = 0; i < CPL; ++i) {
-        const T* v = reinterpret_cast<const T*>(&raw[rr][i]);
-        if (lane + 64 * i < cpr)
+        const int c = lane + 64 * i;
+        if (c >= cpr) continue;
+        u32x4 v = raw[rr][i];
+        if (b >= p.B) v = u32x4{0u, 0u, 0u, 0u};
+        if constexpr (PROJ) {
+          if (blockIdx.x == 0 && b < p.B)  // x into block slot j
+            st16(reinterpret_cast<T*>(p.x_blk) + ((int64_t)b * p.P + p.slot(b)) * p.d + c * kV, v);
+          const T* xv = reinterpret_cast<const T*>(&v);
+          const T* gv = reinterpret_cast<const T*>(&graw[i]);
+          T uv[kV];
 #pragma unroll
-          for (int e = 0; e < kV; ++e) ss += to_f32(v[e]) * to_f32(v[e]);
+          for (int e = 0; e < kV; ++e) uv[e] = from_f32<T>(to_f32(xv[e]) * inv * to_f32(gv[e]));
+          v = *reinterpret_cast<const u32x4*>(uv);
+        }
+        st16(a_slot(r, c), v);
       }
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
-      inv = 1.0f / sqrtf(ss / (float)p.d + p.eps);
-    }
-#pragma unroll
-    for (int i = 0; i < CPL; ++i) {
-      const int c = lane + 64 * i;
-      if (c >= cpr) continue;
-      u32x4 v = raw[rr][i];
-      if (b >= p.B) v = u32x4{0u, 0u, 0u, 0u};
-      if constexpr (PROJ) {
-        if (blockIdx.x == 0 && b < p.B)  // x into block slot j
-          st16(reinterpret_cast<T*>(p.x_blk) + ((int64_t)b * p.P + p.slot(b)) * p.d + c * kV, v);
-        const T* xv = reinterpret_cast<const T*>(&v);
-        const T* gv = reinterpret_cast<const T*>(&graw[i]);
-        T uv[kV];
-#pragma unroll
-        for (int e = 0; e < kV; ++e) uv[e] = from_f32<T>(to_f32(xv[e]) * inv * to_f32(gv[e]));
-        v = *reinterpret_cast<const u32x4*>(uv);
-      }
-      st16(a_slot(r, c), v);
     }
   }
   __syncthreads();
@@ -314,65 +393,6 @@ __global__ void __launch_bounds__(256) decode_small_gemm_kernel(const DecodeProj
   }
 }
 
-struct DecodeAttnParams {
-  const void* q;       // [B, d]
-  const void* kc;      // [B, h, n_cap, dh]
-  const void* vc;
-  const void* kl;      // [B, h, P, dh]
-  const void* vl;
-  float* part_m;       // [B*h, S+1]
-  float* part_l;
-  float* part_acc;     // [B*h, S+1, dh]
-  const float* alpha;  // [B, h]
-  void* attn;          // [B, d] output A
-  int64_t n, n_cap, P;
-  int j;               // local slots 0..j are valid
-  int nh, splits, chunk;
-  float scale_log2;
-  DecodePos pos;       // per-sequence n and j when pos.ragged
-};
-
-// out[u] = A[b, h, c0 + u * kStride] = A_x + alpha * A_h from the partials of
-// one (sequence, head): cache slices merged in a fixed order with a running
-// maximum (A_h, zero without cached rows), local slice normalised (A_x). The
-// loads of up to kBatch slices, the local part and alpha go out together
-// before any is used, so a step with up to kBatch slices waits for memory once.
-template <int DH, int kC, int kStride, int kBatch>
-__device__ __forceinline__ void merge_partials(const DecodeAttnParams& p, int bh, int c0, float (&out)[kC]) {
-  const int64_t base = (int64_t)bh * (p.splits + 1);
-  const float al = p.alpha[bh];  // alpha is [B, h] as the partials are
-  const float lx = p.part_l[base + p.splits];
-  float ax[kC];
-#pragma unroll
-  for (int u = 0; u < kC; ++u) ax[u] = p.part_acc[(base + p.splits) * DH + c0 + kStride * u];
-  float mrun = -INFINITY, lrun = 0.0f, arun[kC];
-#pragma unroll
-  for (int u = 0; u < kC; ++u) arun[u] = 0.0f;
-  for (int s0 = 0; s0 < p.splits; s0 += kBatch) {
-    float m[kBatch], l[kBatch], a[kBatch][kC];
-#pragma unroll
-    for (int i = 0; i < kBatch; ++i) {
-      const int s = min(s0 + i, p.splits - 1);
-      m[i] = p.part_m[base + s];
-      l[i] = p.part_l[base + s];
-#pragma unroll
-      for (int u = 0; u < kC; ++u) a[i][u] = p.part_acc[(base + s) * DH + c0 + kStride * u];
-    }
-#pragma unroll
-    for (int i = 0; i < kBatch; ++i) {
-      if (s0 + i >= p.splits || m[i] == -INFINITY) continue;
-      const float mn = fmaxf(mrun, m[i]);
-      const float f0 = fast_exp2(mrun - mn), f1 = fast_exp2(m[i] - mn);
-      lrun = lrun * f0 + l[i] * f1;
-#pragma unroll
-      for (int u = 0; u < kC; ++u) arun[u] = arun[u] * f0 + a[i][u] * f1;
-      mrun = mn;
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < kC; ++u) out[u] = ax[u] / lx + al * (mrun == -INFINITY ? 0.0f : arun[u] / lrun);
-}
-
 template <typename T, int DH>
 __global__ void __launch_bounds__(256) decode_attn_kernel(const DecodeAttnParams p) {
   constexpr int kVec = 16 / sizeof(T);
@@ -391,8 +411,10 @@ __global__ void __launch_bounds__(256) decode_attn_kernel(const DecodeAttnParams
   if (s < p.splits) {
     base_k = reinterpret_cast<const T*>(p.kc) + (int64_t)bh * p.n_cap * DH;
     base_v = reinterpret_cast<const T*>(p.vc) + (int64_t)bh * p.n_cap * DH;
-    r0 = (int64_t)s * p.chunk;
-    r1 = std::min<int64_t>(p.pos.ragged ? p.pos.n[b] : p.n, r0 + p.chunk);  // empty slices leave m = -inf
+    const int64_t n = p.pos.ragged ? p.pos.n[b] : p.n;
+    const int chunk = p.pos.ragged ? slice_rows((int)n, p.lean) : p.chunk;
+    r0 = (int64_t)s * chunk;
+    r1 = std::min<int64_t>(n, r0 + chunk);  // empty slices leave m = -inf
   } else {
     base_k = reinterpret_cast<const T*>(p.kl) + (int64_t)bh * p.P * DH;
     base_v = reinterpret_cast<const T*>(p.vl) + (int64_t)bh * p.P * DH;
@@ -516,170 +538,6 @@ __global__ void __launch_bounds__(256) decode_combine_kernel(const DecodeAttnPar
   for (int u = 0; u < DH / 64; ++u) out[lane + 64 * u] = from_f32<T>(v[u]);
 }
 
-// ---- projections of one and two sequences ---------------------------------------
-//
-// With one or two rows the matrix kernel above is mostly what precedes its
-// products: staged copies, the row norms, a barrier, and a sum through LDS.
-// Here a wave takes four output columns and every row: its weights (16-byte
-// loads along a row), the rows and gamma are requested at once, the row norms
-// and the dot products are butterflies over the wave, and there is no LDS or
-// barrier. One sequence at d = 512: 8.8 us with 32 staged rows, 4.6 so; a step
-// of two at d = 512 over 200 rows 18.6 -> 16.8 us; three and four are level or
-// slower (four at d = 2048: 28.5 us on the matrix kernel, 31.7 here).
-constexpr int kGemvRows = 2;      // sequences
-constexpr int kGemvCols = 4;      // output columns per wave
-
-template <int N>
-__device__ __forceinline__ void wave_sums(float (&v)[N]) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1)
-#pragma unroll
-    for (int i = 0; i < N; ++i) v[i] += __shfl_xor(v[i], off);
-}
-
-// Step 1 (see DecodeProjParams): q, k, v, alpha of the new token, and x into
-// its block slot.
-template <typename T, int NB, int CPL>
-__global__ void __launch_bounds__(256) decode_gemv_proj_kernel(const DecodeProjParams p) {
-  constexpr int kV = 16 / sizeof(T);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int cpr = p.d / kV;
-  const int c0 = (blockIdx.x * 4 + wave) * kGemvCols;
-  const int seg = min(c0 / p.d, 3), cs = c0 - seg * p.d, width = p.width[seg];
-  if (cs >= width) return;
-  const T* x = reinterpret_cast<const T*>(p.x);
-  const T* w = reinterpret_cast<const T*>(p.w[seg]);
-  u32x4 wr[kGemvCols][CPL], xr[NB][CPL], gr[CPL];
-#pragma unroll
-  for (int i = 0; i < CPL; ++i) {
-    const int ci = min(lane + 64 * i, cpr - 1) * kV;  // lanes past the row repeat its end, masked below
-#pragma unroll
-    for (int b = 0; b < NB; ++b) xr[b][i] = ld16(x + (int64_t)min(b, p.B - 1) * p.d + ci);
-    gr[i] = ld16(reinterpret_cast<const T*>(p.gamma) + ci);
-#pragma unroll
-    for (int u = 0; u < kGemvCols; ++u) wr[u][i] = ld16(w + (int64_t)min(cs + u, width - 1) * p.d + ci);
-  }
-  const int ob = lane / kGemvCols, oc = cs + lane % kGemvCols;  // this lane's output
-  const T* bias = reinterpret_cast<const T*>(p.bias[seg]);
-  const float bv = bias ? to_f32(bias[min(oc, width - 1)]) : 0.0f;
-  if (blockIdx.x == 0) {  // x into block slot j, one row per wave
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
-      if (wave == b % 4 && b < p.B)
-#pragma unroll
-        for (int i = 0; i < CPL; ++i)
-          if (lane + 64 * i < cpr)
-            st16(reinterpret_cast<T*>(p.x_blk) + ((int64_t)b * p.P + p.slot(b)) * p.d + (lane + 64 * i) * kV, xr[b][i]);
-  }
-  float ss[NB];
-#pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    ss[b] = 0.0f;
-#pragma unroll
-    for (int i = 0; i < CPL; ++i) {
-      const T* v = reinterpret_cast<const T*>(&xr[b][i]);
-      if (lane + 64 * i < cpr)
-#pragma unroll
-        for (int e = 0; e < kV; ++e) ss[b] += to_f32(v[e]) * to_f32(v[e]);
-    }
-  }
-  wave_sums(ss);
-  float acc[NB * kGemvCols];
-#pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    const float inv = 1.0f / sqrtf(ss[b] / (float)p.d + p.eps);
-#pragma unroll
-    for (int u = 0; u < kGemvCols; ++u) acc[b * kGemvCols + u] = 0.0f;
-#pragma unroll
-    for (int i = 0; i < CPL; ++i) {
-      const T* xv = reinterpret_cast<const T*>(&xr[b][i]);
-      const T* gv = reinterpret_cast<const T*>(&gr[i]);
-      const bool ok = lane + 64 * i < cpr;
-#pragma unroll
-      for (int e = 0; e < kV; ++e) {  // u rounded to the activation type, as a stored u would be
-        const float uv = ok ? to_f32(from_f32<T>(to_f32(xv[e]) * inv * to_f32(gv[e]))) : 0.0f;
-#pragma unroll
-        for (int u = 0; u < kGemvCols; ++u)
-          acc[b * kGemvCols + u] = fmaf(uv, to_f32(reinterpret_cast<const T*>(&wr[u][i])[e]), acc[b * kGemvCols + u]);
-      }
-    }
-  }
-  wave_sums(acc);
-  float v = bv;
-#pragma unroll
-  for (int k = 0; k < NB * kGemvCols; ++k)
-    if (lane == k) v += acc[k];
-  if (ob >= p.B || ob >= NB || oc >= width) return;
-  if (seg == 0) {
-    reinterpret_cast<T*>(p.q)[(int64_t)ob * p.d + oc] = from_f32<T>(v);
-  } else if (seg < 3) {
-    T* dst = reinterpret_cast<T*>(seg == 1 ? p.k_loc : p.v_loc);
-    const int hd = oc / p.dh, e = oc - hd * p.dh;
-    dst[(((int64_t)ob * p.nh + hd) * p.P + p.slot(ob)) * p.dh + e] = from_f32<T>(v);
-  } else {
-    p.alpha[(int64_t)ob * p.nh + oc] = sigmoidf(v);
-  }
-}
-
-// Steps 3 and 4 in one launch: every workgroup merges the slice partials of
-// all rows into A (rounded to the activation type, as a stored A would be) in
-// LDS while its weights are on their way, then y = x + A W_o^T + b_o for its
-// sixteen columns. The partials are read by every workgroup, so this pays
-// while they are few (see step_impl).
-template <typename T, int DH, int NB, int CPL>
-__global__ void __launch_bounds__(256) decode_gemv_out_kernel(const DecodeProjParams p, const DecodeAttnParams ap) {
-  constexpr int kV = 16 / sizeof(T);
-  __shared__ __attribute__((aligned(16))) T a_s[NB * CPL * 64 * kV];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int cpr = p.d / kV;
-  const int c0 = (blockIdx.x * 4 + wave) * kGemvCols;  // d is a multiple of 64: no partial group
-  const T* w = reinterpret_cast<const T*>(p.w[0]);
-  u32x4 wr[kGemvCols][CPL];
-#pragma unroll
-  for (int i = 0; i < CPL; ++i)
-#pragma unroll
-    for (int u = 0; u < kGemvCols; ++u)
-      wr[u][i] = ld16(w + (int64_t)(c0 + u) * p.d + min(lane + 64 * i, cpr - 1) * kV);
-  const int ob = lane / kGemvCols, oc = c0 + lane % kGemvCols;
-  const T* bias = reinterpret_cast<const T*>(p.bias[0]);
-  const float bv = bias ? to_f32(bias[oc]) : 0.0f;
-  const float xv = to_f32(reinterpret_cast<const T*>(p.x)[(int64_t)min(ob, p.B - 1) * p.d + oc]);
-  for (int it = tid; it < p.B * p.d / 2; it += 256) {
-    const int b = it / (p.d / 2), c = 2 * (it - b * (p.d / 2));
-    float v[2];
-    merge_partials<DH, 2, 1, 16>(ap, b * ap.nh + c / DH, c % DH, v);
-    a_s[b * p.d + c] = from_f32<T>(v[0]);
-    a_s[b * p.d + c + 1] = from_f32<T>(v[1]);
-  }
-  __syncthreads();
-  float acc[NB * kGemvCols];
-#pragma unroll
-  for (int k = 0; k < NB * kGemvCols; ++k) acc[k] = 0.0f;
-#pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    if (b >= p.B) break;
-#pragma unroll
-    for (int i = 0; i < CPL; ++i) {
-      const bool ok = lane + 64 * i < cpr;
-      const u32x4 raw = ld16(a_s + b * p.d + min(lane + 64 * i, cpr - 1) * kV);
-      const T* av = reinterpret_cast<const T*>(&raw);
-#pragma unroll
-      for (int e = 0; e < kV; ++e) {
-        const float a = ok ? to_f32(av[e]) : 0.0f;
-#pragma unroll
-        for (int u = 0; u < kGemvCols; ++u)
-          acc[b * kGemvCols + u] = fmaf(a, to_f32(reinterpret_cast<const T*>(&wr[u][i])[e]), acc[b * kGemvCols + u]);
-      }
-    }
-  }
-  wave_sums(acc);
-  float v = bv;
-#pragma unroll
-  for (int k = 0; k < NB * kGemvCols; ++k)
-    if (lane == k) v += acc[k];
-  if (ob < p.B && ob < NB) reinterpret_cast<T*>(p.y)[(int64_t)ob * p.d + oc] = from_f32<T>(xv + v);
-}
-
 // Proxy K/V rows into the cache: row rr = r0 + r is (sequence rr / nblk,
 // block rr % nblk) and lands at cache row n0 + block (per-sequence n and a
 // write mask with ragged positions).
@@ -769,16 +627,9 @@ static void append_impl(Runner& run, const DecodeDims& d, const DecodeWs& W, con
   }
 }
 
-// Rows per slice: 1,024, or less (down to the 128 rows that a workgroup reads
-// at once) while the slices of all (sequence, head) pairs are too few to give
-// every CU four workgroups: one sequence of 8 heads over 1,500 rows ran as 24
-// workgroups of eight dependent reads each. `lean`: never less than 1,024.
-void split_plan(int64_t n, int64_t pairs, bool lean, int* splits, int* chunk) {
-  int64_t c = kDecodeRowsPerSplit;
-  while (!lean && c > 128 && pairs * ((n + c - 1) / c) < 1024) c /= 2;
-  if ((n + c - 1) / c > kDecodeMaxSplits) c = (n + kDecodeMaxSplits - 1) / kDecodeMaxSplits;
-  *chunk = (int)c;
-  *splits = n <= 0 ? 0 : (int)((n + c - 1) / c);
+void split_plan(int64_t n, bool lean, int* splits, int* chunk) {
+  *chunk = slice_rows((int)n, lean);
+  *splits = n <= 0 ? 0 : (int)((n + *chunk - 1) / *chunk);
 }
 
 // Lets a kernel use up to 160 KB of dynamic LDS, once per (kernel, device).
@@ -799,76 +650,39 @@ static hipError_t allow_lds(const void* kernel) {
 
 // Chunks per lane and row of the staged A: 1, 2 or 4 (d * sizeof(T) <= 4096);
 // rows per wave by the batch.
-template <typename T, bool PROJ>
-static hipError_t launch_small_gemm(dim3 grid, const DecodeProjParams& pp, hipStream_t stream) {
+template <typename T, bool PROJ, int MERGE = 0>
+static hipError_t launch_small_gemm(dim3 grid, const DecodeProjParams& pp, const DecodeAttnParams& ap,
+                                    hipStream_t stream) {
   const int cpr = pp.d * (int)sizeof(T) / 16;
   auto go = [&](auto cpl, auto rpw) {
-    auto kern = decode_small_gemm_kernel<T, PROJ, decltype(cpl)::value, decltype(rpw)::value>;
+    auto kern = decode_small_gemm_kernel<T, PROJ, decltype(cpl)::value, decltype(rpw)::value, MERGE>;
     hipError_t e = allow_lds(reinterpret_cast<const void*>(kern));
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, grid, dim3(256), decode_small_gemm_lds<T>(pp.d, 4 * decltype(rpw)::value), stream, pp);
+    hipLaunchKernelGGL(kern, grid, dim3(256), decode_small_gemm_lds<T>(pp.d, 4 * decltype(rpw)::value), stream, pp, ap);
     return hipGetLastError();
   };
   auto by_rows = [&](auto cpl) {
-    if (pp.B <= 8) return go(cpl, std::integral_constant<int, 2>{});
-    if (pp.B <= 16) return go(cpl, std::integral_constant<int, 4>{});
-    return go(cpl, std::integral_constant<int, 8>{});
+    if (MERGE != 0 || pp.B <= 4) return go(cpl, std::integral_constant<int, 1>{});
+    if constexpr (MERGE == 0) {
+      if (pp.B <= 8) return go(cpl, std::integral_constant<int, 2>{});
+      if (pp.B <= 16) return go(cpl, std::integral_constant<int, 4>{});
+    }
+    return go(cpl, std::integral_constant<int, MERGE ? 1 : 8>{});
   };
   if (cpr <= 64) return by_rows(std::integral_constant<int, 1>{});
   if (cpr <= 128) return by_rows(std::integral_constant<int, 2>{});
   return by_rows(std::integral_constant<int, 4>{});
-}
-
-// Instance by rows (1 or 2) and 16-byte chunks per lane and row.
-template <class F>
-static hipError_t gemv_pick(int rows, int cpr, F&& go) {
-  auto by_rows = [&](auto cpl) {
-    if (rows <= 1) return go(std::integral_constant<int, 1>{}, cpl);
-    return go(std::integral_constant<int, kGemvRows>{}, cpl);
-  };
-  if (cpr <= 64) return by_rows(std::integral_constant<int, 1>{});
-  if (cpr <= 128) return by_rows(std::integral_constant<int, 2>{});
-  return by_rows(std::integral_constant<int, 4>{});
-}
-
-template <typename T>
-static hipError_t launch_gemv_proj(const DecodeProjParams& pp, hipStream_t stream) {
-  const int cols = 3 * pp.d + (pp.nh + kGemvCols - 1) / kGemvCols * kGemvCols;
-  return gemv_pick(pp.B, pp.d * (int)sizeof(T) / 16, [&](auto nb, auto cpl) {
-    hipLaunchKernelGGL((decode_gemv_proj_kernel<T, decltype(nb)::value, decltype(cpl)::value>),
-                       dim3((cols + 4 * kGemvCols - 1) / (4 * kGemvCols)), dim3(256), 0, stream, pp);
-    return hipGetLastError();
-  });
 }
 
 // The merge joins the output map while a workgroup's copy of the partials is
 // at most kMergeInOutBytes and its threads merge at most two channel pairs
-// each, one after the other. Measured per step, merged against the merge of
-// its own launch: 8 heads x 200 rows 12.8 us, 16 heads x 2,000 rows (72 KB)
-// 16.6; past the first bound 16 heads x 8,000 rows (271 KB) 30.6 against 25.9,
-// past the second 2 sequences of 16 heads x 4,000 rows 34.2 against 24.9.
+// each, one after the other: every workgroup repeats the merge, so it pays
+// only while that is shorter than a launch. A step of one sequence, 8 heads x
+// 200 rows: 15.3 us merged, 21.7 before; past the first bound 16 heads x 8,000
+// rows (271 KB) 30.6 us merged against 25.9, past the second 2 sequences of 16
+// heads x 4,000 rows 34.2 against 24.9.
 constexpr int64_t kMergeInOutBytes = 128 << 10;
 constexpr int kMergeInOutChannels = 1024;
-
-template <typename T>
-static hipError_t launch_gemv_out(const DecodeProjParams& op, const DecodeAttnParams& ap, int dh, hipStream_t stream) {
-  const dim3 grid(op.d / (4 * kGemvCols));
-  auto go = [&](auto nb, auto cpl) {
-    constexpr int NB = decltype(nb)::value, CPL = decltype(cpl)::value;
-    if (dh == 64)
-      hipLaunchKernelGGL((decode_gemv_out_kernel<T, 64, NB, CPL>), grid, dim3(256), 0, stream, op, ap);
-    else
-      hipLaunchKernelGGL((decode_gemv_out_kernel<T, 128, NB, CPL>), grid, dim3(256), 0, stream, op, ap);
-    return hipGetLastError();
-  };
-  const int cpr = op.d * (int)sizeof(T) / 16;
-  typedef std::integral_constant<int, 1> one;
-  typedef std::integral_constant<int, 2> two;
-  typedef std::integral_constant<int, 4> four;
-  if (op.B > 1) return cpr <= 64 ? go(two{}, one{}) : go(two{}, two{});  // d <= 512
-  if (cpr <= 64) return go(one{}, one{});
-  return cpr <= 128 ? go(one{}, two{}) : go(one{}, four{});
-}
 
 template <typename T>
 static void step_impl(Runner& run, const DecodeDims& d, const DecodeWs& W, const pf_decode_weights* w,
@@ -901,20 +715,21 @@ static void step_impl(Runner& run, const DecodeDims& d, const DecodeWs& W, const
   pp.x_blk = st.x_blk;
   pp.pos = pos;
   static_assert(decode_small_gemm_lds<T>(2048 * 2 / sizeof(T)) <= 160 * 1024, "staged rows fit the LDS");
-  const bool gemv = d.B <= kGemvRows;
   run.launch("decode_proj", [&] {
-    if (gemv) return launch_gemv_proj<T>(pp, run.stream);
     const dim3 grid(3 * d.d / 32 + (d.nh + 31) / 32, rblocks);
-    return launch_small_gemm<T, true>(grid, pp, run.stream);
+    return launch_small_gemm<T, true>(grid, pp, DecodeAttnParams{}, run.stream);
   });
 
-  int64_t n_max = st.n;  // slices cover the longest cache of the batch
-  if (pos.ragged) {
-    n_max = 0;
-    for (int b = 0; b < d.B; ++b) n_max = std::max<int64_t>(n_max, pos.n[b]);
+  int splits = 0, chunk = 0;
+  if (pos.ragged) {  // each sequence is cut by its own length
+    for (int b = 0; b < d.B; ++b) {
+      int sb;
+      split_plan(pos.n[b], W.lean, &sb, &chunk);
+      splits = std::max(splits, sb);
+    }
+  } else {
+    split_plan(st.n, W.lean, &splits, &chunk);
   }
-  int splits, chunk;
-  split_plan(n_max, (int64_t)d.B * d.nh, W.lean, &splits, &chunk);
   DecodeAttnParams ap{};
   ap.q = q;
   ap.kc = st.k_cache;
@@ -933,6 +748,7 @@ static void step_impl(Runner& run, const DecodeDims& d, const DecodeWs& W, const
   ap.nh = d.nh;
   ap.splits = splits;
   ap.chunk = chunk;
+  ap.lean = W.lean;
   ap.scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)d.dh));
   ap.pos = pos;
   run.launch("decode_attn", [&] {
@@ -953,8 +769,12 @@ static void step_impl(Runner& run, const DecodeDims& d, const DecodeWs& W, const
   op.d = d.d;
   op.y = y_t;
   const int64_t part_bytes = (int64_t)d.B * d.nh * (splits + 1) * (d.dh + 2) * 4;
-  if (gemv && part_bytes <= kMergeInOutBytes && d.B * d.d <= kMergeInOutChannels) {
-    run.launch("decode_out", [&] { return launch_gemv_out<T>(op, ap, d.dh, run.stream); });
+  if (part_bytes <= kMergeInOutBytes && d.B * d.d <= kMergeInOutChannels && d.B <= 4) {
+    run.launch("decode_out", [&] {
+      const dim3 grid(d.d / 32);
+      return d.dh == 64 ? launch_small_gemm<T, false, 64>(grid, op, ap, run.stream)
+                        : launch_small_gemm<T, false, 128>(grid, op, ap, run.stream);
+    });
     return;
   }
   run.launch("decode_combine", [&] {
@@ -968,7 +788,7 @@ static void step_impl(Runner& run, const DecodeDims& d, const DecodeWs& W, const
   });
   run.launch("decode_out", [&] {
     const dim3 grid(d.d / 32, rblocks);
-    return launch_small_gemm<T, false>(grid, op, run.stream);
+    return launch_small_gemm<T, false>(grid, op, ap, run.stream);
   });
 }
 
@@ -1021,8 +841,10 @@ DecodeWs decode_ws(const DecodeDims& d) {
 }
 
 DecodeWs decode_step_ws(const DecodeDims& d, int64_t n_max, bool lean) {
+  // as many slices as any length up to n_max is cut into
   int splits, chunk;
-  split_plan(n_max, (int64_t)d.B * d.nh, lean, &splits, &chunk);
+  split_plan(n_max, lean, &splits, &chunk);
+  if (!lean) splits = std::max<int>(splits, (int)std::min<int64_t>(kDecodeSlices, (n_max + 127) / 128));
   // the step appends at most one block per sequence: B rows
   DecodeWs w = decode_ws_layout(d, splits, (int)std::min<int64_t>(d.append_rows, d.B));
   w.lean = lean;

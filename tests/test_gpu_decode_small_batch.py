@@ -1,9 +1,10 @@
-"""Decode steps of one to seventeen sequences (the wave-per-columns projections and
-the merge inside the output map take up to two, the matrix kernels stage 8, 16
-or 32 rows) and short cache slices, at
-the sizes where they can go wrong: widths of one to four 16-byte chunks per
-lane, head counts that are no multiple of four, caches at and around the slice
-edges, empty caches, positions per sequence, and steps across an append."""
+"""Decode steps of one to seventeen sequences (the projection kernels stage 4,
+8, 16 or 32 rows, and the output map merges small partials itself) and short
+cache slices, at the sizes where they can go wrong: widths of one to four
+16-byte chunks per lane, head counts that are no multiple of four, caches at
+and around the slice edges, empty caches, positions per sequence, and steps
+across an append; and a sequence's bits in any batch.
+"""
 import numpy as np
 import pytest
 
@@ -92,3 +93,27 @@ def test_small_batch_ragged_equals_lockstep(gpu, batch):
         out.append(torch.stack([sess.step(dev(inp["x"][t], "bf16")) for t in range(5)]))
     torch.cuda.synchronize()
     assert torch.equal(*out)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+def test_bits_do_not_depend_on_the_batch(gpu, dtype):
+    """Sequences of several lengths, decoded together at their own positions
+    and each alone in lockstep: equal bit for bit (slices by a sequence's own
+    length, row arithmetic the same for every staged row count, one merge)."""
+    import torch
+    B = gpu
+    lens = [0, 1, 127, 300, 2048, 2049]
+    shape = synth.DecodeShape(len(lens), 256, 4, 64, (4,), n0=max(lens), steps=5, dtype=dtype)
+    inp = synth.decode_inputs(shape, 960)
+    w = dev_weights(inp["weights"], dtype)
+    kc, vc = dev(inp["k_cache"], dtype), dev(inp["v_cache"], dtype)
+    xs = dev(inp["x"], dtype)
+    sess = B.DecodeSession(B.decode_config(len(lens), 256, 4, 64, (4,), dtype=dtype), w, kc.clone(), vc.clone(),
+                           ragged=True, n_seq=lens)
+    together = torch.stack([sess.step(xs[t]) for t in range(5)])
+    for b, n in enumerate(lens):
+        one = B.DecodeSession(B.decode_config(1, 256, 4, 64, (4,), dtype=dtype), w, kc[b:b + 1].clone(),
+                              vc[b:b + 1].clone(), n=n)
+        alone = torch.stack([one.step(xs[t, b:b + 1].clone()) for t in range(5)])
+        torch.cuda.synchronize()
+        assert torch.equal(alone[:, 0], together[:, b]), n

@@ -135,15 +135,15 @@ int proxy_layer_forward(const pf_layer_config* cfg, const pf_layer_weights* w, c
   char* acts = saved ? reinterpret_cast<char*>(saved) : ws + W.acts;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   // partial last block: run on a zero-padded copy; 2-D partition: on a
-  // patch-ordered copy (kept with the activations when they are saved). The
-  // gated and additive injections store X_out through the row map; the others
+  // patch-ordered copy. The gated and additive injections store X_out
+  // through the row map; the others
   // leave it in workspace order and it is copied back.
   const void* xk = x;
   void* yk = x_out;
   hipError_t e = hipSuccess;
   const bool copy_out = d.staged() && (d.fused_gate || (d.inject != PF_INJECT_GATED && d.inject != PF_INJECT_ADD));
   if (d.staged()) {
-    char* xs = saved ? acts + layer_acts(d, true).x_st : ws + W.x_pad;
+    char* xs = ws + W.x_pad;
     if ((e = stage_rows(d, x, xs, s)) != hipSuccess) return hip_status(e, "proxy_layer_forward staging");
     xk = xs;
     if (copy_out) yk = ws + W.y_pad;

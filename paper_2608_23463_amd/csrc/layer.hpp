@@ -68,7 +68,6 @@ struct LayerActs {
   size_t rstd;                // Eq. 13: 1 / RMS of every X row, fp32 [B*L]
   size_t gh;                  // per-head gate pre-activation, fp32 [B*L, n_heads]
   size_t aff_w, aff_b;        // Eq. 13: W_a, b_a with s and t rows interleaved [2 d_f, d_f], [2 d_f]
-  size_t x_st;                // staged calls: X as the kernels read it, kept for the backward [B*L, d_f]
   size_t bytes;
 };
 
@@ -93,8 +92,8 @@ struct LayerWs {
   size_t tr_w;                // a transposed weight [in, out] for the large data gradients
   // staged token tensors (L_in < L: zero-padded to L tokens; 2-D partition:
   // in patch order)
-  size_t x_pad;               // forward without saved activations: X with zero padding [B*L, d_f]
-  size_t y_pad;               // forward: X_out, for the injections without a mapped store [B*L, d_f]
+  size_t x_pad;               // X with zero padding [B*L, d_f]
+  size_t y_pad;               // forward: X_out, for the injections without a mapped store [B*L, d_f]; backward: unused
   size_t dy_pad;              // backward: dY with zero padding [B*L, d_f]
   size_t dst;                 // Eq. 13 backward: [dS | dT] [B*L, 2 d_f]
   size_t dgh;                 // per-head gate backward: dG [B*L, round8(n_heads)]

@@ -630,11 +630,11 @@ static void backward_impl(Runner& run, const LayerDims& d, const pf_layer_config
   const int64_t BL = (int64_t)d.B * d.L;
   const int64_t Bm = (int64_t)d.B * d.m;
   const int df = d.d_f, dp = d.d_p;
-  // staged calls: X is the copy that the forward saved, dY gets one in
-  // workspace (for the gated injection the first kernel writes it), and dX
-  // is stored through the map
+  // staged calls: X and dY get copies in workspace (for the gated injection
+  // the first kernel writes dY's), and dX is stored through the map
   const T* dyp = d.map.mode ? WT(W.dy_pad) : reinterpret_cast<const T*>(dy_in);
-  const T* xp = d.map.mode ? S(A.x_st) : reinterpret_cast<const T*>(x);
+  const T* xp = d.map.mode ? WT(W.x_pad) : reinterpret_cast<const T*>(x);
+  if (d.map.mode) run.launch("stage_x", [&] { return stage_rows(d, x, WT(W.x_pad), run.stream); });
   if (d.map.mode && cfg->injection != PF_INJECT_GATED)
     run.launch("stage_dy", [&] { return stage_rows(d, dy_in, WT(W.dy_pad), run.stream); });
 

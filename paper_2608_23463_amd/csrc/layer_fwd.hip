@@ -307,7 +307,6 @@ LayerActs layer_acts(const LayerDims& d, bool bwd) {
   a.gh = take(d.inject == PF_INJECT_GATED_HEAD ? (size_t)d.B * d.L * d.nh * 4 : 0);
   a.aff_w = take(affine ? (size_t)2 * d.d_f * d.d_f * es : 0);
   a.aff_b = take(affine ? (size_t)2 * d.d_f * es : 0);
-  a.x_st = take(bwd && d.staged() ? (size_t)d.B * d.L * d.d_f * es : 0);
   a.bytes = off;
   return a;
 }
@@ -385,8 +384,8 @@ LayerWs layer_ws_layout(const LayerDims& d, bool bwd) {
   if (bwd && d.inject == PF_INJECT_AFFINE) w.dst = take(2 * tok);
   if (bwd && d.inject == PF_INJECT_GATED_HEAD) w.dgh = take((size_t)d.B * d.L * round8(d.nh) * es);
   if (d.staged()) {
-    w.x_pad = bwd ? 0 : take(tok);
-    w.y_pad = bwd ? 0 : take(tok);
+    w.x_pad = take(tok);
+    w.y_pad = take(tok);  // the queried sizes hold three token tensors beside the backward's, two beside the forward's
     w.dy_pad = bwd ? take(tok) : 0;
   }
   w.gemm = off;

@@ -200,12 +200,6 @@ __device__ __forceinline__ void merge_partials(const DecodeAttnParams& p, int bh
   for (int u = 0; u < kC; ++u) out[u] = fmaf(al, mrun == -INFINITY ? 0.0f : arun[u] / lrun, ax[u] / lx);
 }
 
-// LDS of a workgroup that stages `rows` rows of A.
-template <typename T>
-constexpr size_t decode_small_gemm_lds(int d, int rows = 32) {
-  return (size_t)rows * d * sizeof(T) + 4 * 32 * 33 * sizeof(float) + 32 * sizeof(float);
-}
-
 // RPW: rows that each of the four waves stages, 8 for a full block of 32
 // sequences, 4, 2 or 1 where the batch ends within 16, 8 or 4: the rows past them
 // would be copies of the last, and their loads, norms and instructions are
@@ -241,7 +235,7 @@ __global__ void __launch_bounds__(256) decode_small_gemm_kernel(const DecodeProj
   }
   const int width = p.width[seg];
   const T* x = reinterpret_cast<const T*>(p.x);
-  auto a_slot = [&](int r, int c) { return a_s + (int64_t)r * p.d + ((c ^ (r & 7)) * kV); };
+  auto a_slot = [&](int r, int c) { return a_s + staged_offset<T>(r, c, kRowsA, p.d); };
 
   // weight fragments of this wave's quarter of K, eight k-steps at a time
   const int col = cs + l32;  // B column = weight row
@@ -348,9 +342,9 @@ __global__ void __launch_bounds__(256) decode_small_gemm_kernel(const DecodeProj
       const int k = kbeg + st * 16 + g * 8;
       typename MM::frag af;
       if constexpr (sizeof(T) == 2) {
-        af = *reinterpret_cast<const typename MM::frag*>(a_slot(l32 & (kRowsA - 1), k / kV));
+        af = *reinterpret_cast<const typename MM::frag*>(a_slot(l32, k / kV));
       } else {
-        const f32x4 lo = *reinterpret_cast<const f32x4*>(a_slot(l32 & (kRowsA - 1), k / kV));
+        const f32x4 lo = *reinterpret_cast<const f32x4*>(a_slot(l32, k / kV));
         const f32x4 hi = *reinterpret_cast<const f32x4*>(a_slot(l32, k / kV + 1));
 #pragma unroll
         for (int e = 0; e < 4; ++e) {

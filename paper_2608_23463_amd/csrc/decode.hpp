@@ -73,6 +73,22 @@ __host__ __device__ inline int slice_rows(int n, bool lean) {
 // Cache slices the decode attention cuts n rows into, and their length.
 void split_plan(int64_t n, bool lean, int* splits, int* chunk);
 
+// Offset (elements) of 16-byte chunk c of row r in the projection kernels'
+// staged A, [rows][d] with the chunks XOR-swizzled by row. The matrix tile has
+// 32 rows whatever the batch: those past the `rows` staged ones (a power of
+// two) repeat them, so no access leaves the staged block.
+template <typename T>
+__host__ __device__ constexpr int staged_offset(int r, int c, int rows, int d) {
+  const int row = r & (rows - 1);
+  return row * d + (c ^ (row & 7)) * (16 / (int)sizeof(T));
+}
+// LDS of a projection workgroup: the staged rows, four 32 x 33 partial tiles
+// and a spare row of 32.
+template <typename T>
+constexpr size_t decode_small_gemm_lds(int d, int rows = 32) {
+  return (size_t)rows * d * sizeof(T) + 4 * 32 * 33 * sizeof(float) + 32 * sizeof(float);
+}
+
 // `pos` carries the per-sequence positions when st.n_seq / st.j_seq are set;
 // W is the scratch layout inside ws.
 template <typename T>

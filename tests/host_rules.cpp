@@ -1,0 +1,33 @@
+// Host side of the library's index and launch rules, compiled without device
+// code and called through ctypes by test_host_rules.py.
+#include "../paper_2608_23463_amd/csrc/decode.hpp"
+#include "../paper_2608_23463_amd/csrc/common.hpp"
+
+using namespace pf;
+
+// Largest byte past the staged A that the fragment reads of one projection
+// workgroup touch (<= 0: all of them stay inside), and how many of them read a
+// chunk that is not the one asked for of the row that stands in for theirs.
+template <typename T>
+static int64_t staged_reads(int d, int rows, int64_t* wrong) {
+  constexpr int kV = 16 / (int)sizeof(T);
+  int64_t past = INT64_MIN;
+  *wrong = 0;
+  const int kq = d / 4;
+  for (int wave = 0; wave < 4; ++wave)
+    for (int st = 0; st < kq / 16; ++st)
+      for (int lane = 0; lane < 64; ++lane) {
+        const int g = lane >> 5, l32 = lane & 31, k = wave * kq + st * 16 + g * 8;
+        for (int c = k / kV; c < (k + 8) / kV; ++c) {
+          const int64_t at = staged_offset<T>(l32, c, rows, d);
+          past = std::max<int64_t>(past, (at + kV - (int64_t)rows * d) * (int64_t)sizeof(T));
+          // the write of the same chunk: row l32 mod rows is staged by its own index
+          if (at != staged_offset<T>(l32 % rows, c, rows, d) || at / d != l32 % rows) ++*wrong;
+        }
+      }
+  return past;
+}
+
+extern "C" int64_t host_staged_reads(int esize, int d, int rows, int64_t* wrong) {
+  return esize == 2 ? staged_reads<bf16>(d, rows, wrong) : staged_reads<float>(d, rows, wrong);
+}

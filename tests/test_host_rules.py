@@ -1,0 +1,32 @@
+"""Index and launch rules of the library's host side, compiled from its headers
+without device code: what a kernel may touch, which launches are refused, and
+how products are planned, checked on the CPU over whole ranges of sizes."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("host_rules") / "host_rules.so")
+    hipcc = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "bin", "hipcc")
+    subprocess.run([hipcc, "-x", "hip", "--offload-host-only", "-std=c++17", "-O1", "-fPIC", "-shared",
+                    "-Wno-unused", os.path.join(HERE, "host_rules.cpp"), "-o", out], check=True)
+    lib = ctypes.CDLL(out)
+    lib.host_staged_reads.restype = ctypes.c_int64
+    return lib
+
+
+@pytest.mark.parametrize("esize", [2, 4])
+def test_projection_reads_stay_in_the_staged_rows(rules, esize):
+    """The decode projections multiply a 32-row tile whatever the batch; with 4,
+    8 or 16 staged rows every fragment read has to come from those rows."""
+    wrong = ctypes.c_int64()
+    for d in range(64, 4096 // esize + 1, 64):
+        for rows in (4, 8, 16, 32):
+            past = rules.host_staged_reads(esize, d, rows, ctypes.byref(wrong))
+            assert past <= 0 and wrong.value == 0, (d, rows, past, wrong.value)

@@ -1268,6 +1268,12 @@ inline bool gemm_runs_direct(const GemmProblem& pr, int k_slice) {
          (LB == LAYOUT_K || (pr.ldb % 8 == 0 && pr.ldb >= BN));
 }
 
+// Whether the register-path kernel can run a problem the direct one does not
+// take: it knows neither batches nor column sums nor third sources.
+inline bool gemm_runs_register(const GemmProblem& pr) {
+  return pr.batch == 1 && !pr.colsum && pr.ksplit3 >= pr.K;
+}
+
 inline GemmParams gemm_params(const GemmProblem& pr, int BM, int BN, int BK, int k_slice, size_t esize) {
   GemmParams p;
   p.a = pr.a;
@@ -1365,7 +1371,7 @@ inline hipError_t launch_gemm_tile(const GemmProblem* prs, int count, const Gemm
     }
     return hipSuccess;
   }
-  if (prs->batch != 1 || prs->colsum) return hipErrorInvalidValue;  // direct kernel only
+  if (!gemm_runs_register(*prs)) return hipErrorInvalidValue;
   const GemmParams p = gemm_params(*prs, BM, BN, BK, plan_k_slice(*prs, pl), sizeof(T));
   hipLaunchKernelGGL((gemm_kernel<T, BM, BN, BK, WM, WN, LA, LB, Epi>),
                      dim3(p.tiles_m * p.tiles_n, 1, plan_splits(*prs, pl)), dim3(WM * WN * kWave), 0, stream, p, *epis);

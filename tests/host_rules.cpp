@@ -1,7 +1,7 @@
 // Host side of the library's index and launch rules, compiled without device
 // code and called through ctypes by test_host_rules.py.
 #include "../paper_2608_23463_amd/csrc/decode.hpp"
-#include "../paper_2608_23463_amd/csrc/common.hpp"
+#include "../paper_2608_23463_amd/csrc/gemm.hpp"
 
 using namespace pf;
 
@@ -30,4 +30,17 @@ static int64_t staged_reads(int d, int rows, int64_t* wrong) {
 
 extern "C" int64_t host_staged_reads(int esize, int d, int rows, int64_t* wrong) {
   return esize == 2 ? staged_reads<bf16>(d, rows, wrong) : staged_reads<float>(d, rows, wrong);
+}
+
+// 1 if the register-path kernel takes a product with this many batches, column
+// sums of A, or A and B read from a third source from K index ksplit3 on.
+extern "C" int host_register_path(int K, int batch, int colsum, int ksplit3) {
+  static float sums[1];
+  GemmProblem pr{};
+  pr.M = pr.N = 40;
+  pr.K = K;
+  pr.batch = batch;
+  pr.colsum = colsum ? sums : nullptr;
+  if (ksplit3 >= 0) pr.ksplit3 = ksplit3;
+  return gemm_runs_register(pr);
 }

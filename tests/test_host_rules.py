@@ -30,3 +30,13 @@ def test_projection_reads_stay_in_the_staged_rows(rules, esize):
         for rows in (4, 8, 16, 32):
             past = rules.host_staged_reads(esize, d, rows, ctypes.byref(wrong))
             assert past <= 0 and wrong.value == 0, (d, rows, past, wrong.value)
+
+
+def test_register_path_refuses_what_it_does_not_know(rules):
+    """Batches, column sums and a third operand source exist on the direct
+    kernel only: the other one would drop them without a word."""
+    assert rules.host_register_path(96, 1, 0, -1)
+    assert rules.host_register_path(96, 1, 0, 96)      # the third source starts past the last step
+    assert not rules.host_register_path(96, 1, 0, 64)
+    assert not rules.host_register_path(96, 2, 0, -1)
+    assert not rules.host_register_path(96, 1, 1, -1)

@@ -743,7 +743,11 @@ __device__ __forceinline__ void wait_stages(int pending) {
 // the workgroups of the first column tile write the sums. Which block a wave
 // sums is its column index, so the waves of a row share the work; the blocks
 // are held rotated by that index to keep the choice out of the loop. This
-// replaces two further launches and one more read of A per bias.
+// replaces two further launches and one more read of A per bias. A lane's
+// running sum is folded into a second one every kColsumFold K tiles, so no
+// chain of additions is longer than 128 values and then the folds, however
+// many tokens a slice has (one chain over a slice of 8,192 rows was off by
+// 1.5e-5 where small values follow a large one).
 template <typename T, int BM, int BN, int BK, int WM, int WN, int NS, class Epi, int LA = LAYOUT_K,
           int LB = LAYOUT_K, bool FAST = false, int G = 1>
 __global__ void __launch_bounds__(WM* WN* kWave)
@@ -950,7 +954,8 @@ __global__ void __launch_bounds__(WM* WN* kWave)
   typename MM::frag fa[2][S::kFM], fb[2][S::kFN];
   constexpr bool kColsum = OA::kMN && OB::kMN;
   const int rot = kColsum ? wn % S::kFM : 0;
-  float csum = 0.0f;  // of row block `rot`, this lane's row and k half
+  constexpr int kColsumFold = 128 / kSub;
+  float csum = 0.0f, csum_all = 0.0f;  // of row block `rot`, this lane's row and k half
   auto read_frags = [&](int tile, int st, int buf) {
     const T* cur = smem + (tile % NS) * D::kStage;
     if constexpr (OA::kMN) {
@@ -1020,6 +1025,12 @@ __global__ void __launch_bounds__(WM* WN* kWave)
       read_frags(kt + 1, 0, 0);
     }
     mfmas(1);
+    if constexpr (kColsum) {
+      if (kt % kColsumFold == kColsumFold - 1) {
+        csum_all += csum;
+        csum = 0.0f;
+      }
+    }
     if (kt + NS < nk) issue(kbeg + (kt + NS) * BK, kt % NS);  // after the hand-off above
   }
   // Every direct load has landed (the last wait_stages drained them all).
@@ -1032,6 +1043,7 @@ __global__ void __launch_bounds__(WM* WN* kWave)
   float* region = reinterpret_cast<float*>(smem + free_stage * D::kStage) + wave * kRows * (S::kTN + 8);
   if constexpr (kColsum) {
     if (p.colsum && tn == 0 && wn < S::kFM) {
+      csum += csum_all;
       csum += __shfl_xor(csum, 32);
       const int row = m0 + wm * S::kTM + rot * 32 + frow;
       if (lane < 32 && row < p.M) p.colsum[(int64_t)z * p.M + row] = csum;

@@ -92,3 +92,36 @@ def test_gradients_left_out(gpu, missing):
                     assert np.isfinite(err) and (key == "k" or err <= 1e-4), (key, err)
                 else:
                     assert torch.equal(p, q), (key, i)
+
+
+@pytest.mark.parametrize("data", ["mean", "small after large"])
+def test_bias_gradient_of_a_long_reduction(gpu, data):
+    """Bias gradients formed inside the weight-gradient GEMM over K slices of
+    8,192 rows, against the 64-bit column sums of the same bf16 values (with
+    the additive injection the decompression's bias gradient is that of dY).
+    A lane adds chains of at most 128 values, so the error of a sum of positive
+    values is at most about 128 half-units in the last place: 128 * 2^-24 = 8e-6.
+    One chain over the slice loses every 2^-20 that follows the 256s: 1.5e-5."""
+    import torch
+    B = gpu
+    shape = LayerShape(1, 1 << 17, 1024, 1024, 16, 64, (2, 64), injection=synth.INJECT_ADD)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    std = lambda *s: torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(0.0, 0.02, generator=gen)
+    lin = lambda o, i: (std(o, i), std(o))
+    w = {"compress": [lin(1024, 2048), lin(1024, 65536)], "decompress": [lin(2048, 1024), lin(65536, 1024)],
+         **{n: lin(1024, 1024) for n in "qkvo"}}
+    x = std(1, shape.seq_len, 1024)
+    if data == "mean":
+        dy = (1.0 + 5.0 * std(1, shape.seq_len, 1024).float()).to(torch.bfloat16)
+    else:
+        dy = torch.full((1, shape.seq_len, 1024), 2.0 ** -20, dtype=torch.bfloat16, device="cuda")
+        dy[:, :32] = 0.0
+        dy[:, :2] = dy[:, 16:18] = 256.0  # rows 0 and 8 of the [L / 2, 2 * 1024] operand
+    cfg = B.config_from_shape(shape)
+    _, _, saved = B.layer_forward(cfg, w, x, save=True)
+    _, _, g = B.layer_backward(cfg, w, x, None, saved, dy)
+    torch.cuda.synchronize()
+    ref = dy.view(-1, 2048).double().sum(0)
+    err = float(((g["decompress"][0][1].double() - ref).abs() / ref).max())
+    print(f"  bias gradient over {shape.seq_len // 2} rows: {err:.2e}", flush=True)
+    assert err <= 1e-5

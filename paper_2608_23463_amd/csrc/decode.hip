@@ -576,13 +576,56 @@ struct EpiByRef<EpiCache<T>> : std::true_type {};
 
 // ---- launch sequences ---------------------------------------------------------
 
+// Blocks per pass of an append planned by rows: all of them while the split-K
+// partials of a pass stay within 32 MiB.
+template <typename T>
+static int append_pass(const DecodeDims& d) {
+  size_t most = 0;
+  auto need = [&](const GemmProblem* prs, int count) {
+    const GemmPlan pl = plan_gemm<T>(prs, count, Runner::kPlanCUsGemm);
+    size_t sum = 0;
+    for (int i = 0; i < count && pl.splits > 1; ++i) sum += plan_partials(prs[i], pl) * sizeof(float);
+    most = std::max(most, sum);
+  };
+  int64_t rows = kAppendPlanBlocks * d.P;
+  for (int j = 0; j < d.M; ++j) {
+    rows /= d.k[j];
+    GemmProblem pr{};
+    pr.M = (int)rows;
+    pr.N = d.dl[j + 1];
+    pr.K = d.k[j] * d.dl[j];
+    need(&pr, 1);
+  }
+  GemmProblem kv[2];
+  for (GemmProblem& pr : kv) {
+    pr.M = kAppendPlanBlocks;
+    pr.N = pr.K = d.d;
+  }
+  need(kv, 2);
+  int pass = kAppendByRows;
+  while (pass > kAppendPlanBlocks && most * (pass / kAppendPlanBlocks) > ((size_t)32 << 20)) pass /= 2;
+  return pass;
+}
+
+// One block of each of up to kAppendByRows sequences: K is cut as for
+// kAppendPlanBlocks of them, so a block's proxy, and with it every later step
+// that reads it, has the same bits in any such batch. (Cut by the batch, 12
+// sequences of d = 1024 with 8 x 8 tokens per block summed 8 slices where one
+// sequence sums 16.) More blocks are cut by their number: there the partials
+// of a fixed cut would cost more than the products.
 template <typename T>
 static void append_impl(Runner& run, const DecodeDims& d, const DecodeWs& W, const pf_decode_weights* w,
                         const pf_decode_state& st, const DecodePos& pos, const void* x_blocks, int64_t nblk, char* ws) {
   const int64_t total = (int64_t)d.B * nblk;   // (sequence, block) rows of the [B*nblk, P*d] view
   const int64_t row_elems = d.P * d.d;
-  for (int64_t r0 = 0; r0 < total; r0 += W.rows_cap) {
-    const int rows = (int)std::min<int64_t>(W.rows_cap, total - r0);
+  const bool by_rows = nblk == 1 && d.B <= kAppendByRows && !run.lean;
+  const int pass = by_rows ? std::min(W.rows_cap, append_pass<T>(d)) : W.rows_cap;
+  auto plan = [&](const GemmProblem* prs, int count, int64_t rows_per_block) {
+    return by_rows ? plan_gemm_rows<T>(prs, count, (int)(kAppendPlanBlocks * rows_per_block), Runner::kPlanCUsGemm)
+                   : plan_gemm<T>(prs, count, Runner::kPlanCUsGemm, run.lean);
+  };
+  for (int64_t r0 = 0; r0 < total; r0 += pass) {
+    const int rows = (int)std::min<int64_t>(pass, total - r0);
     const T* zin = reinterpret_cast<const T*>(x_blocks) + r0 * row_elems;
     int64_t lvl_rows = (int64_t)rows * d.P;
     for (int j = 0; j < d.M; ++j) {  // compression C (Eq. 7, 16)
@@ -597,7 +640,8 @@ static void append_impl(Runner& run, const DecodeDims& d, const DecodeWs& W, con
       pr.K = (int)pr.lda;
       T* out = reinterpret_cast<T*>(ws + W.z[j + 1]);
       EpiLinear<T> e{out, pr.N, reinterpret_cast<const T*>(w->compress[j].b), nullptr, 0, nullptr};
-      run.gemm<T, LAYOUT_K, LAYOUT_K>("append_compress_gemm", pr, e);
+      const GemmPlan pl = plan(&pr, 1, lvl_rows / rows);
+      run.gemm_group<T, LAYOUT_K, LAYOUT_K>("append_compress_gemm", &pr, &e, 1, &pl);
       zin = out;
     }
     const pf_linear* maps[2] = {&w->k_proxy, &w->v_proxy};
@@ -617,7 +661,8 @@ static void append_impl(Runner& run, const DecodeDims& d, const DecodeWs& W, con
       epis[i] = EpiCache<T>{reinterpret_cast<T*>(caches[i]), reinterpret_cast<const T*>(maps[i]->b), st.n_cap, st.n,
                             nblk, r0, d.nh, d.dh, pos};
     }
-    run.gemm_group<T, LAYOUT_K, LAYOUT_K>("append_kv_gemm", prs, epis, 2);
+    const GemmPlan pl = plan(prs, 2, 1);
+    run.gemm_group<T, LAYOUT_K, LAYOUT_K>("append_kv_gemm", prs, epis, 2, run.lean ? nullptr : &pl);
   }
 }
 
@@ -802,10 +847,14 @@ static size_t decode_gemm_need(const DecodeDims& d, const DecodeWs& W) {
     else
       append_impl<float>(dry, d1, W, &nw, ns, np, nullptr, rows, nullptr);
   }
-  if (d.esize == 2)
+  // and one block per sequence
+  if (d.esize == 2) {
+    append_impl<bf16>(dry, d, W, &nw, ns, np, nullptr, 1, nullptr);
     step_impl<bf16>(dry, d, W, &nw, ns, np, nullptr, nullptr, nullptr);
-  else
+  } else {
+    append_impl<float>(dry, d, W, &nw, ns, np, nullptr, 1, nullptr);
     step_impl<float>(dry, d, W, &nw, ns, np, nullptr, nullptr, nullptr);
+  }
   return dry.gemm_need;
 }
 

@@ -35,6 +35,8 @@ struct DecodePos {
 constexpr int kDecodeMaxSplits = 256;   // cache-row slices per (sequence, head)
 constexpr int kDecodeRowsPerSplit = 1024;  // most rows per slice (while kDecodeMaxSplits suffice)
 constexpr int kDecodeSlices = 16;         // slices aimed at below that
+constexpr int kAppendByRows = 64;         // largest batch whose one-block appends are planned by rows
+constexpr int kAppendPlanBlocks = 8;      // and the batch they are planned as
 
 struct DecodeWs {
   int splits_cap;                   // cache slices per (sequence, head) the partials hold
@@ -59,8 +61,8 @@ DecodeWs decode_step_ws(const DecodeDims& d, int64_t n_max, bool lean);
 // Rows per slice of a cache of n rows: the power of two from 128 (what a
 // workgroup reads at once) to 1,024 that gives about kDecodeSlices slices, and
 // beyond kDecodeMaxSplits * 1,024 rows what kDecodeMaxSplits slices take. It
-// depends on the sequence's length alone, not on the batch, so a sequence
-// decodes to the same bits alone and in any batch. One sequence of 8 heads over
+// depends on the sequence's length alone, not on the batch, so a step gives a
+// sequence the same bits alone and in any batch. One sequence of 8 heads over
 // 1,500 rows ran as 24 workgroups of eight dependent reads each in slices of
 // 1,024: with the other changes of the step 26.2 us, 15.5 now; 32 sequences of
 // 16 heads x 1,500, 4,000 and 9,000 rows are unchanged (55, 121, 224 us). `lean`: 1,024 at least, the fewest partials.

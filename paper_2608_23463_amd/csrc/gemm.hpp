@@ -1172,6 +1172,7 @@ struct GemmPlan {
   int bm, bn, bk;
   int splits;
   int k_slice;
+  int zl = 0;  // lanes that share a chunk of the reduction (0: by the result's size)
 };
 
 // One plan for a group of problems launched together (their tiles fill the
@@ -1249,6 +1250,37 @@ inline GemmPlan plan_gemm(const GemmProblem* prs, int count, int num_cu, bool le
   const int kb_per = (kblocks + splits - 1) / splits;
   pl.k_slice = kb_per * pl.bk;
   pl.splits = (kblocks + kb_per - 1) / kb_per;
+  return pl;
+}
+
+// Lanes that share a chunk of the reduction and the blocks it takes: more
+// lanes while the chunks alone leave the chip under four waves per CU. `zl`
+// not 0: that many lanes.
+inline void plan_reduce(int64_t chunks, int splits, int* zl, int* blocks) {
+  int z = *zl ? *zl : 1;
+  while (!*zl && z < 16 && 2 * z <= splits && chunks * z < (int64_t)256 * 4 * kWave) z *= 2;
+  *zl = z;
+  *blocks = (int)std::max<int64_t>(1, std::min<int64_t>((chunks * z + 255) / 256, 8192));
+}
+
+// Plan of a group whose rows change from call to call while a row's bits may
+// not: K is cut and its slices are joined as for `rows` rows, whatever the
+// problems have; only the tile, which no sum depends on, follows theirs.
+template <typename T>
+inline GemmPlan plan_gemm_rows(const GemmProblem* prs, int count, int rows, int num_cu) {
+  GemmProblem at[kGemmGroup];
+  int64_t chunks = 0;
+  for (int i = 0; i < count; ++i) {
+    at[i] = prs[i];
+    at[i].M = rows;
+    chunks = std::max<int64_t>(chunks, (int64_t)rows * prs[i].N / 8);
+  }
+  const GemmPlan ref = plan_gemm<T>(at, count, num_cu);
+  GemmPlan pl = plan_gemm<T>(prs, count, num_cu);
+  pl.splits = ref.splits;
+  pl.k_slice = ref.k_slice;  // the K step depends on the type alone
+  int blocks;
+  plan_reduce(chunks * count, ref.splits, &pl.zl, &blocks);
   return pl;
 }
 
@@ -1428,15 +1460,6 @@ inline hipError_t launch_gemm_plan(const GemmProblem* prs, int count, const Gemm
   }
 }
 
-// Lanes that share a chunk of the reduction and the blocks it takes: more
-// lanes while the chunks alone leave the chip under four waves per CU.
-inline void plan_reduce(int64_t chunks, int splits, int* zl, int* blocks) {
-  int z = 1;
-  while (z < 16 && 2 * z <= splits && chunks * z < (int64_t)256 * 4 * kWave) z *= 2;
-  *zl = z;
-  *blocks = (int)std::max<int64_t>(1, std::min<int64_t>((chunks * z + 255) / 256, 8192));
-}
-
 // Joins the split-K partials of a planned group (parts[i]: problem i's
 // [slices][M][N]) through the epilogues.
 template <class Epi>
@@ -1457,6 +1480,7 @@ inline hipError_t launch_splitk_reduce(const GemmProblem* prs, int count, const 
     const int64_t mn = (int64_t)prs[i].M * prs[i].N;
     chunks = std::max<int64_t>(chunks, prs[i].N % 8 == 0 ? mn / 8 : mn);
   }
+  a.zl = pl.zl;
   plan_reduce(chunks * count, pl.splits, &a.zl, &a.blocks);
   a.blocks = (a.blocks + count - 1) / count;
   const dim3 grid(a.blocks + (cs_rows + 255) / 256, count);

@@ -44,3 +44,21 @@ extern "C" int host_register_path(int K, int batch, int colsum, int ksplit3) {
   if (ksplit3 >= 0) pr.ksplit3 = ksplit3;
   return gemm_runs_register(pr);
 }
+
+// How an append's product of `rows` rows cuts K and joins the slices, planned as
+// for `plan_rows` rows (0: for its own): slices, their length, lanes per chunk.
+template <typename T>
+static void row_plan(int rows, int n, int k, int plan_rows, int count, int* out) {
+  GemmProblem pr[2];
+  for (GemmProblem& q : pr) q.M = rows, q.N = n, q.K = k;
+  const GemmPlan pl = plan_rows ? plan_gemm_rows<T>(pr, count, plan_rows, 256) : plan_gemm<T>(pr, count, 256);
+  int zl = pl.zl, blocks;
+  plan_reduce((int64_t)rows * n / 8 * count, pl.splits, &zl, &blocks);
+  out[0] = plan_splits(pr[0], pl);
+  out[1] = plan_k_slice(pr[0], pl);
+  out[2] = zl;
+}
+
+extern "C" void host_row_plan(int esize, int rows, int n, int k, int plan_rows, int count, int* out) {
+  esize == 2 ? row_plan<bf16>(rows, n, k, plan_rows, count, out) : row_plan<float>(rows, n, k, plan_rows, count, out);
+}

@@ -117,3 +117,48 @@ def test_bits_do_not_depend_on_the_batch(gpu, dtype):
         alone = torch.stack([one.step(xs[t, b:b + 1].clone()) for t in range(5)])
         torch.cuda.synchronize()
         assert torch.equal(alone[:, 0], together[:, b]), n
+
+
+@pytest.mark.parametrize("dtype,heads,factors", [("bf16", 16, (8, 8)), ("fp32", 8, (4, 16))])
+def test_bits_do_not_depend_on_the_batch_across_an_append(gpu, dtype, heads, factors):
+    """64 sequences together, 12 of them, and each of a few alone, through a
+    step that completes a block and two that read it: cached rows and outputs
+    equal bit for bit. The compressions are long enough to be cut along K."""
+    import torch
+    B = gpu
+    d, p, steps = heads * 64, factors[0] * factors[1], 3
+    gen = torch.Generator(device="cuda").manual_seed(970)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+
+    def rnd(*shape, std=1.0):
+        return (torch.randn(shape, generator=gen, device="cuda") * std).to(dt)
+
+    shape = synth.DecodeShape(1, d, heads, 64, factors, n0=0, steps=1, dtype=dtype)
+    w = dev_weights(synth.decode_inputs(shape, 971)["weights"], dtype)
+    lens = [(37 * b) % 200 for b in range(64)]
+    kc, vc = rnd(64, heads, 210, 64), rnd(64, heads, 210, 64)
+    blk, kl, vl = rnd(64, p, d), rnd(64, heads, p, 64), rnd(64, heads, p, 64)
+    xs = rnd(steps, 64, d)
+
+    def decode(rows):
+        ragged = len(rows) > 1
+        kw = dict(ragged=True, n_seq=[lens[b] for b in rows], j_seq=[p - 1] * len(rows)) if ragged else dict(n=lens[rows[0]])
+        s = B.DecodeSession(B.decode_config(len(rows), d, heads, 64, factors, dtype=dtype), w, kc[rows].clone(),
+                            vc[rows].clone(), **kw)
+        s.x_blk.copy_(blk[rows])
+        s.k_loc.copy_(kl[rows])
+        s.v_loc.copy_(vl[rows])
+        if not ragged:
+            s.state.j = p - 1
+        y = torch.stack([s.step(xs[t, rows].clone()) for t in range(steps)])
+        torch.cuda.synchronize()
+        return y, s.k_cache, s.v_cache
+
+    whole = decode(list(range(64)))
+    for rows in [list(range(12))] + [[b] for b in (0, 5, 11, 40, 63)]:
+        part = decode(rows)
+        new = [lens[b] for b in rows]  # the row the block was appended at
+        for i, b in enumerate(rows):
+            for c in (1, 2):
+                assert torch.equal(part[c][i, :, new[i]], whole[c][b, :, new[i]]), (len(rows), b, "cached row")
+            assert torch.equal(part[0][:, i], whole[0][:, b]), (len(rows), b)

@@ -40,3 +40,21 @@ def test_register_path_refuses_what_it_does_not_know(rules):
     assert not rules.host_register_path(96, 1, 0, 64)
     assert not rules.host_register_path(96, 2, 0, -1)
     assert not rules.host_register_path(96, 1, 1, -1)
+
+
+@pytest.mark.parametrize("esize", [2, 4])
+def test_append_cuts_do_not_depend_on_the_batch(rules, esize):
+    """One block of each of 1 to 64 sequences: every product of the append cuts
+    K and joins the slices the same way, which its own rows would not do."""
+    out = (ctypes.c_int * 3)()
+    own = set()
+    for d in (128, 512, 1024, 2048):
+        for per_block, k, count in ((8, 8, 1), (1, 8, 1), (16, 4, 1), (256, 4, 1), (1, 1, 2)):
+            seen = set()
+            for batch in range(1, 65):
+                rules.host_row_plan(esize, batch * per_block, d, k * d, 8 * per_block, count, out)
+                seen.add(tuple(out))
+                rules.host_row_plan(esize, batch * per_block, d, k * d, 0, count, out)
+                own.add((d, per_block, k, count) + tuple(out))
+            assert len(seen) == 1, (d, per_block, k, count, seen)
+    assert len(own) > 4 * 5, "the plan by a product's own rows differs from batch to batch"

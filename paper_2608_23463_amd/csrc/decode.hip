@@ -839,13 +839,17 @@ static size_t decode_gemm_need(const DecodeDims& d, const DecodeWs& W) {
   ns.n_cap = 1;
   const DecodePos np{};
   for (int rows = 1; rows <= W.rows_cap; ++rows) {
-    // one append of `rows` blocks of a single sequence exercises every chunk size
+    // one append of `rows` blocks of a single sequence exercises every chunk
+    // size; a last chunk of one block, two chunks of one
     DecodeDims d1 = d;
     d1.B = 1;
+    DecodeWs w1 = W;
+    w1.rows_cap = rows;
+    const int nblk = std::max(rows, 2);
     if (d.esize == 2)
-      append_impl<bf16>(dry, d1, W, &nw, ns, np, nullptr, rows, nullptr);
+      append_impl<bf16>(dry, d1, w1, &nw, ns, np, nullptr, nblk, nullptr);
     else
-      append_impl<float>(dry, d1, W, &nw, ns, np, nullptr, rows, nullptr);
+      append_impl<float>(dry, d1, w1, &nw, ns, np, nullptr, nblk, nullptr);
   }
   // and one block per sequence
   if (d.esize == 2) {

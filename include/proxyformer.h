@@ -285,10 +285,13 @@ int proxy_decode_step(const pf_decode_config* cfg, const pf_decode_weights* w,
  * device memory, one per GPU, held until the process ends. It calls no
  * allocation routine; its device address is looked up once per device on the
  * first call there (with that device current).
- *  A step needs about B * n_heads * (head_dim + 2) * 4 bytes per 1,024 cached
- *  rows of its longest sequence, plus the append of one block per sequence
- *  (about 5 MiB at 32 sequences x 16,384 rows, d_model 1024); a step needing
- *  more than 64 MiB returns PF_ERR_UNSUPPORTED before any launch.
+ *  A step needs about B * n_heads * (head_dim + 2) * 4 bytes per slice of its
+ *  longest sequence's cache and one more (slices of 128 rows up to 16 of them,
+ *  then of 256, 512 and 1,024 rows), plus the append of one block per sequence
+ *  (about 10 MiB in all at 32 sequences x 16,384 rows, d_model 1024, blocks of
+ *  64 tokens). Where that passes 64 MiB both entry points run the step on
+ *  slices of at least 1,024 rows and append without partial sums; a step that
+ *  needs more even so returns PF_ERR_UNSUPPORTED here before any launch.
  *  Every call on one GPU uses that GPU's one array: calls that overlap on one
  *  GPU (other streams, other threads) race and corrupt each other's results.
  *  Nothing in the array needs to start at zero; it keeps the last call's

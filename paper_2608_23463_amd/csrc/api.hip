@@ -315,13 +315,21 @@ static int check_step_io(const DecodeDims& d, const void* x_t, void* y_t) {
   return PF_OK;
 }
 
+// Rows of the longest cache of the batch.
+static int64_t longest_cache(const DecodeDims& d, const pf_decode_state* st) {
+  if (!st->n_seq) return st->n;
+  int64_t n = 0;
+  for (int b = 0; b < d.B; ++b) n = std::max<int64_t>(n, st->n_seq[b]);
+  return n;
+}
+
 int proxy_decode_step(const pf_decode_config* cfg, const pf_decode_weights* w, pf_decode_state* st, const void* x_t,
                       void* y_t, void* workspace, size_t ws_bytes, void* stream) {
   DecodeDims d;
   int s = check_decode_common(cfg, w, st, &d, workspace, ws_bytes);
   if (s != PF_OK) return s;
   if ((s = check_step_io(d, x_t, y_t)) != PF_OK) return s;
-  return decode_step_on(d, decode_ws(d), w, st, x_t, y_t, reinterpret_cast<char*>(workspace),
+  return decode_step_on(d, decode_ws_for_step(d, longest_cache(d, st)), w, st, x_t, y_t, reinterpret_cast<char*>(workspace),
                         reinterpret_cast<hipStream_t>(stream), "proxy_decode_step");
 }
 
@@ -331,7 +339,6 @@ int proxy_decode_step(const pf_decode_config* cfg, const pf_decode_weights* w, p
 // runs on, held until the process ends. In host code `scratch` only names the
 // array; its device address comes from hipGetSymbolAddress, looked up once per
 // device (with that device current) on the first call there.
-static constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
 static constexpr int kMaxDevices = 64;
 static __device__ __align__(256) char scratch[kStaticScratchBytes];
 
@@ -361,13 +368,7 @@ int proxy_decode_step_static(const pf_decode_config* cfg, const pf_decode_weight
   int s = check_decode_common(cfg, w, st, &d, nullptr, 0, -1, false);
   if (s != PF_OK) return s;
   if ((s = check_step_io(d, x_t, y_t)) != PF_OK) return s;
-  int64_t n_max = st->n;  // the slices cover the longest cache of the batch
-  if (st->n_seq) {
-    n_max = 0;
-    for (int b = 0; b < d.B; ++b) n_max = std::max<int64_t>(n_max, st->n_seq[b]);
-  }
-  DecodeWs W = decode_step_ws(d, n_max, false);
-  if (W.bytes > kStaticScratchBytes) W = decode_step_ws(d, n_max, true);
+  const DecodeWs W = decode_step_ws(d, longest_cache(d, st));
   if (W.bytes > kStaticScratchBytes)
     return fail(PF_ERR_UNSUPPORTED,
                 "proxy_decode_step_static: this step needs %zu bytes of scratch, the static scratch holds %zu "

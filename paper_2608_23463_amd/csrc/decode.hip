@@ -612,17 +612,20 @@ static int append_pass(const DecodeDims& d) {
 // that reads it, has the same bits in any such batch. (Cut by the batch, 12
 // sequences of d = 1024 with 8 x 8 tokens per block summed 8 slices where one
 // sequence sums 16.) More blocks are cut by their number: there the partials
-// of a fixed cut would cost more than the products.
+// of a fixed cut would cost more than the products. A lean step does not cut
+// those at all.
 template <typename T>
 static void append_impl(Runner& run, const DecodeDims& d, const DecodeWs& W, const pf_decode_weights* w,
                         const pf_decode_state& st, const DecodePos& pos, const void* x_blocks, int64_t nblk, char* ws) {
   const int64_t total = (int64_t)d.B * nblk;   // (sequence, block) rows of the [B*nblk, P*d] view
   const int64_t row_elems = d.P * d.d;
-  const bool by_rows = nblk == 1 && d.B <= kAppendByRows && !run.lean;
+  const bool by_rows = nblk == 1 && d.B <= kAppendByRows;
   const int pass = by_rows ? std::min(W.rows_cap, append_pass<T>(d)) : W.rows_cap;
   auto plan = [&](const GemmProblem* prs, int count, int64_t rows_per_block) {
-    return by_rows ? plan_gemm_rows<T>(prs, count, (int)(kAppendPlanBlocks * rows_per_block), Runner::kPlanCUsGemm)
-                   : plan_gemm<T>(prs, count, Runner::kPlanCUsGemm, run.lean);
+    if (by_rows) return plan_gemm_rows<T>(prs, count, (int)(kAppendPlanBlocks * rows_per_block), Runner::kPlanCUsGemm);
+    GemmPlan pl = plan_gemm<T>(prs, count, Runner::kPlanCUsGemm);
+    if (W.lean) pl.splits = 1;
+    return pl;
   };
   for (int64_t r0 = 0; r0 < total; r0 += pass) {
     const int rows = (int)std::min<int64_t>(pass, total - r0);
@@ -662,7 +665,7 @@ static void append_impl(Runner& run, const DecodeDims& d, const DecodeWs& W, con
                             nblk, r0, d.nh, d.dh, pos};
     }
     const GemmPlan pl = plan(prs, 2, 1);
-    run.gemm_group<T, LAYOUT_K, LAYOUT_K>("append_kv_gemm", prs, epis, 2, run.lean ? nullptr : &pl);
+    run.gemm_group<T, LAYOUT_K, LAYOUT_K>("append_kv_gemm", prs, epis, 2, &pl);
   }
 }
 
@@ -831,85 +834,95 @@ static void step_impl(Runner& run, const DecodeDims& d, const DecodeWs& W, const
   });
 }
 
-// Split-K need of every GEMM a step or an append can issue (any chunk size).
-static size_t decode_gemm_need(const DecodeDims& d, const DecodeWs& W) {
-  Runner dry(true);
+// Dry run of an append of nblk blocks per sequence.
+static void dry_append(Runner& dry, const DecodeDims& d, const DecodeWs& W, int64_t nblk) {
   pf_decode_weights nw{};
   pf_decode_state ns{};
   ns.n_cap = 1;
   const DecodePos np{};
-  for (int rows = 1; rows <= W.rows_cap; ++rows) {
+  if (d.esize == 2)
+    append_impl<bf16>(dry, d, W, &nw, ns, np, nullptr, nblk, nullptr);
+  else
+    append_impl<float>(dry, d, W, &nw, ns, np, nullptr, nblk, nullptr);
+}
+
+// Split-K need (bytes) of the GEMMs of a config, which the appends issue.
+struct DecodeNeed {
+  size_t any;   // an append of any size, and any step's
+  size_t step;  // one block per sequence on the full plan
+};
+
+static DecodeNeed decode_need_of(const DecodeDims& d) {
+  DecodeWs w{};
+  Runner any(true), step(true);
+  for (int rows = 1; rows <= d.append_rows; ++rows) {
     // one append of `rows` blocks of a single sequence exercises every chunk
     // size; a last chunk of one block, two chunks of one
     DecodeDims d1 = d;
     d1.B = 1;
-    DecodeWs w1 = W;
-    w1.rows_cap = rows;
-    const int nblk = std::max(rows, 2);
-    if (d.esize == 2)
-      append_impl<bf16>(dry, d1, w1, &nw, ns, np, nullptr, nblk, nullptr);
-    else
-      append_impl<float>(dry, d1, w1, &nw, ns, np, nullptr, nblk, nullptr);
+    w.rows_cap = rows;
+    dry_append(any, d1, w, std::max(rows, 2));
   }
-  // and one block per sequence
-  if (d.esize == 2) {
-    append_impl<bf16>(dry, d, W, &nw, ns, np, nullptr, 1, nullptr);
-    step_impl<bf16>(dry, d, W, &nw, ns, np, nullptr, nullptr, nullptr);
-  } else {
-    append_impl<float>(dry, d, W, &nw, ns, np, nullptr, 1, nullptr);
-    step_impl<float>(dry, d, W, &nw, ns, np, nullptr, nullptr, nullptr);
-  }
-  return dry.gemm_need;
+  w.rows_cap = d.append_rows;
+  dry_append(step, d, w, 1);
+  return {std::max(any.gemm_need, step.gemm_need), step.gemm_need};
+}
+
+// Memoised for the last few configs of the thread: the sweep plans every
+// append size (about 0.25 ms) and its result is asked for on every call;
+// sessions of several configs may take turns.
+static DecodeNeed decode_need(const DecodeDims& d) {
+  constexpr int kMemo = 8;
+  static thread_local DecodeDims seen[kMemo];
+  static thread_local DecodeNeed need[kMemo];
+  static thread_local int count = 0, next = 0;
+  for (int at = 0; at < count; ++at)
+    if (memcmp(&seen[at], &d, sizeof(d)) == 0) return need[at];
+  const DecodeNeed n = decode_need_of(d);
+  seen[next] = d;
+  need[next] = n;
+  next = (next + 1) % kMemo;
+  count = std::min(count + 1, kMemo);
+  return n;
 }
 
 DecodeWs decode_ws(const DecodeDims& d) {
-  // memoised for the last few configs of the thread: the sizing sweep plans
-  // every append size (about 0.25 ms) and its result is asked for on every
-  // call; sessions of several configs may take turns
-  constexpr int kMemo = 8;
-  static thread_local DecodeDims seen[kMemo];
-  static thread_local size_t seen_need[kMemo];
-  static thread_local int count = 0, next = 0;
   DecodeWs w = decode_ws_layout(d, kDecodeMaxSplits, d.append_rows);
-  size_t need = 0;
-  int at = 0;
-  while (at < count && memcmp(&seen[at], &d, sizeof(d)) != 0) ++at;
-  if (at < count) {
-    need = seen_need[at];
-  } else {
-    need = decode_gemm_need(d, w);
-    seen[next] = d;
-    seen_need[next] = need;
-    next = (next + 1) % kMemo;
-    count = std::min(count + 1, kMemo);
-  }
-  w.bytes = w.gemm + align256(need);
+  w.bytes = w.gemm + align256(decode_need(d).any);
   return w;
 }
 
-DecodeWs decode_step_ws(const DecodeDims& d, int64_t n_max, bool lean) {
-  // as many slices as any length up to n_max is cut into
+// Slice partials a step over up to n_max rows writes: as many as any length
+// up to n_max is cut into.
+static int step_splits(int64_t n_max, bool lean) {
   int splits, chunk;
   split_plan(n_max, lean, &splits, &chunk);
-  if (!lean) splits = std::max<int>(splits, (int)std::min<int64_t>(kDecodeSlices, (n_max + 127) / 128));
-  // the step appends at most one block per sequence: B rows
-  DecodeWs w = decode_ws_layout(d, splits, (int)std::min<int64_t>(d.append_rows, d.B));
-  w.lean = lean;
-  Runner dry(true);
-  dry.lean = lean;
-  pf_decode_weights nw{};
-  pf_decode_state ns{};
-  ns.n_cap = 1;
-  ns.n = n_max;
-  const DecodePos np{};
-  if (d.esize == 2) {
-    append_impl<bf16>(dry, d, w, &nw, ns, np, nullptr, 1, nullptr);
-    step_impl<bf16>(dry, d, w, &nw, ns, np, nullptr, nullptr, nullptr);
-  } else {
-    append_impl<float>(dry, d, w, &nw, ns, np, nullptr, 1, nullptr);
-    step_impl<float>(dry, d, w, &nw, ns, np, nullptr, nullptr, nullptr);
+  return lean ? splits : std::max<int>(splits, (int)std::min<int64_t>(kDecodeSlices, (n_max + 127) / 128));
+}
+
+static DecodeWs full_step_ws(const DecodeDims& d, int64_t n_max) {
+  DecodeWs w = decode_ws_layout(d, step_splits(n_max, false), std::min(d.append_rows, d.B));
+  w.bytes = w.gemm + align256(decode_need(d).step);
+  return w;
+}
+
+DecodeWs decode_step_ws(const DecodeDims& d, int64_t n_max) {
+  DecodeWs w = full_step_ws(d, n_max);
+  for (int pass = w.rows_cap; w.bytes > kStaticScratchBytes; pass /= 2) {
+    w = decode_ws_layout(d, step_splits(n_max, true), pass);
+    w.lean = true;
+    Runner dry(true);
+    dry_append(dry, d, w, 1);
+    w.bytes = w.gemm + align256(dry.gemm_need);
+    if (pass == 1 || d.B > kAppendByRows) break;
   }
-  w.bytes = w.gemm + align256(dry.gemm_need);
+  return w;
+}
+
+DecodeWs decode_ws_for_step(const DecodeDims& d, int64_t n_max) {
+  const DecodeWs step = decode_step_ws(d, n_max);
+  DecodeWs w = decode_ws(d);
+  w.lean = step.lean && step.bytes <= kStaticScratchBytes;
   return w;
 }
 
@@ -918,7 +931,6 @@ hipError_t decode_step_run(const DecodeDims& d, const DecodeWs& W, const pf_deco
                            const pf_decode_state& st, const DecodePos& pos, const void* x_t, void* y_t, char* ws,
                            hipStream_t stream) {
   Runner run(false, stream, reinterpret_cast<float*>(ws + W.gemm));
-  run.lean = W.lean;
   step_impl<T>(run, d, W, w, st, pos, x_t, y_t, ws);
   return run.err;
 }
@@ -928,7 +940,6 @@ hipError_t cache_append_run(const DecodeDims& d, const DecodeWs& W, const pf_dec
                             const pf_decode_state& st, const DecodePos& pos, const void* x_blocks, int64_t nblk,
                             char* ws, hipStream_t stream) {
   Runner run(false, stream, reinterpret_cast<float*>(ws + W.gemm));
-  run.lean = W.lean;
   append_impl<T>(run, d, W, w, st, pos, x_blocks, nblk, ws);
   return run.err;
 }

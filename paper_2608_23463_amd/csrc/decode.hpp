@@ -32,6 +32,7 @@ struct DecodePos {
   int32_t ragged;
 };
 
+constexpr size_t kStaticScratchBytes = (size_t)64 << 20;  // of the step without a workspace
 constexpr int kDecodeMaxSplits = 256;   // cache-row slices per (sequence, head)
 constexpr int kDecodeRowsPerSplit = 1024;  // most rows per slice (while kDecodeMaxSplits suffice)
 constexpr int kDecodeSlices = 16;         // slices aimed at below that
@@ -46,7 +47,7 @@ struct DecodeWs {
   size_t z[PF_MAX_LEVELS];          // append: compression level outputs (j = 1..M)
   size_t gemm;
   size_t bytes;
-  bool lean;                        // the plans with the least scratch
+  bool lean;                        // the plan with the least scratch (decode_step_ws)
 };
 
 int decode_dims(const pf_decode_config* c, DecodeDims* d, const char** why);
@@ -54,10 +55,17 @@ int decode_dims(const pf_decode_config* c, DecodeDims* d, const char** why);
 DecodeWs decode_ws(const DecodeDims& d);
 // Scratch of one decode step whose longest cache holds n_max rows: its own
 // slice partials and the append of one block per sequence (smaller than
-// decode_ws; the layout differs, the kernels are the same). `lean`: the
-// plans with the least scratch (fewest slices and partials), for a caller
-// whose scratch is fixed.
-DecodeWs decode_step_ws(const DecodeDims& d, int64_t n_max, bool lean);
+// decode_ws; the layout differs, the kernels are the same). Where that passes
+// kStaticScratchBytes, the lean plan: slices of at least 1,024 rows, and an
+// append without split-K partials (or, of a batch whose bits must not depend
+// on it, in passes of as many blocks as fit).
+DecodeWs decode_step_ws(const DecodeDims& d, int64_t n_max);
+// The general workspace with the plan that decode_step_ws has for this step,
+// so a step gives the same bits with a workspace and without. (Where the lean
+// plan sets in, its slices are the faster ones: 512 sequences of 32 heads x
+// 2,000 rows 1,684 us a step, 1,739 in slices of 128.) A step beyond that
+// scratch on either plan takes the full one.
+DecodeWs decode_ws_for_step(const DecodeDims& d, int64_t n_max);
 // Rows per slice of a cache of n rows: the power of two from 128 (what a
 // workgroup reads at once) to 1,024 that gives about kDecodeSlices slices, and
 // beyond kDecodeMaxSplits * 1,024 rows what kDecodeMaxSplits slices take. It
@@ -65,7 +73,8 @@ DecodeWs decode_step_ws(const DecodeDims& d, int64_t n_max, bool lean);
 // sequence the same bits alone and in any batch. One sequence of 8 heads over
 // 1,500 rows ran as 24 workgroups of eight dependent reads each in slices of
 // 1,024: with the other changes of the step 26.2 us, 15.5 now; 32 sequences of
-// 16 heads x 1,500, 4,000 and 9,000 rows are unchanged (55, 121, 224 us). `lean`: 1,024 at least, the fewest partials.
+// 16 heads x 1,500, 4,000 and 9,000 rows are unchanged (55, 121, 224 us).
+// `lean`: 1,024 rows at least, the fewest partials.
 __host__ __device__ inline int slice_rows(int n, bool lean) {
   int c = lean ? kDecodeRowsPerSplit : 128;
   while (c < kDecodeRowsPerSplit && n > kDecodeSlices * c) c *= 2;

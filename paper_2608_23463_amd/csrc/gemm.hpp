@@ -1176,14 +1176,12 @@ struct GemmPlan {
 };
 
 // One plan for a group of problems launched together (their tiles fill the
-// chip together; each has its own k_slice). `lean`: 128x128 tiles for all but
-// the smallest products and at most one workgroup per CU, which bounds the
-// split-K partials by 32 MiB.
+// chip together; each has its own k_slice).
 template <typename T>
-inline GemmPlan plan_gemm(const GemmProblem* prs, int count, int num_cu, bool lean = false) {
+inline GemmPlan plan_gemm(const GemmProblem* prs, int count, int num_cu) {
   GemmPlan pl;
   int64_t mn = 0, t256 = 0, t128 = 0;
-  int min_m = prs[0].M, min_n = prs[0].N, max_mn = 0, max_k = 0;
+  int min_m = prs[0].M, min_n = prs[0].N, max_k = 0;
   for (int i = 0; i < count; ++i) {
     const GemmProblem& q = prs[i];
     mn += (int64_t)q.M * q.N;
@@ -1191,7 +1189,6 @@ inline GemmPlan plan_gemm(const GemmProblem* prs, int count, int num_cu, bool le
     t128 += (int64_t)((q.M + 127) / 128) * ((q.N + 127) / 128) * q.batch;
     min_m = std::min(min_m, q.M);
     min_n = std::min(min_n, q.N);
-    max_mn = std::max(max_mn, std::max(q.M, q.N));
     max_k = std::max(max_k, q.K);
   }
   pl.bk = sizeof(T) == 4 ? 32 : 64;
@@ -1200,8 +1197,7 @@ inline GemmPlan plan_gemm(const GemmProblem* prs, int count, int num_cu, bool le
   // operand loads, and four times the workgroups with four stages in flight
   // instead of two wait a quarter as long.
   const int64_t kb = (max_k + pl.bk - 1) / pl.bk;
-  const bool small = lean ? sizeof(T) == 2 && max_mn <= 64
-                          : t128 * std::max<int64_t>(1, kb / 8) < num_cu || (min_n <= 64 && max_k <= 2 * pl.bk);
+  const bool small = t128 * std::max<int64_t>(1, kb / 8) < num_cu || (min_n <= 64 && max_k <= 2 * pl.bk);
   const int max_dim_tile = small ? TILE_64x64 : TILE_128x128;
   // Without a split, 256x256 tiles (one per CU) against 128x128 (two per CU)
   // by the share of the chip's rounds that the result fills; a 256x256 tile
@@ -1211,8 +1207,8 @@ inline GemmPlan plan_gemm(const GemmProblem* prs, int count, int num_cu, bool le
   auto fill = [&](int64_t t, int64_t slots, int64_t edge) {
     return (double)mn / (double)((t + slots - 1) / slots * slots * edge * edge);
   };
-  const bool wide_fills = lean ? mn >= (int64_t)256 * 256 * num_cu
-                               : t256 * 10 >= num_cu * 9 && fill(t256, num_cu, 256) * 1.15 >= fill(t128, 2 * num_cu, 128);
+  const bool wide_fills =
+      t256 * 10 >= num_cu * 9 && fill(t256, num_cu, 256) * 1.15 >= fill(t128, 2 * num_cu, 128);
   if (sizeof(T) == 4) {
     pl.tile = max_dim_tile;
   } else if (min_m >= 256 && min_n >= 256 &&
@@ -1224,7 +1220,7 @@ inline GemmPlan plan_gemm(const GemmProblem* prs, int count, int num_cu, bool le
     pl.tile = max_dim_tile;
   }
   pl.bm = pl.bn = pl.tile == TILE_256x256 ? 256 : pl.tile == TILE_128x128 ? 128 : 64;
-  const bool one_pass = pl.tile == TILE_256x256 && wide_fills && !lean;
+  const bool one_pass = pl.tile == TILE_256x256 && wide_fills;
   int64_t tiles = 0;
   int batch = 1;
   for (int i = 0; i < count; ++i) {
@@ -1240,13 +1236,13 @@ inline GemmPlan plan_gemm(const GemmProblem* prs, int count, int num_cu, bool le
   auto more = [&](int s) {
     if (batch != 1 || one_pass) return false;
     if (tiles * s < num_cu) return kblocks / (s * 2) >= 8;
-    return !lean && pl.tile == TILE_128x128 && tiles * s < 2 * num_cu && kblocks / (s * 2) >= 16;
+    return pl.tile == TILE_128x128 && tiles * s < 2 * num_cu && kblocks / (s * 2) >= 16;
   };
   while (more(splits)) splits *= 2;
   // a split pays its partials and the reduction's launch (5 us and more), so
   // it has to take enough steps off the longest chain: ten of a 64x64 tile's
   // (0.35 us each, and up to 1 us with an M/N-major operand)
-  if (!lean && pl.tile == TILE_64x64 && kblocks - kblocks / splits < 10) splits = 1;
+  if (pl.tile == TILE_64x64 && kblocks - kblocks / splits < 10) splits = 1;
   const int kb_per = (kblocks + splits - 1) / splits;
   pl.k_slice = kb_per * pl.bk;
   pl.splits = (kblocks + kb_per - 1) / kb_per;

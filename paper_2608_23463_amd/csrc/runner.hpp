@@ -14,7 +14,6 @@ struct Runner {
   float* gemm_ws;      // split-K partials (may be NULL in a dry run)
   size_t gemm_need;    // dry run: max bytes any GEMM asked for
   hipError_t err;
-  bool lean = false;   // GEMM plans with the least split-K workspace, one product at a time
 
   explicit Runner(bool dry_run, hipStream_t s = nullptr, float* ws = nullptr)
       : dry(dry_run), stream(s), gemm_ws(ws), gemm_need(0), err(hipSuccess) {}
@@ -37,11 +36,7 @@ struct Runner {
     if (!ok() || count <= 0) return;
     for (int i = 0; i < count; ++i)
       if (prs[i].M <= 0 || prs[i].N <= 0) return;
-    if (lean && count > 1) {
-      for (int i = 0; i < count; ++i) gemm_group<T, LA, LB>(label, prs + i, epis + i, 1);
-      return;
-    }
-    GemmPlan pl = plan ? *plan : plan_gemm<T>(prs, count, kPlanCUsGemm, lean);
+    GemmPlan pl = plan ? *plan : plan_gemm<T>(prs, count, kPlanCUsGemm);
     if (dry) {
       if (pl.splits > 1) {
         size_t need = 0;

@@ -14,7 +14,7 @@ import pytest
 
 from paper_2608_23463_amd import synth
 from paper_2608_23463_amd.synth import DecodeShape
-from helpers import dev
+from helpers import dev, dev_weights
 from test_gpu_decode import make_session
 
 pytestmark = pytest.mark.gpu
@@ -51,3 +51,35 @@ def test_static_scratch_step_matches_workspace_step(gpu):
         n = a.n
         assert torch.equal(a.k_cache[:, :, :n], b.k_cache[:, :, :n]), label
         assert torch.equal(a.v_cache[:, :, :n], b.v_cache[:, :, :n]), label
+
+
+def test_static_step_past_the_full_plans_scratch(gpu):
+    """512 sequences of 32 heads over 2,000 rows: the partials of the short
+    slices alone take more than the 64 MiB, so the step takes the plan with
+    less scratch, through either entry point: outputs and appended rows are
+    bit-identical, as they are over 100 rows, where the full plan fits."""
+    import torch
+    B = gpu
+    nb, nh, d, p = 512, 32, 2048, 4
+    w = dev_weights(synth.decode_inputs(DecodeShape(1, d, nh, 64, (p,), n0=0, steps=1), 9100)["weights"], "bf16")
+    gen = torch.Generator(device="cuda").manual_seed(9101)
+
+    def rnd(*s):
+        return torch.randn(s, generator=gen, device="cuda", dtype=torch.bfloat16)
+
+    blk, kl, vl, xs = rnd(nb, p, d), rnd(nb, nh, p, 64), rnd(nb, nh, p, 64), rnd(3, nb, d)
+    for n in (2000, 100):
+        kc, vc = rnd(nb, nh, n + 2, 64), rnd(nb, nh, n + 2, 64)
+        out = []
+        for static in (False, True):
+            s = B.DecodeSession(B.decode_config(nb, d, nh, 64, (p,)), w, kc.clone(), vc.clone(), n=n)
+            s.x_blk.copy_(blk)
+            s.k_loc.copy_(kl)
+            s.v_loc.copy_(vl)
+            s.state.j = p - 2
+            print(f"[no-alloc decode] 512 x 2048, n = {n}, static {static}", flush=True)
+            ys = [(s.step_static if static else s.step)(xs[t]) for t in range(3)]
+            torch.cuda.synchronize()
+            out.append((torch.stack(ys), s.k_cache, s.v_cache))
+        for a, b in zip(*out):
+            assert torch.equal(a, b), n

@@ -1,7 +1,8 @@
 // Proxy-KV-cache decode step and block-triggered append (Eq. 19-21, Sec. 3.8).
 //
 // Step (one token per sequence, the batch in lockstep), four launches (three
-// for up to four sequences over few slices, which merge in the fourth):
+// for up to 1,024 channels of the batch over few slices, which merge in the
+// fourth):
 //  1. decode_proj_kernel: u = RMSNorm(x) * gamma formed on the fly and
 //     multiplied by W_q, W_k, W_v and W_alpha (one 32-column block of the
 //     concatenated outputs per workgroup, MFMA over 32 batch rows): q to
@@ -717,13 +718,15 @@ static hipError_t launch_small_gemm(dim3 grid, const DecodeProjParams& pp, const
 }
 
 // The merge joins the output map while a workgroup's copy of the partials is
-// at most kMergeInOutBytes and its threads merge at most two channel pairs
-// each, one after the other: every workgroup repeats the merge, so it pays
-// only while that is shorter than a launch. A step of one sequence, 8 heads x
-// 200 rows: 15.3 us merged, 21.7 before; past the first bound 16 heads x 8,000
-// rows (271 KB) 30.6 us merged against 25.9, past the second 2 sequences of 16
-// heads x 4,000 rows 34.2 against 24.9.
-constexpr int64_t kMergeInOutBytes = 128 << 10;
+// at most kMergeInOutBytes (16 heads of 64 channels over 16 slices and the
+// block's) and its threads merge at most two channel pairs each, one after the
+// other: every workgroup repeats the merge, so it pays only while that is
+// shorter than a launch. us a step, merged and not: one sequence of 8 heads x
+// 1,500, 30,000 (65 KB) and 60,000 rows (126 KB) 14.4 / 16.4, 26.7 / 27.5 and
+// 37.2 / 37.1; of 16 heads x 16,384 (72 KB) and 24,000 rows (106 KB) 29.0 /
+// 29.4 and 35.0 / 32.5; past the second bound 2 sequences of 16 heads x 1,500
+// rows 23.4 / 19.1.
+constexpr int64_t kMergeInOutBytes = 72 << 10;
 constexpr int kMergeInOutChannels = 1024;
 
 template <typename T>

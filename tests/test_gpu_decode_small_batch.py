@@ -27,7 +27,9 @@ CASES = {
     "B2_d512_fp32_n150": (2, 8, 64, "fp32", 150),
     "B2_d512_n700_merged": (2, 8, 64, "bf16", 700),      # two rows in the merged output map
     "B4_d256_fp32_n90": (4, 4, 64, "fp32", 90),
-    "B4_d1024_n3000_combine": (4, 16, 64, "bf16", 3000),  # partials past the merge's bound
+    "B4_d1024_n3000_combine": (4, 16, 64, "bf16", 3000),  # more channels than the merge takes
+    "merge_past_B1_d1024_n16500": (1, 16, 64, "bf16", 16500),  # 17 slices: partials past the merge's bound
+    "merge_B1_d1024_n16380": (1, 16, 64, "bf16", 16380),       # 16, at the bound
     "B8_d320_n90": (8, 5, 64, "bf16", 90),              # two staged rows per wave
     "B9_d512_n200": (9, 8, 64, "bf16", 200),            # four
     "B16_d1024_n60_dh128": (16, 8, 128, "bf16", 60),

@@ -692,7 +692,7 @@ static hipError_t allow_lds(const void* kernel) {
 }
 
 // Chunks per lane and row of the staged A: 1, 2 or 4 (d * sizeof(T) <= 4096);
-// rows per wave by the batch.
+// rows per wave by the batch (at most four sequences merge in the output map).
 template <typename T, bool PROJ, int MERGE = 0>
 static hipError_t launch_small_gemm(dim3 grid, const DecodeProjParams& pp, const DecodeAttnParams& ap,
                                     hipStream_t stream) {
@@ -714,7 +714,8 @@ static hipError_t launch_small_gemm(dim3 grid, const DecodeProjParams& pp, const
   };
   if (cpr <= 64) return by_rows(std::integral_constant<int, 1>{});
   if (cpr <= 128) return by_rows(std::integral_constant<int, 2>{});
-  return by_rows(std::integral_constant<int, 4>{});
+  if constexpr (MERGE == 0 || sizeof(T) == 4) return by_rows(std::integral_constant<int, 4>{});
+  return hipErrorInvalidValue;  // the merge takes at most kMergeInOutChannels: two chunks in bf16
 }
 
 // The merge joins the output map while a workgroup's copy of the partials is

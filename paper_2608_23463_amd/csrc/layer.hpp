@@ -93,7 +93,7 @@ struct LayerWs {
   // staged token tensors (L_in < L: zero-padded to L tokens; 2-D partition:
   // in patch order)
   size_t x_pad;               // X with zero padding [B*L, d_f]
-  size_t y_pad;               // forward: X_out, for the injections without a mapped store [B*L, d_f]; backward: unused
+  size_t y_pad;               // forward: X_out, for the injections without a mapped store [B*L, d_f]; else unused
   size_t dy_pad;              // backward: dY with zero padding [B*L, d_f]
   size_t dst;                 // Eq. 13 backward: [dS | dT] [B*L, 2 d_f]
   size_t dgh;                 // per-head gate backward: dG [B*L, round8(n_heads)]

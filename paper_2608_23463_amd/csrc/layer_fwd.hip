@@ -385,7 +385,9 @@ LayerWs layer_ws_layout(const LayerDims& d, bool bwd) {
   if (bwd && d.inject == PF_INJECT_GATED_HEAD) w.dgh = take((size_t)d.B * d.L * round8(d.nh) * es);
   if (d.staged()) {
     w.x_pad = take(tok);
-    w.y_pad = take(tok);  // the queried sizes hold three token tensors beside the backward's, two beside the forward's
+    // the mapped stores leave y_pad unread in the backward and in two forwards,
+    // but the size queries promise room for a copy of every token tensor
+    w.y_pad = take(tok);
     w.dy_pad = bwd ? take(tok) : 0;
   }
   w.gemm = off;

@@ -86,6 +86,12 @@ struct GemmShape {
   static constexpr int kStride = BK + kVec;    // LDS row stride (elements)
   static constexpr int kTM = BM / WM, kTN = BN / WN;
   static constexpr int kFM = kTM / 32, kFN = kTN / 32;
+  // fp32 with one accumulator per wave (64x64 tiles): the odd k-steps have one
+  // of their own, which halves the chain of additions behind a result. These
+  // tiles cut K into up to twice longer slices than 128x128 ones would, whose
+  // error the sums would otherwise not reach (Q, K and V of 4,928 rows at
+  // K = 576: 4.3e-7 of the result with one chain over K, 3.1e-7 with two).
+  static constexpr bool kPair = sizeof(T) == 4 && kFM * kFN == 1;
   static constexpr int kALoads = BM * BK / (kThreads * kVec);
   static constexpr int kBLoads = BN * BK / (kThreads * kVec);
   static constexpr int kStageElems = (BM + BN) * kStride;
@@ -598,6 +604,7 @@ __global__ void __launch_bounds__(WM* WN* kWave)
   LdB ldb_;
   lda_.init(p, m0, p.M, tid);
   ldb_.init(p, n0, p.N, tid);
+  f32x16 odd{};  // kPair: the sums of the odd k-steps
   u32x4 ra[LdA::kLoads], rb[LdB::kLoads];
   const int nk = (kend - kbeg + BK - 1) / BK;
   if (nk > 0) {
@@ -637,7 +644,10 @@ __global__ void __launch_bounds__(WM* WN* kWave)
 #pragma unroll
       for (int i = 0; i < S::kFM; ++i)
 #pragma unroll
-        for (int j = 0; j < S::kFN; ++j) acc[i][j] = MM::mma(fa[cb][i], fb[cb][j], acc[i][j]);
+        for (int j = 0; j < S::kFN; ++j) {
+          f32x16& c = S::kPair && cb ? odd : acc[i][j];
+          c = MM::mma(fa[cb][i], fb[cb][j], c);
+        }
     }
     if constexpr (sizeof(T) == 2) pin_kstep_schedule<S::kFM + S::kFN, S::kFM * S::kFN, BK / 16>();
     if (more) {
@@ -648,6 +658,7 @@ __global__ void __launch_bounds__(WM* WN* kWave)
     __syncthreads();
   }
 
+  if constexpr (S::kPair) acc[0][0] += odd;
   static_assert((size_t)S::kTM * (BN + 8) * sizeof(float) <= S::kLdsBytes, "epilogue band must fit in LDS");
   gemm_store<S, BM, BN, WM>(acc, reinterpret_cast<float*>(smem), p, m0, n0, wm, wn, lane, tid, epi);
 }
@@ -952,6 +963,7 @@ __global__ void __launch_bounds__(WM* WN* kWave)
     return f;
   };
   typename MM::frag fa[2][S::kFM], fb[2][S::kFN];
+  f32x16 odd{};  // kPair: the sums of the odd k-steps
   constexpr bool kColsum = OA::kMN && OB::kMN;
   const int rot = kColsum ? wn % S::kFM : 0;
   constexpr int kColsumFold = 128 / kSub;
@@ -981,7 +993,10 @@ __global__ void __launch_bounds__(WM* WN* kWave)
 #pragma unroll
     for (int i = 0; i < S::kFM; ++i)
 #pragma unroll
-      for (int j = 0; j < S::kFN; ++j) acc[i][j] = MM::mma(fa[buf][i], fb[buf][j], acc[i][j]);
+      for (int j = 0; j < S::kFN; ++j) {
+        f32x16& c = S::kPair && buf ? odd : acc[i][j];
+        c = MM::mma(fa[buf][i], fb[buf][j], c);
+      }
     if constexpr (kColsum) {
       float v[8];
 #pragma unroll
@@ -1033,6 +1048,7 @@ __global__ void __launch_bounds__(WM* WN* kWave)
     }
     if (kt + NS < nk) issue(kbeg + (kt + NS) * BK, kt % NS);  // after the hand-off above
   }
+  if constexpr (S::kPair) acc[0][0] += odd;
   // Every direct load has landed (the last wait_stages drained them all).
   // The stage that held tile nk-2 is free on every wave: nothing reads it
   // after the barrier that handed over tile nk-1 and no load refills it;
@@ -1221,10 +1237,13 @@ inline GemmPlan plan_gemm(const GemmProblem* prs, int count, int num_cu) {
   }
   pl.bm = pl.bn = pl.tile == TILE_256x256 ? 256 : pl.tile == TILE_128x128 ? 128 : 64;
   const bool one_pass = pl.tile == TILE_256x256 && wide_fills;
+  // K is cut by the tiles of the group, in fp32 by those of its largest member:
+  // there the sums are as long as the member's own launch would have them
   int64_t tiles = 0;
   int batch = 1;
   for (int i = 0; i < count; ++i) {
-    tiles += (int64_t)((prs[i].M + pl.bm - 1) / pl.bm) * ((prs[i].N + pl.bn - 1) / pl.bn) * prs[i].batch;
+    const int64_t t = (int64_t)((prs[i].M + pl.bm - 1) / pl.bm) * ((prs[i].N + pl.bn - 1) / pl.bn) * prs[i].batch;
+    tiles = sizeof(T) == 4 ? std::max(tiles, t) : tiles + t;
     batch = std::max(batch, prs[i].batch);
   }
   const int kblocks = (max_k + pl.bk - 1) / pl.bk;
@@ -1261,7 +1280,8 @@ inline void plan_reduce(int64_t chunks, int splits, int* zl, int* blocks) {
 
 // Plan of a group whose rows change from call to call while a row's bits may
 // not: K is cut and its slices are joined as for `rows` rows, whatever the
-// problems have; only the tile, which no sum depends on, follows theirs.
+// problems have; only the bf16 tile, which no sum depends on, follows theirs
+// (fp32 tiles differ in GemmShape::kPair).
 template <typename T>
 inline GemmPlan plan_gemm_rows(const GemmProblem* prs, int count, int rows, int num_cu) {
   GemmProblem at[kGemmGroup];
@@ -1272,7 +1292,7 @@ inline GemmPlan plan_gemm_rows(const GemmProblem* prs, int count, int rows, int 
     chunks = std::max<int64_t>(chunks, (int64_t)rows * prs[i].N / 8);
   }
   const GemmPlan ref = plan_gemm<T>(at, count, num_cu);
-  GemmPlan pl = plan_gemm<T>(prs, count, num_cu);
+  GemmPlan pl = sizeof(T) == 4 ? ref : plan_gemm<T>(prs, count, num_cu);
   pl.splits = ref.splits;
   pl.k_slice = ref.k_slice;  // the K step depends on the type alone
   int blocks;

@@ -46,7 +46,8 @@ extern "C" int host_register_path(int K, int batch, int colsum, int ksplit3) {
 }
 
 // How an append's product of `rows` rows cuts K and joins the slices, planned as
-// for `plan_rows` rows (0: for its own): slices, their length, lanes per chunk.
+// for `plan_rows` rows (0: for its own): slices, their length, lanes per chunk,
+// and in fp32, whose tiles sum in different chains, the tile.
 template <typename T>
 static void row_plan(int rows, int n, int k, int plan_rows, int count, int* out) {
   GemmProblem pr[2];
@@ -57,6 +58,7 @@ static void row_plan(int rows, int n, int k, int plan_rows, int count, int* out)
   out[0] = plan_splits(pr[0], pl);
   out[1] = plan_k_slice(pr[0], pl);
   out[2] = zl;
+  out[3] = sizeof(T) == 4 ? pl.tile : 0;
 }
 
 extern "C" void host_row_plan(int esize, int rows, int n, int k, int plan_rows, int count, int* out) {

@@ -125,3 +125,37 @@ def test_bias_gradient_of_a_long_reduction(gpu, data):
     err = float(((g["decompress"][0][1].double() - ref).abs() / ref).max())
     print(f"  bias gradient over {shape.seq_len // 2} rows: {err:.2e}", flush=True)
     assert err <= 1e-5
+
+
+@pytest.mark.parametrize("batch,tokens,heads", [(7, 610, 10), (1, 250, 8), (2, 1002, 8)])
+def test_fp32_projections_error_of_short_chains(gpu, batch, tokens, heads):
+    """fp32 Q, K and V in one launch: the K and V of a prefill's unfinished
+    block against 64 bits. A sum of K products in chains of K / 2 is off by
+    about 1.3e-8 sqrt(K) of the result (2-norms; 3.3e-7 measured at K = 640),
+    one chain by sqrt(2) times that; the bound lies halfway."""
+    import torch
+    B = gpu
+    d, p = heads * 64, 64
+    gen = torch.Generator(device="cuda").manual_seed(4190 + tokens)
+
+    def rnd(*shape, std=1.0):
+        return torch.randn(shape, generator=gen, device="cuda") * std
+
+    lin = lambda o, i: (rnd(o, i, std=0.05), torch.zeros(o, device="cuda"))
+    w = {"rms_gamma": torch.ones(d, device="cuda"), "alpha": lin(heads, d), "compress": [lin(d, p * d)]}
+    for name in ("q", "k", "v", "o", "k_proxy", "v_proxy"):
+        w[name] = lin(d, d)
+    print(f"[case {batch} x {tokens} x {d}]", flush=True)
+    s = B.DecodeSession(B.decode_config(batch, d, heads, 64, (p,), dtype="fp32"), w, rnd(batch, heads, 20, 64),
+                        rnd(batch, heads, 20, 64), n=2)
+    x = rnd(batch, tokens, d)
+    s.prefill(x)
+    torch.cuda.synchronize()
+    tail = tokens % p
+    xt = x[:, tokens - tail:].double().cpu()
+    u = xt / torch.sqrt((xt * xt).mean(-1, keepdim=True) + 1e-6)
+    for name, got in (("k", s.k_loc), ("v", s.v_loc)):
+        ref = (u.reshape(-1, d) @ w[name][0].double().cpu().T).reshape(batch, tail, heads, 64).transpose(1, 2)
+        err = float((got[:, :, :tail].double().cpu() - ref).norm() / ref.norm())
+        print(f"  {name}: {err:.2e} ({err / d ** 0.5:.2e} sqrt(K))", flush=True)
+        assert err <= 1.55e-8 * d ** 0.5

@@ -46,7 +46,7 @@ def test_register_path_refuses_what_it_does_not_know(rules):
 def test_append_cuts_do_not_depend_on_the_batch(rules, esize):
     """One block of each of 1 to 64 sequences: every product of the append cuts
     K and joins the slices the same way, which its own rows would not do."""
-    out = (ctypes.c_int * 3)()
+    out = (ctypes.c_int * 4)()
     own = set()
     for d in (128, 512, 1024, 2048):
         for per_block, k, count in ((8, 8, 1), (1, 8, 1), (16, 4, 1), (256, 4, 1), (1, 1, 2)):

@@ -207,10 +207,10 @@ __global__ void __launch_bounds__(256) colsum_partial8_kernel(const T* __restric
   store8(&sums[rl][cg * 8], s);
   __syncthreads();
   if (threadIdx.x < 64 && blockIdx.x * 64 + threadIdx.x < n) {
-    float o = 0.0f;
-#pragma unroll 8
-    for (int k = 0; k < 32; ++k) o += sums[k][threadIdx.x];
-    part[(int64_t)chunk * n + blockIdx.x * 64 + threadIdx.x] = o;
+    float o[4] = {0, 0, 0, 0};  // four short chains: the sums of few rows are this join alone
+#pragma unroll
+    for (int k = 0; k < 32; ++k) o[k & 3] += sums[k][threadIdx.x];
+    part[(int64_t)chunk * n + blockIdx.x * 64 + threadIdx.x] = (o[0] + o[1]) + (o[2] + o[3]);
   }
 }
 

@@ -159,3 +159,20 @@ def test_fp32_projections_error_of_short_chains(gpu, batch, tokens, heads):
         err = float((got[:, :, :tail].double().cpu() - ref).norm() / ref.norm())
         print(f"  {name}: {err:.2e} ({err / d ** 0.5:.2e} sqrt(K))", flush=True)
         assert err <= 1.55e-8 * d ** 0.5
+
+
+def test_bias_gradient_of_few_rows(gpu):
+    """fp32 bias gradients over 31 rows: chains of eight values and two joins,
+    so at most ten roundings of 2^-24, where one chain loses each of the thirty
+    2^-25 that follow a one (8.9e-7)."""
+    import torch
+    B = gpu
+    shape = LayerShape(1, 16 * 31, 64, 64, 1, 64, (16,), dtype="fp32", injection=synth.INJECT_ADD)
+    inp = synth.layer_inputs(shape, 4180, with_dy=True)
+    inp["dy"][:] = 2.0 ** -25
+    inp["dy"][:, :16] = 1.0
+    print(f"[case] {shape}", flush=True)
+    db = run_gpu_backward(shape, inp)[2]["decompress"][0][1].double().cpu()
+    err = float((db - (1.0 + 30 * 2.0 ** -25)).abs().max())
+    print(f"  {err:.2e}", flush=True)
+    assert err <= 10 * 2.0 ** -24

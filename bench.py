@@ -116,7 +116,7 @@ def layer_flops(shape):
         comp += 2 * rows * (k * dims[j]) * dims[j + 1]
     return {
         "compress_gemm": comp / len(shape.factors),
-        "qkv_gemm": 2 * B * m * dp * dp,
+        "qkv_gemm": 3 * 2 * B * m * dp * dp,   # Q, K and V in one launch
         "attention_fwd": 2.0 * B * dp * m * (m + 1),   # QK^T and PV over the causal triangle
         "o_gemm": 2 * B * m * dp * dp,
         "decompress_gemm": comp / len(shape.factors),

@@ -70,7 +70,7 @@ DecodeWs decode_ws_for_step(const DecodeDims& d, int64_t n_max);
 // workgroup reads at once) to 1,024 that gives about kDecodeSlices slices, and
 // beyond kDecodeMaxSplits * 1,024 rows what kDecodeMaxSplits slices take. It
 // depends on the sequence's length alone, not on the batch, so a step gives a
-// sequence the same bits alone and in any batch. One sequence of 8 heads over
+// sequence the same bits alone and in any batch on the full plan. One sequence of 8 heads over
 // 1,500 rows ran as 24 workgroups of eight dependent reads each in slices of
 // 1,024: with the other changes of the step 26.2 us, 15.5 now; 32 sequences of
 // 16 heads x 1,500, 4,000 and 9,000 rows are unchanged (55, 121, 224 us).

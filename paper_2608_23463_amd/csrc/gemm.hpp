@@ -1211,7 +1211,9 @@ inline GemmPlan plan_gemm(const GemmProblem* prs, int count, int num_cu) {
   // 64x64 tiles where 128x128 ones, split along K into slices of eight steps,
   // would still leave CUs without work: a product of that size waits on its
   // operand loads, and four times the workgroups with four stages in flight
-  // instead of two wait a quarter as long.
+  // instead of two wait a quarter as long. And for results at most 64 wide over
+  // at most two K steps (the gate of a 64-wide stream, 136 -> 127 us): a wider
+  // tile stages and multiplies as much again for nothing; longer K not measured.
   const int64_t kb = (max_k + pl.bk - 1) / pl.bk;
   const bool small = t128 * std::max<int64_t>(1, kb / 8) < num_cu || (min_n <= 64 && max_k <= 2 * pl.bk);
   const int max_dim_tile = small ? TILE_64x64 : TILE_128x128;

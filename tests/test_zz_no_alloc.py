@@ -83,3 +83,37 @@ def test_static_step_past_the_full_plans_scratch(gpu):
             out.append((torch.stack(ys), s.k_cache, s.v_cache))
         for a, b in zip(*out):
             assert torch.equal(a, b), n
+
+
+def test_static_step_appends_in_passes(gpu):
+    """19 sequences with blocks of 2,000 tokens: the append's partials and
+    level outputs do not fit beside each other, so without a workspace it runs
+    in passes of a few blocks, cut along K as the whole batch is: bit-identical."""
+    import torch
+    B = gpu
+    nb, nh, dh, factors = 19, 7, 128, (4, 100, 5)
+    d, p, n = nh * dh, 2000, 11
+    gen = torch.Generator(device="cuda").manual_seed(9102)
+
+    def rnd(*s, std=1.0):
+        return torch.randn(s, generator=gen, device="cuda") * std
+
+    lin = lambda o, i: (rnd(o, i, std=0.02), rnd(o, std=0.02))
+    w = {"rms_gamma": torch.ones(d, device="cuda"), "alpha": lin(nh, d), "compress": [lin(d, k * d) for k in factors]}
+    for name in ("q", "k", "v", "o", "k_proxy", "v_proxy"):
+        w[name] = lin(d, d)
+    kc, vc, xs = rnd(nb, nh, n + 2, dh), rnd(nb, nh, n + 2, dh), rnd(3, nb, d)
+    blk, kl, vl = rnd(nb, p, d), rnd(nb, nh, p, dh), rnd(nb, nh, p, dh)
+    out = []
+    for static in (False, True):
+        print(f"[no-alloc decode] 19 x 896 fp32, blocks of 2,000, static {static}", flush=True)
+        s = B.DecodeSession(B.decode_config(nb, d, nh, dh, factors, dtype="fp32"), w, kc.clone(), vc.clone(), n=n)
+        s.x_blk.copy_(blk)
+        s.k_loc.copy_(kl)
+        s.v_loc.copy_(vl)
+        s.state.j = p - 2
+        ys = [(s.step_static if static else s.step)(xs[t]) for t in range(3)]
+        torch.cuda.synchronize()
+        out.append((torch.stack(ys), s.k_cache, s.v_cache))
+    for a, b in zip(*out):
+        assert torch.isfinite(a).all() and torch.equal(a, b)
